@@ -6,8 +6,8 @@
 // net and block and the block weights.  A pair's result is the source side
 // X of its region (built by flow_regions_build): a region vertex of block i
 // outside X moves to block j, one of block j inside X to block i.  The
-// sequences are applied one after another in the given order by one
-// workgroup: moves whose vertex left its expected block are dropped; if
+// result is that of applying the sequences one after another in the given
+// order: moves whose vertex left its expected block are dropped; if
 // blocks i or j would exceed Lmax nothing is applied; otherwise every move
 // is applied and the exact change of sum w(e) (lambda(e) - 1) is summed from
 // the pin-count transitions (a count of the source block dropping to zero
@@ -41,7 +41,6 @@ struct fp_partition {
 namespace hf {
 namespace {
 
-constexpr int kMvBlock = 1024;
 
 size_t mv_align(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -104,128 +103,166 @@ __global__ void k_mv_offsets(const int32_t* keys, long long count, int n, int32_
   }
 }
 
-// phi(e, b) and block weights from the partition
-__global__ void k_mv_counts(fp_partition pt) {
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < pt.E; e += gridDim.x * blockDim.x)
-    for (int p = pt.off[e]; p < pt.off[e + 1]; ++p)
-      atomicAdd(&pt.phi[(long long)e * pt.k + pt.block[pt.pins[p]]], 1);
-  for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < pt.V; v += gridDim.x * blockDim.x)
-    atomicAdd(&pt.bw[pt.block[v]], (unsigned long long)pt.cv[v]);
+// phi(e, b) and block weights from the partition.  Bound by the atomics: a
+// thread per pin (a thread per net left a wave waiting for its largest net)
+// and the k block weights summed in LDS first, since every vertex adds into
+// the same few words (2,000,000 vertices, 10 M pins, k = 64: 4.83 -> 0.62 ms).
+// dynamic LDS: k block weights
+__global__ void __launch_bounds__(256) k_mv_counts(fp_partition pt, const int32_t* pin_net) {
+  extern __shared__ unsigned long long mv_bw[];
+  for (int b = threadIdx.x; b < pt.k; b += blockDim.x) mv_bw[b] = 0ull;
+  __syncthreads();
+  const long long t0 = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  const long long ts = (long long)gridDim.x * blockDim.x;
+  for (long long p = t0; p < pt.P; p += ts)
+    atomicAdd(&pt.phi[(long long)pin_net[p] * pt.k + pt.block[pt.pins[p]]], 1);
+  for (long long v = t0; v < pt.V; v += ts)
+    atomicAdd(&mv_bw[pt.block[v]], (unsigned long long)pt.cv[v]);
+  __syncthreads();
+  for (int b = threadIdx.x; b < pt.k; b += blockDim.x)
+    if (mv_bw[b]) atomicAdd(&pt.bw[b], mv_bw[b]);
 }
 
-// objective sum w(e) (lambda(e) - 1), added into *out
-__global__ void k_mv_objective(fp_partition pt, unsigned long long* out) {
+// Lanes that read one net's row of pin counts together: the power of two
+// that holds k, at most a wave.
+__device__ __forceinline__ int mv_row_lanes(int k) {
+  int l = 1;
+  while (l < k && l < 64) l <<= 1;
+  return l;
+}
+
+// objective sum w(e) (lambda(e) - 1), added into *out.  Bound by the E * k
+// pin counts: mv_row_lanes lanes read a net's row together (consecutive
+// words) and count its blocks by a ballot, and a workgroup adds once
+// (2.8 M nets, k = 64: 2.48 -> 0.26 ms against a thread per net's row and an
+// atomic per thread).
+__global__ void __launch_bounds__(256) k_mv_objective(fp_partition pt, unsigned long long* out) {
   unsigned long long acc = 0;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < pt.E; e += gridDim.x * blockDim.x) {
+  const int L = mv_row_lanes(pt.k), lane = __lane_id(), gl = lane & (L - 1);
+  const int per = 64 / L;  // nets of a wave
+  const unsigned long long mine =
+      (L == 64 ? ~0ull : ((1ull << L) - 1ull)) << (lane - gl);
+  const long long nw = (long long)gridDim.x * (blockDim.x >> 6);
+  for (long long e0 = (blockIdx.x * (long long)(blockDim.x >> 6) + (threadIdx.x >> 6)) * per;
+       e0 < pt.E; e0 += nw * per) {
+    const long long e = e0 + lane / L;
     int lam = 0;
-    for (int b = 0; b < pt.k; ++b) lam += pt.phi[(long long)e * pt.k + b] > 0;
-    if (lam > 1) acc += (unsigned long long)pt.w[e] * (unsigned long long)(lam - 1);
+    for (int b0 = 0; b0 < pt.k; b0 += L) {
+      const int b = b0 + gl;
+      const bool has = e < pt.E && b < pt.k && pt.phi[e * pt.k + b] > 0;
+      lam += __popcll(__ballot(has) & mine);
+    }
+    if (gl == 0 && lam > 1) acc += (unsigned long long)pt.w[e] * (unsigned long long)(lam - 1);
   }
-  if (acc) atomicAdd(out, acc);
+  block_add_u64(out, acc);
 }
 
-// Workgroup sum of one value per thread (block-uniform).
-__device__ long long mv_sum(long long v) {
-  __shared__ long long part[kMvBlock / 64];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  const int wid = threadIdx.x >> 6;
-  if (__lane_id() == 0) part[wid] = v;
-  __syncthreads();
-  long long s = 0;
-  for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s += part[i];
-  __syncthreads();
-  return s;
-}
-
+// The sequences of pairs that share no block are independent: a sequence
+// reads and writes only the vertices whose block was i or j when the regions
+// were built, the pin counts phi(., i) and phi(., j) and the weights of
+// blocks i and j.  The host therefore groups the tried pairs into stages -- a
+// pair's stage is one past the last stage that held block i or j -- and a
+// stage's pairs run side by side, several workgroups each, in three launches
+// (weights, moves, undo): the outcome is that of the given order.  One
+// workgroup walking the pairs in order waited on a chain of dependent atomics
+// with one CU busy (500 pairs of 64 blocks, 69 stages: 91.2 -> 2.9 ms).
 struct MvSeq {
-  int32_t npairs;
   const int32_t* pairs;        // 2 per pair
   const long long* vbase;      // per pair: first region vertex
   const long long* nloc;       // per pair: region vertices
   const int32_t* vgid;
   const int8_t* vside;         // 0 = region of block i, 1 = of block j
   const uint8_t* const* sides; // per pair: device pointer to its source side map
-  const long long* gain_exp;   // per pair
+  const int32_t* stage;        // pairs in stage order
   long long lmax;
-  uint8_t* flag;               // scratch: max n bytes
+  uint8_t* flag;               // per region vertex (indexed from vbase): 1 = move
+  unsigned long long* acc;     // per pair: change of c(V_i), moves, exact gain
   long long* out;              // per pair: status, gain, moves
 };
 
-// One workgroup; the sequences in order.
-__global__ void __launch_bounds__(kMvBlock) k_mv_apply(fp_partition pt, MvSeq s) {
-  for (int q = 0; q < s.npairs; ++q) {
-    if (s.gain_exp[q] <= 0) {
-      if (threadIdx.x == 0) {
-        s.out[3 * q] = 0;
-        s.out[3 * q + 1] = 0;
-        s.out[3 * q + 2] = 0;
-      }
-      continue;
+// Stage pair blockIdx.y, part blockIdx.x of its vertices: which moves are
+// still possible, and what they do to the block weights.
+__global__ void __launch_bounds__(256) k_mv_select(fp_partition pt, MvSeq s, int first) {
+  const int q = s.stage[first + blockIdx.y];
+  const int i = s.pairs[2 * q], j = s.pairs[2 * q + 1];
+  const long long vb = s.vbase[q];
+  const int n = (int)s.nloc[q];
+  const uint8_t* side = s.sides[q];
+  long long dwi = 0, cnt = 0;
+  for (int l = blockIdx.x * blockDim.x + threadIdx.x; l < n; l += gridDim.x * blockDim.x) {
+    const int u = s.vgid[vb + l];
+    const int exp = s.vside[vb + l] ? j : i;
+    const int to = side[l] ? i : j;
+    const bool mv = to != exp && pt.block[u] == exp;
+    s.flag[vb + l] = mv ? 1 : 0;
+    if (mv) {
+      dwi += to == i ? (long long)pt.cv[u] : -(long long)pt.cv[u];
+      ++cnt;
     }
-    const int i = s.pairs[2 * q], j = s.pairs[2 * q + 1];
-    const long long vb = s.vbase[q];
-    const int n = (int)s.nloc[q];
-    const uint8_t* side = s.sides[q];
-    long long dwi = 0, cnt = 0;
-    for (int l = threadIdx.x; l < n; l += blockDim.x) {
-      const int u = s.vgid[vb + l];
-      const int exp = s.vside[vb + l] ? j : i;
-      const int to = side[l] ? i : j;
-      const bool mv = to != exp && pt.block[u] == exp;
-      s.flag[l] = mv ? 1 : 0;
-      if (mv) {
-        dwi += to == i ? (long long)pt.cv[u] : -(long long)pt.cv[u];
-        ++cnt;
-      }
+  }
+  block_add_u64(&s.acc[3 * q], (unsigned long long)dwi, &s.acc[3 * q + 1],
+                (unsigned long long)cnt);
+}
+
+// Applies the moves unless block i or j would exceed Lmax and sums the gain.
+__global__ void __launch_bounds__(256) k_mv_move(fp_partition pt, MvSeq s, int first) {
+  const int q = s.stage[first + blockIdx.y];
+  const int i = s.pairs[2 * q], j = s.pairs[2 * q + 1];
+  const long long vb = s.vbase[q];
+  const int n = (int)s.nloc[q];
+  const long long dwi = (long long)s.acc[3 * q];
+  const long long wi = (long long)pt.bw[i] + dwi, wj = (long long)pt.bw[j] - dwi;
+  const bool fits = wi <= s.lmax && wj <= s.lmax;  // block-uniform
+  if (blockIdx.x == 0 && threadIdx.x == 0) s.out[3 * q] = fits ? 1 : 2;
+  if (!fits) return;
+  long long gain = 0;
+  for (int l = blockIdx.x * blockDim.x + threadIdx.x; l < n; l += gridDim.x * blockDim.x) {
+    if (!s.flag[vb + l]) continue;
+    const int u = s.vgid[vb + l];
+    const int frm = s.vside[vb + l] ? j : i, to = frm == i ? j : i;
+    pt.block[u] = to;
+    for (int x = pt.voff[u]; x < pt.voff[u + 1]; ++x) {
+      const int e = pt.vnet[x];
+      const long long base = (long long)e * pt.k;
+      if (atomicSub(&pt.phi[base + frm], 1) == 1) gain += pt.w[e];
+      if (atomicAdd(&pt.phi[base + to], 1) == 0) gain -= pt.w[e];
     }
-    dwi = mv_sum(dwi);
-    cnt = mv_sum(cnt);
-    const long long wi = (long long)pt.bw[i] + dwi, wj = (long long)pt.bw[j] - dwi;
-    if (wi > s.lmax || wj > s.lmax) {
-      if (threadIdx.x == 0) {
-        s.out[3 * q] = 2;
-        s.out[3 * q + 1] = 0;
-        s.out[3 * q + 2] = 0;
-      }
-      continue;
-    }
-    long long gain = 0;
-    for (int l = threadIdx.x; l < n; l += blockDim.x) {
-      if (!s.flag[l]) continue;
+  }
+  block_add_u64(&s.acc[3 * q + 2], (unsigned long long)gain);
+}
+
+// Undoes the moves of a sequence with a negative gain; else takes over the
+// block weights.
+__global__ void __launch_bounds__(256) k_mv_settle(fp_partition pt, MvSeq s, int first) {
+  const int q = s.stage[first + blockIdx.y];
+  const int i = s.pairs[2 * q], j = s.pairs[2 * q + 1];
+  const long long vb = s.vbase[q];
+  const int n = (int)s.nloc[q];
+  const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+  const long long gain = (long long)s.acc[3 * q + 2];
+  // a rejected sequence moved nothing: gain 0, no moves
+  const bool moved = s.acc[3 * q + 1] != 0ull && s.out[3 * q] != 2;
+  if (gain < 0) {
+    for (int l = blockIdx.x * blockDim.x + threadIdx.x; l < n; l += gridDim.x * blockDim.x) {
+      if (!s.flag[vb + l]) continue;
       const int u = s.vgid[vb + l];
       const int frm = s.vside[vb + l] ? j : i, to = frm == i ? j : i;
-      pt.block[u] = to;
+      pt.block[u] = frm;
       for (int x = pt.voff[u]; x < pt.voff[u + 1]; ++x) {
-        const int e = pt.vnet[x];
-        const long long base = (long long)e * pt.k;
-        if (atomicSub(&pt.phi[base + frm], 1) == 1) gain += pt.w[e];
-        if (atomicAdd(&pt.phi[base + to], 1) == 0) gain -= pt.w[e];
+        const long long base = (long long)pt.vnet[x] * pt.k;
+        atomicSub(&pt.phi[base + to], 1);
+        atomicAdd(&pt.phi[base + frm], 1);
       }
     }
-    gain = mv_sum(gain);
-    if (gain < 0) {
-      for (int l = threadIdx.x; l < n; l += blockDim.x) {
-        if (!s.flag[l]) continue;
-        const int u = s.vgid[vb + l];
-        const int frm = s.vside[vb + l] ? j : i, to = frm == i ? j : i;
-        pt.block[u] = frm;
-        for (int x = pt.voff[u]; x < pt.voff[u + 1]; ++x) {
-          const long long base = (long long)pt.vnet[x] * pt.k;
-          atomicSub(&pt.phi[base + to], 1);
-          atomicAdd(&pt.phi[base + frm], 1);
-        }
-      }
-    } else if (threadIdx.x == 0) {
-      pt.bw[i] = (unsigned long long)wi;
-      pt.bw[j] = (unsigned long long)wj;
-    }
-    if (threadIdx.x == 0) {
-      s.out[3 * q] = gain < 0 ? 3 : 1;
-      s.out[3 * q + 1] = gain;
-      s.out[3 * q + 2] = cnt;
-    }
-    __syncthreads();
+  } else if (lead && moved) {
+    const unsigned long long dwi = s.acc[3 * q];
+    pt.bw[i] += dwi;
+    pt.bw[j] -= dwi;
+  }
+  if (lead) {
+    if (gain < 0) s.out[3 * q] = 3;
+    s.out[3 * q + 1] = gain;
+    s.out[3 * q + 2] = moved ? (long long)s.acc[3 * q + 1] : 0;
   }
 }
 
@@ -365,7 +402,8 @@ static fp_status partition_create(int32_t V, int32_t E, const int32_t* off_in,
   k_mv_zero<<<mv_grid((long long)E * k), 256, 0, s>>>(reinterpret_cast<uint32_t*>(pt->phi),
                                                       (long long)E * k);
   k_mv_zero<<<1, 64, 0, s>>>(reinterpret_cast<uint32_t*>(pt->bw), 2ll * k);
-  k_mv_counts<<<mv_grid(std::max(E, V)), 256, 0, s>>>(*pt);
+  k_mv_counts<<<std::min(2048, mv_grid(std::max<long long>(P, V))), 256, k * 8ull, s>>>(*pt,
+                                                                                      pin_net);
   MV_TRY(hipStreamSynchronize(s), "counting the pins per block");
   *out = pt.release();
   return FP_OK;
@@ -377,8 +415,30 @@ static fp_status partition_apply(fp_partition* pt, const fp_regions* rg,
                                  int32_t* moved) {
   const int npairs = rg->npairs;
   if (npairs == 0) return FP_OK;
-  long long nmax = 1;
-  for (int q = 0; q < npairs; ++q) nmax = std::max(nmax, rg->nloc[q]);
+  // stages of pairs that share no block, in the given order along every block
+  std::vector<int32_t> stage_of(npairs, -1), free_at(pt->k, 0);
+  int nstages = 0;
+  long long nv = 0;
+  for (int q = 0; q < npairs; ++q) {
+    nv = std::max(nv, rg->vtx_base[q] + rg->nloc[q]);
+    if (gains[q] <= 0) continue;  // no improvement expected: not tried
+    int32_t &fi = free_at[rg->pairs[2 * q]], &fj = free_at[rg->pairs[2 * q + 1]];
+    stage_of[q] = std::max(fi, fj);
+    fi = fj = stage_of[q] + 1;
+    nstages = std::max(nstages, stage_of[q] + 1);
+  }
+  std::vector<int32_t> first(nstages + 1, 0), order;
+  std::vector<long long> nmax(nstages, 1);
+  for (int q = 0; q < npairs; ++q)
+    if (stage_of[q] >= 0) {
+      ++first[stage_of[q] + 1];
+      nmax[stage_of[q]] = std::max(nmax[stage_of[q]], rg->nloc[q]);
+    }
+  for (int t = 0; t < nstages; ++t) first[t + 1] += first[t];
+  order.resize(first[nstages]);
+  std::vector<int32_t> fill(first.begin(), first.end());
+  for (int q = 0; q < npairs; ++q)
+    if (stage_of[q] >= 0) order[fill[stage_of[q]]++] = q;
   void* mem = nullptr;
   size_t bytes = 0;
   std::vector<size_t> at;
@@ -390,21 +450,21 @@ static fp_status partition_apply(fp_partition* pt, const fp_regions* rg,
   add(npairs * 8ull);   // 1 vbase
   add(npairs * 8ull);   // 2 nloc
   add(npairs * 8ull);   // 3 side pointers
-  add(npairs * 8ull);   // 4 expected gains
-  add((size_t)nmax);    // 5 flags
-  add(npairs * 24ull);  // 6 out
+  add(npairs * 4ull);   // 4 pairs in stage order
+  add((size_t)nv);      // 5 flags
+  add(npairs * 48ull);  // 6 sums, then out
   MV_TRY(hipMalloc(&mem, bytes), "allocating");
   std::unique_ptr<void, void (*)(void*)> guard(mem, [](void* p) { (void)hipFree(p); });
   char* b = static_cast<char*>(mem);
   MvSeq q{};
-  q.npairs = npairs;
   q.pairs = reinterpret_cast<int32_t*>(b + at[0]);
   q.vbase = reinterpret_cast<long long*>(b + at[1]);
   q.nloc = reinterpret_cast<long long*>(b + at[2]);
   q.sides = reinterpret_cast<const uint8_t* const*>(b + at[3]);
-  q.gain_exp = reinterpret_cast<long long*>(b + at[4]);
+  q.stage = reinterpret_cast<int32_t*>(b + at[4]);
   q.flag = reinterpret_cast<uint8_t*>(b + at[5]);
-  q.out = reinterpret_cast<long long*>(b + at[6]);
+  q.acc = reinterpret_cast<unsigned long long*>(b + at[6]);
+  q.out = reinterpret_cast<long long*>(b + at[6]) + 3ll * npairs;
   q.vgid = rg->vgid;
   q.vside = rg->vside;
   q.lmax = lmax;
@@ -415,8 +475,26 @@ static fp_status partition_apply(fp_partition* pt, const fp_regions* rg,
   MV_TRY(hipMemcpyAsync(b + at[2], rg->nloc.data(), npairs * 8ull, hipMemcpyHostToDevice, s),
          "copy");
   MV_TRY(hipMemcpyAsync(b + at[3], sides, npairs * 8ull, hipMemcpyHostToDevice, s), "copy");
-  MV_TRY(hipMemcpyAsync(b + at[4], gains, npairs * 8ull, hipMemcpyHostToDevice, s), "copy");
-  k_mv_apply<<<1, kMvBlock, 0, s>>>(*pt, q);
+  if (!order.empty())
+    MV_TRY(hipMemcpyAsync(b + at[4], order.data(), order.size() * 4ull, hipMemcpyHostToDevice, s),
+           "copy");
+  k_mv_zero<<<mv_grid(12ll * npairs), 256, 0, s>>>(reinterpret_cast<uint32_t*>(q.acc),
+                                                   12ll * npairs);
+  // A vertex holds a few nets and each costs two dependent atomics, so a
+  // thread takes one vertex until a stage alone fills the chip.
+  for (int t = 0; t < nstages; ++t) {
+    const int np = first[t + 1] - first[t];
+    for (int f = 0; f < np; f += 65535) {  // grid y limit
+      const int m = std::min(65535, np - f);
+      const dim3 grid((unsigned)std::max<long long>(
+                          1, std::min<long long>((nmax[t] + 255) / 256, 1 + 8192 / m)),
+                      (unsigned)m);
+      k_mv_select<<<grid, 256, 0, s>>>(*pt, q, first[t] + f);
+      k_mv_move<<<grid, 256, 0, s>>>(*pt, q, first[t] + f);
+      k_mv_settle<<<grid, 256, 0, s>>>(*pt, q, first[t] + f);
+    }
+  }
+  MV_TRY(hipGetLastError(), "applying the moves");
   std::vector<long long> res(3ull * npairs);
   MV_TRY(hipMemcpyAsync(res.data(), q.out, 24ull * npairs, hipMemcpyDeviceToHost, s), "reading");
   MV_TRY(hipStreamSynchronize(s), "applying the moves");

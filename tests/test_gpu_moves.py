@@ -145,3 +145,20 @@ def test_refine_rounds_vs_oracle(hf, merge):
     assert traj.tolist() == list(ref_traj)
     assert (blocks == ref_block).all()
     assert res["objective_after"] == obj == ref_traj[-1] < ref_traj[0]
+
+
+@pytest.mark.parametrize("k", [2, 3, 17, 64, 65, 300])
+def test_partition_counts_and_objective(hf, k):
+    """Pin counts, block weights and the objective of a random partition for
+    block counts around the lane groups that read a net's row together."""
+    from oracle import moves as omoves
+    hg = inputs.uniform_hypergraph(k, num_vertices=1501, num_nets=2203)
+    rng = np.random.default_rng(k)
+    block = rng.integers(0, k, hg.num_vertices).astype(np.int32)
+    vw = rng.integers(1, 9, hg.num_vertices).astype(np.int32)
+    with hf.FlowPartition(hg.num_vertices, hg.net_offsets, hg.pins, hg.net_weights, vw, block,
+                          k) as part:
+        blocks, bw, obj = part.get()
+    assert (blocks == block).all()
+    assert bw.tolist() == np.bincount(block, weights=vw, minlength=k).astype(int).tolist()
+    assert obj == omoves.connectivity(hg, block)

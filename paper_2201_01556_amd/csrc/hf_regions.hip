@@ -138,11 +138,6 @@ __global__ void k_rg_check_rest(int V, int P, int k, const int32_t* pins, const 
   if (e_) atomicOr(err, e_);
 }
 
-__global__ void k_rg_pin_net(int E, const int32_t* off, int32_t* pin_net) {
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < E; e += gridDim.x * blockDim.x)
-    for (int p = off[e]; p < off[e + 1]; ++p) pin_net[p] = e;
-}
-
 // off[x] = first sorted position holding a key >= x, for x in [0, n]
 __global__ void k_rg_offsets(const int32_t* keys, int count, int n, int32_t* offs) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i <= count; i += gridDim.x * blockDim.x) {
@@ -152,18 +147,58 @@ __global__ void k_rg_offsets(const int32_t* keys, int count, int n, int32_t* off
   }
 }
 
+// {block, block-local id} of every vertex, together because a pin lookup
+// needs both and each scattered read moves a whole line.
 __global__ void k_rg_local(int V, const int32_t* bverts, const int32_t* bkeys,
-                           const int32_t* boff, int32_t* blocal) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < V; i += gridDim.x * blockDim.x)
-    blocal[bverts[i]] = i - boff[bkeys[i]];
+                           const int32_t* boff, int2* bl) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < V; i += gridDim.x * blockDim.x) {
+    const int b = bkeys[i];
+    bl[bverts[i]] = make_int2(b, i - boff[b]);
+  }
 }
 
-__global__ void k_rg_masks(int E, const int32_t* off, const int32_t* pins, const int32_t* block,
-                           unsigned long long* mask) {
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < E; e += gridDim.x * blockDim.x) {
-    unsigned long long m = 0ull;
-    for (int p = off[e]; p < off[e + 1]; ++p) m |= 1ull << block[pins[p]];
-    mask[e] = m;
+// weight of block blockIdx.x
+__global__ void __launch_bounds__(1024) k_rg_block_weights(const int32_t* bverts,
+                                                           const int32_t* boff, const int32_t* cv,
+                                                           unsigned long long* bw) {
+  if (threadIdx.x == 0) bw[blockIdx.x] = 0ull;
+  unsigned long long sum = 0ull;
+  for (int i = boff[blockIdx.x] + threadIdx.x; i < boff[blockIdx.x + 1]; i += blockDim.x)
+    sum += (unsigned long long)cv[bverts[i]];
+  __syncthreads();
+  block_add_u64(&bw[blockIdx.x], sum);
+}
+
+// Net of every pin and the blocks of every net, a wave per 64 nets with
+// their pins spread over its lanes (a thread per net left its wave walking a
+// 2,000-pin net alone: 1.23 + 0.52 -> 0.16 ms for 2.8 M nets of 10 M pins).
+__global__ void __launch_bounds__(256) k_rg_pins(int E, const int32_t* off, const int32_t* pins,
+                                                 const int32_t* block, int32_t* pin_net,
+                                                 unsigned long long* mask) {
+  __shared__ unsigned long long slots[256];
+  const int lane = __lane_id();
+  unsigned long long* mine = slots + (threadIdx.x & ~63u);
+  const int nwaves = gridDim.x * (blockDim.x >> 6);
+  for (int base = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64; base < E;
+       base += nwaves * 64) {
+    const int e = base + lane;
+    const int end = off[min(e, E - 1) + 1], first = off[base];
+    mine[lane] = 0ull;
+    const int last = __shfl(end, 63);
+    for (int p0 = first; p0 < last; p0 += 64) {
+      const int p = p0 + lane;
+      // owner: the first net whose end lies beyond p
+      int lo = -1;
+#pragma unroll
+      for (int st = 32; st > 0; st >>= 1)
+        if (__shfl(end, lo + st) <= p) lo += st;
+      ++lo;
+      if (p < last) {
+        pin_net[p] = base + lo;
+        atomicOr(&mine[lo], 1ull << block[pins[p]]);
+      }
+    }
+    if (e < E) mask[e] = mine[lane];
   }
 }
 
@@ -183,13 +218,13 @@ struct RgGraph {
   const int32_t* pins;
   const int32_t* w;
   const int32_t* cv;      // vertex weights
-  const int32_t* block;
   const int32_t* voff;    // vertex -> nets
   const int32_t* vnet;
   const int32_t* bverts;  // vertices by block, increasing id
   const int32_t* boff;
-  const int32_t* blocal;
+  const int2* bl;         // {block, block-local id} of every vertex
   const unsigned long long* mask;
+  const unsigned long long* bw;  // block weights
 };
 
 struct RgSide {
@@ -205,9 +240,55 @@ struct RgSide {
   long long* out;             // per side: weight, count, boundary, c(block)
 };
 
+// Level 0 of every pair side: the pins in block b of a net that also holds
+// block o, for every requested side (b, o).  One pass over the pins, a thread
+// each (a large net's pins meet up to 63 other blocks, so its pins are spread
+// widely); the sides of a block pair are chained from head[b * k + o].  (Each
+// side looking through all nets of its block's vertices read 160 M net masks
+// for 1,000 sides.)
+__global__ void __launch_bounds__(256) k_rg_seed(RgGraph g, RgSide r, int P,
+                                                 const int32_t* pin_net, int k,
+                                                 const int32_t* head, const int32_t* next) {
+  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < P; p += gridDim.x * blockDim.x) {
+    unsigned long long mo = g.mask[pin_net[p]];
+    if (!(mo & (mo - 1ull))) continue;
+    const int2 y = g.bl[g.pins[p]];
+    const uint32_t bit = 1u << (y.y & 31);
+    for (mo &= ~(1ull << y.x); mo; mo &= mo - 1ull) {
+      for (int s = head[y.x * k + __builtin_ctzll(mo)]; s >= 0; s = next[s]) {
+        const int words = (g.boff[y.x + 1] - g.boff[y.x] + 31) >> 5;
+        uint32_t* vis = r.bits + r.bits_at[s];
+        if (vis[y.y >> 5] & bit) continue;  // a stale word only repeats the marks
+        atomicOr(&vis[y.y >> 5], bit);
+        atomicOr(&vis[words + (y.y >> 5)], bit);
+      }
+    }
+  }
+}
+
+// largest t < n with off[t] <= a (off[0] = 0)
+__device__ __forceinline__ int rg_tile_owner(const int* off, int n, int a) {
+  int lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (off[mid] <= a) lo = mid;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// The levels after level 0 (in the next-level bitmap at the start).  A side
+// is a chain of dependent scattered reads (vertex -> nets -> pins -> block
+// and visited bit), so a level's arcs are spread over the whole workgroup
+// twice: a thread per (added vertex, net) claims the nets not expanded yet,
+// then a thread per pin of the claimed nets marks what it reaches.  1,000
+// sides of 31,250-vertex blocks: 10.05 -> 3.46 ms (and 0.67 for k_rg_seed), against a
+// wave per vertex walking its nets one after another.
 __global__ void __launch_bounds__(kRegBlock) k_rg_grow(RgGraph g, RgSide r) {
+  __shared__ int t_beg[kRegBlock], t_off[kRegBlock + 1];  // vertices of a chunk: nets
+  __shared__ int n_beg[kRegBlock], n_off[kRegBlock + 1];  // claimed nets of a step: pins
   const int s = blockIdx.x, q = s >> 1, side = s & 1;
-  const int blk = r.pairs[2 * q + side], oth = r.pairs[2 * q + 1 - side];
+  const int blk = r.pairs[2 * q + side];
   const long long cap_w = r.caps[2 * q + side];
   const int nb = g.boff[blk + 1] - g.boff[blk];
   const long long cap_n = (long long)nb - 1;
@@ -218,24 +299,8 @@ __global__ void __launch_bounds__(kRegBlock) k_rg_grow(RgGraph g, RgSide r) {
   uint32_t* added = nq + words;
   int32_t* lev = r.lev + r.lev_at[s];
   uint32_t* xm = r.xmark + (long long)s * r.xwords;
-  const int lane = __lane_id(), wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int tid = threadIdx.x;
 
-  // block weight; level 0: the block's vertices on a net with a pin in the
-  // other block of the pair (every net of a block vertex has a pin in the
-  // block), i.e. its pins on the nets cut between the two blocks
-  long long bw = 0;
-  for (int l = threadIdx.x; l < nb; l += blockDim.x) {
-    const int u = bv[l];
-    bw += g.cv[u];
-    for (int a = g.voff[u]; a < g.voff[u + 1]; ++a)
-      if ((g.mask[g.vnet[a]] >> oth) & 1ull) {
-        atomicOr(&vis[l >> 5], 1u << (l & 31));
-        atomicOr(&nq[l >> 5], 1u << (l & 31));
-        break;
-      }
-  }
-  long long bw_tot = 0;
-  rg_scan_i64(bw, &bw_tot);
   long long wsum = 0, cnt = 0, boundary = -1;
   while (true) {
     const int L = rg_compact_bits(nq, words, lev, true);
@@ -245,7 +310,7 @@ __global__ void __launch_bounds__(kRegBlock) k_rg_grow(RgGraph g, RgSide r) {
     // positive, so those that fit in a chunk form its prefix
     bool stop = false;
     for (int b0 = 0; b0 < L; b0 += blockDim.x) {
-      const int i = b0 + (int)threadIdx.x;
+      const int i = b0 + tid;
       const int chunk = min((int)blockDim.x, L - b0);
       const long long c = i < L ? (long long)g.cv[bv[lev[i]]] : 0ll;
       long long tot = 0;
@@ -263,36 +328,56 @@ __global__ void __launch_bounds__(kRegBlock) k_rg_grow(RgGraph g, RgSide r) {
       }
     }
     if (stop) break;  // the growth ends at the first vertex that does not fit
-    __syncthreads();
-    // next level: a wave per added vertex, its lanes over the pins of each of
-    // its nets that this side has not expanded yet
-    for (int a = wid; a < L; a += nw) {
-      const int u = bv[lev[a]];
-      for (int x = g.voff[u]; x < g.voff[u + 1]; ++x) {
-        const int e = g.vnet[x];
-        uint32_t old = 0;
-        if (lane == 0) old = atomicOr(&xm[e >> 5], 1u << (e & 31));
-        old = __shfl(old, 0);
-        if (old & (1u << (e & 31))) continue;
-        for (int p = g.off[e] + lane; p < g.off[e + 1]; p += 64) {
-          const int y = g.pins[p];
-          if (g.block[y] != blk) continue;
-          const int l = g.blocal[y];
-          const uint32_t bit = 1u << (l & 31);
-          if (!(__atomic_load_n(&vis[l >> 5], __ATOMIC_RELAXED) & bit)) {
-            const uint32_t o = atomicOr(&vis[l >> 5], bit);
-            if (!(o & bit)) atomicOr(&nq[l >> 5], bit);
+    for (int c0 = 0; c0 < L; c0 += blockDim.x) {
+      const int nt = min((int)blockDim.x, L - c0);
+      int beg = 0, deg = 0;
+      if (tid < nt) {
+        const int u = bv[lev[c0 + tid]];
+        beg = g.voff[u];
+        deg = g.voff[u + 1] - beg;
+      }
+      long long arcs = 0;
+      const int incl = (int)rg_scan_i64(deg, &arcs);
+      t_beg[tid] = beg;
+      t_off[tid] = incl - deg;
+      __syncthreads();
+      for (int a0 = 0; a0 < (int)arcs; a0 += blockDim.x) {
+        const int a = a0 + tid;
+        int nbeg = 0, size = 0;
+        if (a < (int)arcs) {
+          const int o = rg_tile_owner(t_off, nt, a);
+          const int e = g.vnet[t_beg[o] + (a - t_off[o])];
+          const uint32_t bit = 1u << (e & 31);
+          if (!(atomicOr(&xm[e >> 5], bit) & bit)) {
+            nbeg = g.off[e];
+            size = g.off[e + 1] - nbeg;
           }
         }
+        long long np = 0;
+        const int pincl = (int)rg_scan_i64(size, &np);
+        n_beg[tid] = nbeg;
+        n_off[tid] = pincl - size;
+        __syncthreads();
+        for (int p = tid; p < (int)np; p += blockDim.x) {
+          const int o = rg_tile_owner(n_off, blockDim.x, p);
+          const int2 y = g.bl[g.pins[n_beg[o] + (p - n_off[o])]];
+          if (y.x != blk) continue;
+          const uint32_t bit = 1u << (y.y & 31);
+          if (!(__atomic_load_n(&vis[y.y >> 5], __ATOMIC_RELAXED) & bit)) {
+            const uint32_t old = atomicOr(&vis[y.y >> 5], bit);
+            if (!(old & bit)) atomicOr(&nq[y.y >> 5], bit);
+          }
+        }
+        __syncthreads();  // the tiles are rewritten
       }
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     r.out[4 * s + 0] = wsum;
     r.out[4 * s + 1] = cnt;
     r.out[4 * s + 2] = boundary;
-    r.out[4 * s + 3] = bw_tot;
+    r.out[4 * s + 3] = (long long)g.bw[blk];
   }
 }
 
@@ -403,7 +488,8 @@ struct RgNets {
 // (t).
 __device__ __forceinline__ int rg_classify(const RgGraph& g, const RgSide& r, const int32_t* lmap,
                                            int q, int y, int* lid, bool* in_i) {
-  const int b = g.block[y];
+  const int2 yb = g.bl[y];
+  const int b = yb.x;
   const int i = r.pairs[2 * q], j = r.pairs[2 * q + 1];
   if (b != i && b != j) return 0;
   const int side = b == i ? 0 : 1;
@@ -411,7 +497,7 @@ __device__ __forceinline__ int rg_classify(const RgGraph& g, const RgSide& r, co
   const int nb = g.boff[b + 1] - g.boff[b];
   const int words = (nb + 31) >> 5;
   const uint32_t* added = r.bits + r.bits_at[s] + 2ll * words;
-  const int l = g.blocal[y];
+  const int l = yb.y;
   *in_i = side == 0;
   if ((added[l >> 5] >> (l & 31)) & 1u) {
     *lid = lmap[r.lev_at[s] + l];
@@ -1029,8 +1115,9 @@ fp_status regions_build(int32_t V, int32_t E, const int32_t* off_in, const int32
   }
 
   // vertex -> nets (stable radix sort of the pins by vertex, values = nets)
-  int32_t *pin_net, *vkeys, *vnet, *voff, *bkeys, *bverts, *boff, *blocal, *iota;
-  unsigned long long* mask;
+  int32_t *pin_net, *vkeys, *vnet, *voff, *bkeys, *bverts, *boff;
+  int2* bl;
+  unsigned long long *mask, *bweight;
   RG_TRY(sc.get((size_t)P, &pin_net), "allocating");
   RG_TRY(sc.get((size_t)P, &vkeys), "allocating");
   RG_TRY(sc.get((size_t)P, &vnet), "allocating");
@@ -1038,10 +1125,10 @@ fp_status regions_build(int32_t V, int32_t E, const int32_t* off_in, const int32
   RG_TRY(sc.get((size_t)V, &bkeys), "allocating");
   RG_TRY(sc.get((size_t)V, &bverts), "allocating");
   RG_TRY(sc.get(k + 1ull, &boff), "allocating");
-  RG_TRY(sc.get((size_t)V, &blocal), "allocating");
-  RG_TRY(sc.get((size_t)V, &iota), "allocating");
+  RG_TRY(sc.get((size_t)V, &bl), "allocating");
+  RG_TRY(sc.get((size_t)k, &bweight), "allocating");
   RG_TRY(sc.get((size_t)E, &mask), "allocating");
-  k_rg_pin_net<<<rg_grid(E), 256, 0, s>>>(E, off, pin_net);
+  if (E) k_rg_pins<<<rg_grid(E), 256, 0, s>>>(E, off, pins, block, pin_net, mask);
   {
     const unsigned vb = rg_bits(V);
     size_t tb = 0;
@@ -1064,9 +1151,9 @@ fp_status regions_build(int32_t V, int32_t E, const int32_t* off_in, const int32
     RG_TRY(rocprim::radix_sort_pairs(tmp, tb, block, bkeys, cnt, bverts, (size_t)V, 0u, kb, s),
            "sorting the vertices by block");
     k_rg_offsets<<<rg_grid(V + 1ll), 256, 0, s>>>(bkeys, V, k, boff);
-    k_rg_local<<<rg_grid(V), 256, 0, s>>>(V, bverts, bkeys, boff, blocal);
+    k_rg_local<<<rg_grid(V), 256, 0, s>>>(V, bverts, bkeys, boff, bl);
+    k_rg_block_weights<<<k, 1024, 0, s>>>(bverts, boff, cv, bweight);
   }
-  k_rg_masks<<<rg_grid(E), 256, 0, s>>>(E, off, pins, block, mask);
   std::vector<int32_t> boff_h(k + 1);
   RG_TRY(hipMemcpyAsync(boff_h.data(), boff, (k + 1) * 4ull, hipMemcpyDeviceToHost, s), "reading");
   RG_TRY(hipStreamSynchronize(s), "preparing the hypergraph");
@@ -1120,8 +1207,20 @@ fp_status regions_build(int32_t V, int32_t E, const int32_t* off_in, const int32
   k_rg_zero<<<rg_grid(bw, 256), 256, 0, s>>>(bits, bw);
   k_rg_zero<<<4096, 256, 0, s>>>(xmark, (long long)S * xwords);
 
-  RgGraph g{V, E, off, pins, w, cv, block, voff, vnet, bverts, boff, blocal, mask};
+  RgGraph g{V, E, off, pins, w, cv, voff, vnet, bverts, boff, bl, mask, bweight};
   RgSide rs{pairs_d, caps_d, bits_at_d, lev_at_d, bits, lev, xmark, xwords, side_out};
+  // sides of each ordered block pair, chained (a pair may be asked for twice)
+  std::vector<int32_t> chain((size_t)k * k + S, -1);
+  for (int t = 0; t < S; ++t) {
+    int32_t& h = chain[(size_t)pairs[t] * k + pairs[t ^ 1]];
+    chain[(size_t)k * k + t] = h;
+    h = t;
+  }
+  int32_t* chain_d;
+  RG_TRY(sc.get(chain.size(), &chain_d), "allocating");
+  RG_TRY(hipMemcpyAsync(chain_d, chain.data(), chain.size() * 4ull, hipMemcpyHostToDevice, s),
+         "copy");
+  k_rg_seed<<<rg_grid(P), 256, 0, s>>>(g, rs, P, pin_net, k, chain_d, chain_d + (size_t)k * k);
   k_rg_grow<<<S, kRegBlock, 0, s>>>(g, rs);
   std::vector<long long> side_h(4ull * S);
   RG_TRY(hipMemcpyAsync(side_h.data(), side_out, 32ull * S, hipMemcpyDeviceToHost, s), "reading");

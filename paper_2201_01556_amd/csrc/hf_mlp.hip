@@ -8,16 +8,17 @@
 //
 // Hand-written FP32 kernels (plain VALU: the layers are 64 wide and the
 // whole network has 5,057 parameters):
-//   k_norm_stats   column mean and population deviation of log1p(features)
-//                  in float64 (one wave per column)
+//   k_log1p        log1p(features) in float64
+//   k_norm_stats   their column mean and population deviation in float64 (one
+//                  wave per column)
 //   k_norm_apply   z-scored float features
 //   k_fwd_bwd      one workgroup per tile of 64 samples: forward pass with
 //                  parameters and activations in LDS, mean binary
 //                  cross-entropy on logits, backward pass, per-tile partial
-//                  gradients (fixed summation order)
+//                  gradients (fixed summation order); without kGrad the
+//                  forward pass only, sigmoid probabilities
 //   k_reduce_adam  sum of the tile partials in tile order (deterministic),
 //                  optional Adam step (Kingma and Ba)
-//   k_predict      forward pass only, sigmoid probabilities
 //
 // Parameter layout (row-major): W1 [64 x 12], b1 [64], W2 [64 x 64], b2 [64],
 // W3 [64], b3.
@@ -33,7 +34,7 @@ namespace hf {
 constexpr int kIn = 12;
 constexpr int kHid = 64;
 constexpr int kTile = 64;  // samples per workgroup
-constexpr int kMlpThreads = 256;
+constexpr int kMlpThreads = 512;
 constexpr int oW1 = 0;
 constexpr int ob1 = oW1 + kHid * kIn;    // 768
 constexpr int oW2 = ob1 + kHid;          // 832
@@ -42,7 +43,7 @@ constexpr int oW3 = ob2 + kHid;          // 4992
 constexpr int ob3 = oW3 + kHid;          // 5056
 constexpr int kParams = ob3 + 1;         // 5057
 static_assert(kParams == FP_SCORER_PARAMS, "parameter count");
-constexpr int kPart = kParams + 1;       // partial gradients + partial loss
+constexpr int kPart = (kParams + 1 + 3) & ~3;  // partial gradients, partial loss, 16-byte rows
 
 __device__ __forceinline__ double wave_sum_f64(double v) {
 #pragma unroll
@@ -50,17 +51,29 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return v;
 }
 
+// one row of n values per feature column
+__global__ void k_log1p(const int64_t* __restrict__ f, int n, double* __restrict__ lg) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n * kIn) lg[(size_t)(i % kIn) * n + i / kIn] = log1p((double)f[i]);
+}
+
 // One wave per feature column: mean, then the population deviation (two
-// passes, float64); a deviation below 1e-9 counts as a constant column.
-__global__ void __launch_bounds__(kIn * 64) k_norm_stats(const int64_t* __restrict__ f, int n,
+// passes, float64); a deviation below 1e-9 counts as a constant column.  The
+// order of the sums is fixed, so the twelve waves keep their serial chains;
+// the logarithms, which were most of the time, come from k_log1p on the whole
+// chip (12,000 samples: 289 -> 40 us for both kernels).
+__global__ void __launch_bounds__(kIn * 64) k_norm_stats(const double* __restrict__ lg, int n,
                                                          double* __restrict__ ms) {
   const int col = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const double* row = lg + (size_t)col * n;
   double s = 0.0;
-  for (int i = lane; i < n; i += 64) s += log1p((double)f[(size_t)i * kIn + col]);
+#pragma unroll 16
+  for (int i = lane; i < n; i += 64) s += row[i];
   const double mean = wave_sum_f64(s) / (double)n;
   double q = 0.0;
+#pragma unroll 16
   for (int i = lane; i < n; i += 64) {
-    const double d = log1p((double)f[(size_t)i * kIn + col]) - mean;
+    const double d = row[i] - mean;
     q += d * d;
   }
   const double sd = sqrt(wave_sum_f64(q) / (double)n);
@@ -78,143 +91,270 @@ __global__ void k_norm_apply(const int64_t* __restrict__ f, int n, const double*
   x[i] = (float)((log1p((double)f[i]) - ms[col]) / ms[kIn + col]);
 }
 
-// Forward (and with kGrad the backward) pass over one tile of samples.
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+constexpr int kLd = 72;  // row stride of the 64 x 64 LDS matrices: 16-byte rows, and both ways
+                         // of reading an operand (along and across the rows) meet at most two
+                         // lanes per bank
+
+// One wave's 16 x (16 * N) outputs by matrix instructions: c[n] += sum over
+// k of A(row, k) * B(16 n + col, k), k ascending.  An operand's element (i, k)
+// lies at p[i * si + k * sk].  Lane l supplies element (l & 15, k0 + (l >> 4))
+// of both operands of a 16 x 16 x 4 instruction and holds rows
+// 4 (l >> 4) .. + 3 of column l & 15 of the result.  The instruction adds its
+// four products one after another, each rounded like a fused multiply-add
+// (checked against such a chain in k order: no bit differs).
+template <int K, int N>
+__device__ __forceinline__ void mm_16(const float* a, int sia, int ska, const float* b, int sib,
+                                      int skb, f4 (&c)[N]) {
+  const int r = threadIdx.x & 15, q = (threadIdx.x & 63) >> 4;
+  const float* ap = a + r * sia + q * ska;
+  const float* bp = b + r * sib + q * skb;
+#pragma unroll
+  for (int k0 = 0; k0 < K; k0 += 4) {
+    const float x = ap[k0 * ska];
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+      c[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, bp[n * 16 * sib + k0 * skb], c[n], 0, 0, 0);
+  }
+}
+
+// Forward (and with kGrad the backward) pass over one tile of samples;
+// with kGrad x holds the normalized samples, else they are computed here from
+// the raw features f.  A tile is three 64 x 64 x 64 products (two of them
+// backward) and a few sums between barriers, one workgroup per CU, so it is
+// bound by latency and LDS reads: the products run on FP32 matrix
+// instructions (eight waves of 16 units x 32 samples, operands read straight
+// from one row-major copy of each matrix), the loss is one term per sample,
+// and the short serial sums go to different waves.  Every sum keeps its order
+// (k ascending, one accumulator), so results are those of a scalar loop to
+// the bit.  The first form, in which a lane read its own row of W2 (64 lanes
+// on one LDS bank) and one thread recomputed every sample's logit for the
+// loss, took 70.8 us a step (12,000 samples, 188 tiles), 4 x 4 register tiles
+// of vector multiply-adds 21.1, this one 11.9; 500 predictions 14.3 + 4.5
+// (normalization), now 6.2 to 9.5.
 template <bool kGrad>
 __global__ void __launch_bounds__(kMlpThreads)
     k_fwd_bwd(const float* __restrict__ prm, const float* __restrict__ x,
+              const int64_t* __restrict__ f, const double* __restrict__ ms,
               const float* __restrict__ y, int n, float inv_n, float* __restrict__ part,
               float* __restrict__ prob) {
-  __shared__ float P[kParams];
-  __shared__ float X[kTile * kIn];
-  __shared__ float H1[kTile * kHid];
-  __shared__ float H2[kTile * kHid];
-  __shared__ float D2[kTile * kHid];  // dL/dz2, then dL/dz1
-  __shared__ float DZ[kTile];
+  __shared__ __attribute__((aligned(16))) float W1[kHid * kIn];       // [unit][input]
+  __shared__ __attribute__((aligned(16))) float X[kTile * kIn + 16];  // [sample][input]
+  __shared__ __attribute__((aligned(16))) float W2[kHid * kLd];       // [unit][input]
+  __shared__ __attribute__((aligned(16))) float H1[kTile * kLd];      // [sample][unit]
+  __shared__ __attribute__((aligned(16))) float H2[kTile * kLd];      // [sample][unit]; then D1
+  __shared__ __attribute__((aligned(16))) float D2[kGrad ? kTile * kLd : 4];  // dL/dz2
+  __shared__ __attribute__((aligned(16))) float B1[kHid], B2[kHid], W3[kHid];
+  __shared__ float DZ[kTile], LS[kTile];
   const int tid = threadIdx.x;
+  const int lane = tid & 63, wid = tid >> 6;
   const int s0 = blockIdx.x * kTile;
   const int ns = min(kTile, n - s0);
-  for (int i = tid; i < kParams; i += kMlpThreads) P[i] = prm[i];
-  for (int i = tid; i < kTile * kIn; i += kMlpThreads)
-    X[i] = i < ns * kIn ? x[(size_t)s0 * kIn + i] : 0.f;
-  __syncthreads();
-  const int h = tid & (kHid - 1);  // unit of this thread
-  const int sq = tid >> 6;         // first sample (stride 4)
-  // layer 1
-  for (int s = sq; s < kTile; s += 4) {
-    float z = P[ob1 + h];
-#pragma unroll
-    for (int j = 0; j < kIn; ++j) z += P[oW1 + h * kIn + j] * X[s * kIn + j];
-    H1[s * kHid + h] = z > 0.f ? z : 0.f;
+  const float b3 = prm[ob3];
+  for (int i = tid; i < kHid * kHid / 4; i += kMlpThreads)
+    *reinterpret_cast<float4*>(W2 + (i >> 4) * kLd + (i & 15) * 4) =
+        *reinterpret_cast<const float4*>(prm + oW2 + i * 4);
+  for (int i = tid; i < kHid * kIn; i += kMlpThreads) {
+    W1[i] = prm[oW1 + i];
+    float v = 0.f;
+    if (i < ns * kIn) {
+      if (kGrad) v = x[(size_t)s0 * kIn + i];
+      else {
+        const int col = i % kIn;
+        v = (float)((log1p((double)f[(size_t)s0 * kIn + i]) - ms[col]) / ms[kIn + col]);
+      }
+    }
+    X[i] = v;
   }
+  if (tid < kHid) {
+    B1[tid] = prm[ob1 + tid];
+    B2[tid] = prm[ob2 + tid];
+    W3[tid] = prm[oW3 + tid];
+  } else if (tid < kHid + 16) {
+    X[kTile * kIn + tid - kHid] = 0.f;  // read as inputs 12 .. 15 of the last sample
+  }
+  __syncthreads();
+  const int u0 = (wid & 3) * 16;   // this wave's units
+  const int m0 = (wid >> 2) * 32;  // its samples (or inputs)
+  const int col = m0 + (lane & 15), row = u0 + (lane >> 4) * 4;
+  f4 c[2];
+  // c holds units row .. row + 3 of samples col and col + 16
+  auto put_relu = [&](float* m) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c[t][i] = c[t][i] > 0.f ? c[t][i] : 0.f;
+      *reinterpret_cast<f4*>(m + (col + 16 * t) * kLd + row) = c[t];
+    }
+  };
+  // layer 1
+  c[0] = c[1] = *reinterpret_cast<const f4*>(B1 + row);
+  mm_16<kIn>(W1 + u0 * kIn, kIn, 1, X + m0 * kIn, kIn, 1, c);
+  put_relu(H1);
   __syncthreads();
   // layer 2
-  for (int s = sq; s < kTile; s += 4) {
-    float z = P[ob2 + h];
-    for (int k = 0; k < kHid; ++k) z += P[oW2 + h * kHid + k] * H1[s * kHid + k];
-    H2[s * kHid + h] = z > 0.f ? z : 0.f;
-  }
+  c[0] = c[1] = *reinterpret_cast<const f4*>(B2 + row);
+  mm_16<kHid>(W2 + u0 * kLd, kLd, 1, H1 + m0 * kLd, kLd, 1, c);
+  put_relu(H2);
   __syncthreads();
-  // output, dL/dz
+  // output, dL/dz, loss term
   if (tid < kTile) {
     const int s = tid;
-    float z = P[ob3];
-    for (int k = 0; k < kHid; ++k) z += P[oW3 + k] * H2[s * kHid + k];
-    float dz = 0.f;
+    float z = b3;
+#pragma unroll
+    for (int k = 0; k < kHid; k += 4) {
+      const f4 h = *reinterpret_cast<const f4*>(H2 + s * kLd + k);
+      const f4 w = *reinterpret_cast<const f4*>(W3 + k);
+      z += w[0] * h[0];
+      z += w[1] * h[1];
+      z += w[2] * h[2];
+      z += w[3] * h[3];
+    }
+    float dz = 0.f, term = 0.f;
     if (s < ns) {
       const float p = 1.f / (1.f + expf(-z));
       if (prob) prob[s0 + s] = p;
-      if (kGrad) dz = (p - y[s0 + s]) * inv_n;
+      if (kGrad) {
+        const float yy = y[s0 + s];
+        dz = (p - yy) * inv_n;
+        // softplus(z) - y z (without overflow)
+        const float sp = z > 0.f ? z + log1pf(expf(-z)) : log1pf(expf(z));
+        term = sp - yy * z;
+      }
     }
     DZ[s] = dz;
+    LS[s] = term;
   }
   if (!kGrad) return;
   __syncthreads();
   float* out = part + (size_t)blockIdx.x * kPart;
-  // output layer gradients; dL/dz2
-  if (tid < kHid) {
-    float g = 0.f;
-    for (int s = 0; s < kTile; ++s) g += DZ[s] * H2[s * kHid + tid];
-    out[oW3 + tid] = g;
+  // dL/dz2 (c still holds H2)
+  {
+    const f4 w = *reinterpret_cast<const f4*>(W3 + row);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const float dz = DZ[col + 16 * t];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c[t][i] = c[t][i] > 0.f ? dz * w[i] : 0.f;
+      *reinterpret_cast<f4*>(D2 + (col + 16 * t) * kLd + row) = c[t];
+    }
   }
-  if (tid == kHid) {
+  __syncthreads();
+  // W2: units row .. row + 3, inputs col and col + 16, summed over the samples
+  c[0] = c[1] = f4{0.f, 0.f, 0.f, 0.f};
+  mm_16<kTile>(D2 + u0, 1, kLd, H1 + m0, 1, kLd, c);
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[oW2 + (row + i) * kHid + col + 16 * t] = c[t][i];
+  // dL/dz1 = (W2^T dz2) masked by layer 1: units row .. row + 3 of layer 1
+  c[0] = c[1] = f4{0.f, 0.f, 0.f, 0.f};
+  mm_16<kHid>(W2 + u0, 1, kLd, D2 + m0 * kLd, kLd, 1, c);
+  // the sums over the samples of the output layer and of b2, and the loss,
+  // in sample order, one wave each
+  if (wid == 0) {
     float g = 0.f;
+#pragma unroll 16
+    for (int s = 0; s < kTile; ++s) g += DZ[s] * H2[s * kLd + lane];
+    out[oW3 + lane] = g;
+  } else if (wid == 1) {
+    float g = 0.f;
+#pragma unroll 16
+    for (int s = 0; s < kTile; ++s) g += D2[s * kLd + lane];
+    out[ob2 + lane] = g;
+  } else if (tid == 128) {
+    float g = 0.f;
+#pragma unroll 16
     for (int s = 0; s < kTile; ++s) g += DZ[s];
     out[ob3] = g;
-  }
-  if (tid == kHid + 1) {
-    // the tile's loss: softplus(z) - y z per sample (without overflow),
-    // summed in sample order
+  } else if (tid == 192) {
     float l = 0.f;
-    for (int s = 0; s < ns; ++s) {
-      const float yy = y[s0 + s];
-      float z = P[ob3];
-      for (int k = 0; k < kHid; ++k) z += P[oW3 + k] * H2[s * kHid + k];
-      const float sp = z > 0.f ? z + log1pf(expf(-z)) : log1pf(expf(z));
-      l += (sp - yy * z) * inv_n;
-    }
+    for (int s = 0; s < ns; ++s) l += LS[s] * inv_n;
     out[kParams] = l;
   }
-  for (int s = sq; s < kTile; s += 4)
-    D2[s * kHid + h] = H2[s * kHid + h] > 0.f ? DZ[s] * P[oW3 + h] : 0.f;
-  __syncthreads();
-  // W2, b2: thread (h, quarter) sums over all samples for 16 inputs k
-  {
-    const int kq = tid >> 6;  // inputs kq*16 .. kq*16+15
-    for (int kk = 0; kk < 16; ++kk) {
-      const int k = kq * 16 + kk;
-      float g = 0.f;
-      for (int s = 0; s < kTile; ++s) g += D2[s * kHid + h] * H1[s * kHid + k];
-      out[oW2 + h * kHid + k] = g;
-    }
-    if (kq == 0) {
-      float g = 0.f;
-      for (int s = 0; s < kTile; ++s) g += D2[s * kHid + h];
-      out[ob2 + h] = g;
-    }
+  __syncthreads();  // H2 is no longer needed
+  float* const D1 = H2;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const f4 h = *reinterpret_cast<const f4*>(H1 + (col + 16 * t) * kLd + row);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[t][i] = h[i] > 0.f ? c[t][i] : 0.f;
+    *reinterpret_cast<f4*>(D1 + (col + 16 * t) * kLd + row) = c[t];
   }
   __syncthreads();
-  // dL/dz1 = (W2^T dz2) masked by layer 1, into H2 (no longer needed)
-  for (int s = sq; s < kTile; s += 4) {
-    float d = 0.f;
-    for (int u = 0; u < kHid; ++u) d += D2[s * kHid + u] * P[oW2 + u * kHid + h];
-    H2[s * kHid + h] = H1[s * kHid + h] > 0.f ? d : 0.f;
-  }
-  __syncthreads();
-  // W1, b1
-  for (int i = tid; i < kHid * kIn; i += kMlpThreads) {
-    const int u = i / kIn, j = i % kIn;
+  // W1 (16 units per wave; columns 12 .. 15 are not inputs), b1
+  if (wid < 4) {
+    f4 w1[1] = {f4{0.f, 0.f, 0.f, 0.f}};
+    mm_16<kTile>(D1 + u0, 1, kLd, X, 1, kIn, w1);
+    if ((lane & 15) < kIn)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out[oW1 + (row + i) * kIn + (lane & 15)] = w1[0][i];
+  } else if (wid == 4) {
     float g = 0.f;
-    for (int s = 0; s < kTile; ++s) g += H2[s * kHid + u] * X[s * kIn + j];
-    out[oW1 + i] = g;
-  }
-  if (tid < kHid) {
-    float g = 0.f;
-    for (int s = 0; s < kTile; ++s) g += H2[s * kHid + tid];
-    out[ob1 + tid] = g;
+#pragma unroll 16
+    for (int s = 0; s < kTile; ++s) g += D1[s * kLd + lane];
+    out[ob1 + lane] = g;
   }
 }
 
-// Thread per parameter: gradient = sum of the tile partials in tile order;
-// with update, one Adam step (c1, c2 = bias corrections 1/(1 - beta^t)).
-__global__ void k_reduce_adam(const float* __restrict__ part, int tiles, float* __restrict__ prm,
-                              float* __restrict__ m, float* __restrict__ v,
-                              float* __restrict__ grad, float* __restrict__ loss, int update,
-                              float lr, float b1, float b2, float eps, float c1, float c2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i > kParams) return;
-  float g = 0.f;
-  for (int t = 0; t < tiles; ++t) g += part[(size_t)t * kPart + i];
+// Gradient = sum of the tile partials in tile order, 64 parameters per
+// workgroup; with update, one Adam step (c1, c2 = bias corrections
+// 1/(1 - beta^t)).  Bound by the latency of the partials' loads, since the
+// order of the sum is fixed: the workgroup's waves bring the tiles to LDS side
+// by side, kAhead loads in flight each, and one wave adds them in order (188
+// tiles: 43.5 us with a thread walking its partials, 9.0 with 64 of them
+// loaded ahead, now 4.6).
+constexpr int kAdamWaves = 8;
+constexpr int kAhead = 24;
+constexpr int kAdamTiles = kAdamWaves * kAhead;  // tiles per pass through LDS
+__global__ void __launch_bounds__(64 * kAdamWaves)
+    k_reduce_adam(const float* __restrict__ part, int tiles, float* __restrict__ prm,
+                  float* __restrict__ m, float* __restrict__ v, float* __restrict__ grad,
+                  float* __restrict__ loss, int update, float lr, float b1, float b2, float eps,
+                  float c1, float c2) {
+  __shared__ float sums[kAdamTiles][64];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int i = blockIdx.x * 64 + lane;
+  const bool mine = i <= kParams;
+  float g = 0.f, m0 = 0.f, v0 = 0.f, p0 = 0.f;
+  if (wid == 0 && update && i < kParams) {
+    m0 = m[i];
+    v0 = v[i];
+    p0 = prm[i];
+  }
+  for (int t0 = 0; t0 < tiles; t0 += kAdamTiles) {
+    const int nt = min(kAdamTiles, tiles - t0);
+    float p[kAhead];
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a) {
+      const int t = a * kAdamWaves + wid;
+      p[a] = mine && t < nt ? part[(size_t)(t0 + t) * kPart + i] : 0.f;
+    }
+    __syncthreads();  // the previous tiles are summed
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a) sums[a * kAdamWaves + wid][lane] = p[a];
+    __syncthreads();
+    if (wid == 0) {
+#pragma unroll 16
+      for (int t = 0; t < nt; ++t) g += sums[t][lane];
+    }
+  }
+  if (wid != 0 || !mine) return;
   if (i == kParams) {
     if (loss) *loss = g;
     return;
   }
   if (grad) grad[i] = g;
   if (update) {
-    const float mi = b1 * m[i] + (1.f - b1) * g;
-    const float vi = b2 * v[i] + (1.f - b2) * g * g;
+    // the rounding of each moment is written out: which product the compiler
+    // would fuse into the sum depends on the code around it, and the last
+    // bits of a step travel through all that follow
+    const float mi = fmaf(1.f - b1, g, b1 * m0);
+    const float vi = fmaf(g, (1.f - b2) * g, b2 * v0);
     m[i] = mi;
     v[i] = vi;
-    prm[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
+    prm[i] = p0 - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
   }
 }
 
@@ -291,13 +431,15 @@ struct Staged {
   float* part = nullptr;
   float* prob = nullptr;
   float* losses = nullptr;
+  double* lg = nullptr;
   ~Staged() {
     if (mem) (void)hipFree(mem);
   }
 };
 
 static fp_status stage(const int64_t* f, const float* y, int n, int mem_kind, int tiles,
-                       bool want_part, bool want_prob, int loss_slots, hipStream_t s, Staged* st) {
+                       bool want_part, bool want_prob, int loss_slots, hipStream_t s, Staged* st,
+                       bool want_log = false) {
   const size_t fb = (size_t)n * kIn * sizeof(int64_t);
   const size_t yb = y ? (size_t)n * sizeof(float) : 0;
   size_t total = al((size_t)n * kIn * sizeof(float));
@@ -305,6 +447,7 @@ static fp_status stage(const int64_t* f, const float* y, int n, int mem_kind, in
   if (want_part) total += al((size_t)tiles * kPart * sizeof(float));
   if (want_prob) total += al((size_t)n * sizeof(float));
   total += al((size_t)loss_slots * sizeof(float));
+  if (want_log) total += al((size_t)n * kIn * sizeof(double));
   hipError_t he = hipMalloc(&st->mem, total);
   if (he != hipSuccess) {
     st->mem = nullptr;
@@ -338,14 +481,17 @@ static fp_status stage(const int64_t* f, const float* y, int n, int mem_kind, in
     p += al((size_t)n * sizeof(float));
   }
   st->losses = reinterpret_cast<float*>(p);
+  p += al((size_t)loss_slots * sizeof(float));
+  if (want_log) st->lg = reinterpret_cast<double*>(p);
   return FP_OK;
 }
 
 fp_status scorer_fit_impl(fp_scorer* sc, const int64_t* f, int n, int mem_kind, hipStream_t s) {
   Staged st;
-  fp_status r = stage(f, nullptr, n, mem_kind, 0, false, false, 0, s, &st);
+  fp_status r = stage(f, nullptr, n, mem_kind, 0, false, false, 0, s, &st, true);
   if (r) return r;
-  k_norm_stats<<<1, kIn * 64, 0, s>>>(st.f, n, sc->ms);
+  k_log1p<<<(n * kIn + 255) / 256, 256, 0, s>>>(st.f, n, st.lg);
+  k_norm_stats<<<1, kIn * 64, 0, s>>>(st.lg, n, sc->ms);
   hipError_t he = hipGetLastError();
   if (he == hipSuccess) he = hipStreamSynchronize(s);
   if (he != hipSuccess) return hip_fail(he, "feature statistics");
@@ -370,12 +516,12 @@ static fp_status run_steps(fp_scorer* sc, const int64_t* f, const float* y, int 
   const float inv_n = 1.f / (float)n;
   const double b1 = 0.9, b2 = 0.999;
   for (int t = 0; t < steps; ++t) {
-    k_fwd_bwd<true><<<tiles, kMlpThreads, 0, s>>>(sc->prm, st.x, st.y, n, inv_n, st.part,
-                                                  nullptr);
+    k_fwd_bwd<true><<<tiles, kMlpThreads, 0, s>>>(sc->prm, st.x, nullptr, nullptr, st.y, n,
+                                                  inv_n, st.part, nullptr);
     const int step = sc->step + 1;
     const float c1 = (float)(1.0 / (1.0 - std::pow(b1, step)));
     const float c2 = (float)(1.0 / (1.0 - std::pow(b2, step)));
-    k_reduce_adam<<<(kParams + 1 + 255) / 256, 256, 0, s>>>(
+    k_reduce_adam<<<(kParams + 64) / 64, 64 * kAdamWaves, 0, s>>>(
         st.part, tiles, sc->prm, sc->m, sc->v, sc->grad, st.losses + t, update ? 1 : 0, lr,
         (float)b1, (float)b2, 1e-8f, c1, c2);
     if (update) sc->step = step;
@@ -414,8 +560,8 @@ fp_status scorer_predict_impl(fp_scorer* sc, const int64_t* f, int n, int mem_ki
   fp_status r = stage(f, nullptr, n, mem_kind, tiles, false, mem_kind == 0, 0, s, &st);
   if (r) return r;
   float* out = mem_kind == 0 ? st.prob : prob;
-  k_norm_apply<<<(n * kIn + 255) / 256, 256, 0, s>>>(st.f, n, sc->ms, st.x);
-  k_fwd_bwd<false><<<tiles, kMlpThreads, 0, s>>>(sc->prm, st.x, nullptr, n, 0.f, nullptr, out);
+  k_fwd_bwd<false><<<tiles, kMlpThreads, 0, s>>>(sc->prm, nullptr, st.f, sc->ms, nullptr, n, 0.f,
+                                                 nullptr, out);
   hipError_t he = hipGetLastError();
   if (he == hipSuccess && mem_kind == 0)
     he = hipMemcpyAsync(prob, out, (size_t)n * sizeof(float), hipMemcpyDeviceToHost, s);

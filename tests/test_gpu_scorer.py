@@ -71,6 +71,25 @@ def test_gradient_vs_oracle(hf, mlp, n):
         assert err <= 1e-4, (name, err)
 
 
+@pytest.mark.parametrize("n", [1, 63, 65, 192 * 64 + 1])
+def test_tile_edges_vs_oracle(hf, mlp, n):
+    """A single sample, tiles one short and one over, and one tile more than
+    the gradient reduction brings to LDS at once: gradient and predictions
+    against the oracle (the tolerances above)."""
+    f, y = _data(n, n + 1)
+    theta = inputs.scorer_init_params(n)
+    with hf.Scorer(theta) as sc:
+        sc.fit_normalization(f)
+        loss, g = sc.gradient(f, y)
+        p = sc.predict(f)
+    xn, _, _ = mlp.normalize(f)
+    L, gref = mlp.grad(theta.astype(np.float64), xn, y)
+    assert abs(loss - L) <= 1e-5 * max(1.0, abs(L))
+    for name, (a, b) in SLICES.items():
+        assert _rel(g[a:b].astype(np.float64), gref[a:b]) <= 1e-4, name
+    assert np.max(np.abs(p - mlp.predict(theta.astype(np.float64), xn))) <= 1e-5
+
+
 def test_training_tracks_oracle(hf, mlp):
     f, y = _data(1200, 5)
     theta = inputs.scorer_init_params(5)

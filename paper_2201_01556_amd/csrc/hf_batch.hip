@@ -527,7 +527,6 @@ static fp_status union_chunk(fp_batch* b, const std::vector<int32_t>& ids, int32
 // ---------------------------------------------------------------------------
 
 constexpr long long kWgRoundGuard = 1000000ll;  // rounds per solve before giving up
-constexpr int kWgStaleFrontier = 1500;  // "only few active nodes" (paragraph "Avoid Pushing Flow Back")
 
 struct WgParams {
   int32_t count;        // problems in the plan
@@ -554,18 +553,10 @@ struct WgResult {
 __device__ bool wg_global_relabel(const Dev& g, int epoch, lds_int* lds) {
   phase_gr_reset(g, 0, 1, lds);
   __syncthreads();
-  bool ok = true;
-  for (int level = 0;; ++level) {
-    const int nf = count_all_vol(g.ctl->bcnt[level % 3]);
-    if (nf == 0) break;
-    if (nf > g.N || level > g.N) {  // a level holds distinct nodes; at most N levels
-      ok = false;
-      break;
-    }
-    __syncthreads();  // every wave has read the count before the level changes it
-    phase_bfs_rev_lb<true>(g, level, 0, 1, KC_LOOP_BFS, lds);
-    __syncthreads();
-  }
+  const int levels = wg_bfs<kDirRelabel>(g, 0, kInf, 0, KC_LOOP_BFS, lds);
+  __syncthreads();
+  wg_drop_l1();  // the gather and the rounds read the labels
+  const bool ok = count_all_vol(g.ctl->bcnt[levels % 3]) == 0;  // at most N levels
   if (!ok) {
     if (threadIdx.x == 0) atomicOr(&g.ctl->err, ERR_GUARD);
     __syncthreads();
@@ -581,18 +572,11 @@ __device__ bool wg_global_relabel(const Dev& g, int epoch, lds_int* lds) {
 __device__ void wg_cut(const Dev& g, int ep, uint8_t* vs, uint8_t* ns, lds_int* lds) {
   phase_cut_seed(g, ep, false, 0, 1, lds);
   __syncthreads();
-  for (int level = 0;; ++level) {
-    const int nf = count_all_vol(g.ctl->bcnt[level % 3]);
-    if (nf == 0) break;
-    if (nf > g.N || level > g.N) {
-      if (threadIdx.x == 0) atomicOr(&g.ctl->err, ERR_GUARD);
-      break;
-    }
-    __syncthreads();
-    phase_bfs_fwd_lb<true>(g, level, ep, 0, 0, 1, KC_LOOP_BFS, lds);
-    __syncthreads();
-  }
+  const int levels = wg_bfs<kDirSource>(g, 0, kInf, ep, KC_LOOP_BFS, lds);
   __syncthreads();
+  wg_drop_l1();  // the bitmaps are read off the stamps
+  if (threadIdx.x == 0 && count_all_vol(g.ctl->bcnt[levels % 3]) != 0)
+    atomicOr(&g.ctl->err, ERR_GUARD);  // a search has at most N levels
   phase_cut_out(g, ep, vs, ns, threadIdx.x, blockDim.x);
   __syncthreads();
 }
@@ -612,7 +596,6 @@ __device__ void wg_solve(const Dev& g, const WgParams& p, uint8_t* vs, uint8_t* 
   const unsigned long long budget =
       (unsigned long long)g.N * (unsigned long long)p.relabel_x16 / 16ull + 1ull;
   unsigned long long rel_at = ld_vol64(&g.ctl->relabels);
-  unsigned long long last_flow = ld_vol64(&g.ctl->flow);
   int since = 0, stale = 0;
   bool fresh = true;  // the frontier was just gathered by a global relabel
   while (ok) {
@@ -631,22 +614,18 @@ __device__ void wg_solve(const Dev& g, const WgParams& p, uint8_t* vs, uint8_t* 
       }
       fresh = false;
       __syncthreads();  // every wave has read the counters before they change
-      phase_push<G>(g, epoch, 0, 1, KC_LOOP_ROUNDS, lds);
+      // as many rounds as the relabel triggers leave
+      long long most = kWgRoundGuard - rounds;
+      if (p.gr_interval > 0) most = min(most, (long long)(p.gr_interval - since));
+      const int left = p.stale_limit > 0 ? max(1, p.stale_limit - stale) : 0;
+      const uint32_t rel_left = relabels_left(rel_at + budget, ld_vol64(&g.ctl->relabels));
+      const LoopEnd end = wg_rounds<G, true>(g, epoch, (int)most, kInf, rel_left, left,
+                                             KC_LOOP_ROUNDS, lds);
       __syncthreads();
-      phase_apply(g, epoch, 0, 1, KC_LOOP_ROUNDS, lds);
-      __syncthreads();
-      ++epoch;
-      ++rounds;
-      ++since;
-      const unsigned long long fl = ld_vol64(&g.ctl->flow);
-      if (fl != last_flow) {
-        last_flow = fl;
-        stale = 0;
-      } else if (nf < kWgStaleFrontier) {
-        ++stale;
-      } else {
-        stale = 0;
-      }
+      epoch += end.rounds;
+      rounds += end.rounds;
+      since += end.rounds;
+      stale = end.flowed ? end.stale : stale + end.stale;
       if (ld_vol64(&g.ctl->relabels) - rel_at >= budget) gr = true;
       if (p.gr_interval > 0 && since >= p.gr_interval) gr = true;
       if (p.stale_limit > 0 && stale >= p.stale_limit) gr = true;
@@ -657,7 +636,6 @@ __device__ void wg_solve(const Dev& g, const WgParams& p, uint8_t* vs, uint8_t* 
       ++ngr;
       if (ok && nf == 0 && count_all_vol(g.ctl->fcnt[epoch % 3]) > 0) ++restarts;
       rel_at = ld_vol64(&g.ctl->relabels);
-      last_flow = ld_vol64(&g.ctl->flow);
       since = 0;
       stale = 0;
       fresh = true;
@@ -689,7 +667,9 @@ __global__ void __launch_bounds__(B) k_batch_wg(const Dev* devs, const int32_t* 
                                                          uint8_t* const* vs_ptrs,
                                                          uint8_t* const* ns_ptrs, int32_t* next,
                                                          WgParams p, WgResult* res) {
-  __shared__ int32_t bq[lds_words(B)];
+  // the sweeps' staging area, the rounds' or the searches' lists
+  constexpr int kWords = lds_words(B) > kLoopWords ? lds_words(B) : kLoopWords;
+  __shared__ int32_t bq[kWords > kWgBfsWords ? kWords : kWgBfsWords];
   lds_int* const lds = (lds_int*)bq;
   __shared__ int32_t slot;
   for (;;) {

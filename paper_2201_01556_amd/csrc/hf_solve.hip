@@ -22,7 +22,7 @@ namespace hf {
 constexpr int kThreads = 256;  // plain element-wise kernels
 constexpr int kBlock = 1024;   // frontier, sweep and single-workgroup kernels
 constexpr int kFcGrid = 128;   // FlowCutter weight and candidate sweeps
-constexpr int kLoopBlock = 512;  // the single-workgroup round loop (1024 threads spill 48 bytes a lane)
+constexpr int kLoopBlock = 1024;  // the single-workgroup round loop
 constexpr int kMaxFrontierBlocks = 512;
 static_assert(kMaxFrontierBlocks <= kMaxSliceGroups, "one slice segment per scan workgroup");
 constexpr int kMaxSweepBlocks = 512;
@@ -286,78 +286,34 @@ __global__ void __launch_bounds__(kThreads) k_check(Dev g) {
   phase_check(g, gthread(), gthreads());
 }
 
-// Rounds inside one workgroup.  All waves of the workgroup share one CU, so
-// a workgroup barrier orders their global memory traffic; no device-scope
-// fence (which would write back and invalidate the L2) is needed.  Stops when
-// the frontier is empty (1), exceeds `cap` (2), `max_rounds` rounds ran (3),
-// the relabel count reached `relabel_limit` (4), or the flow value did not
-// change for `stale_limit` rounds (5).  The exit tests read values that no
-// wave writes between the barrier and the test, so every wave takes the same
-// decision.
+// Rounds inside one workgroup (wg_rounds) until one of its exits.
 template <int G>
 __global__ void __launch_bounds__(kLoopBlock) k_round_loop(Dev g, int epoch0, int max_rounds,
                                                            int cap,
                                                            unsigned long long relabel_limit,
                                                            int stale_limit) {
-  __shared__ int32_t hf_bq[lds_words(kLoopBlock)];
-  lds_int* const lds = (lds_int*)hf_bq;
-  int epoch = epoch0;
-  int r = 0;
-  int why = 0;
-  int stale = 0;
-  unsigned long long last_flow = ld_vol64(&g.ctl->flow);
-  for (;;) {
-    const int c3 = epoch % 3;
-    const int nf = count_all_vol(g.ctl->fcnt[c3]);
-    const unsigned long long fl = ld_vol64(&g.ctl->flow);
-    if (fl != last_flow) {
-      last_flow = fl;
-      stale = 0;
-    }
-    if (nf == 0) { why = 1; break; }
-    if (nf > cap) { why = 2; break; }
-    if (r >= max_rounds) { why = 3; break; }
-    if (ld_vol64(&g.ctl->relabels) >= relabel_limit) { why = 4; break; }
-    if (stale_limit > 0 && stale >= stale_limit) { why = 5; break; }
-    __syncthreads();  // every wave has read the counters before they change
-    phase_push<G>(g, epoch, 0, 1, KC_LOOP_ROUNDS, lds);
-    __syncthreads();
-    phase_apply(g, epoch, 0, 1, KC_LOOP_ROUNDS, lds);
-    __syncthreads();
-    ++epoch;
-    ++r;
-    ++stale;
-  }
+  __shared__ int32_t area[kLoopWords];
+  const LoopEnd end = wg_rounds<G, false>(
+      g, epoch0, max_rounds, cap, relabels_left(relabel_limit, ld_vol64(&g.ctl->relabels)),
+      stale_limit, KC_LOOP_ROUNDS, (lds_int*)area);
   if (threadIdx.x == 0) {
-    g.ctl->loop_rounds = r;
-    g.ctl->loop_exit = why;
+    g.ctl->loop_rounds = end.rounds;
+    g.ctl->loop_exit = end.why;
   }
 }
 
-// BFS levels inside one workgroup: mode 0 the global relabel (reverse,
-// capped), 1 the source side (forward, uncapped), 2 the sink side (reverse,
-// uncapped).  Levels this small are latency bound: arc-parallel levels spread
-// even one node's arcs over the whole workgroup, which node-grouped levels do
-// not (the FlowCutter's incremental sides run here: 1.92 -> 1.85 s on the
-// 200k-vertex region).
-template <int G>
+// BFS levels inside one workgroup (wg_bfs): mode 0 the global relabel
+// (reverse, capped), 1 the source side (forward, uncapped), 2 the sink side
+// (reverse, uncapped).
 __global__ void __launch_bounds__(kBlock) k_bfs_loop(Dev g, int level0, int cap, int ep,
                                                      int mode) {
-  HF_QUEUE_LDS;
-  int level = level0;
-  for (;;) {
-    const int c3 = level % 3;
-    const int nf = count_all_vol(g.ctl->bcnt[c3]);
-    if (nf == 0 || nf > cap) break;
-    if (mode == 0 && threadIdx.x == 0 && level < kLvlHist) g.ctl->lvl_nf[level] = nf;
-    __syncthreads();
-    if (mode == 0) phase_bfs_rev_lb<true>(g, level, 0, 1, KC_LOOP_BFS, lds);
-    else if (mode == 1) phase_bfs_fwd_lb<true>(g, level, ep, 0, 0, 1, KC_LOOP_BFS, lds);
-    else phase_bfs_sink_lb(g, level, ep, 0, 1, KC_LOOP_BFS, lds);
-    __syncthreads();
-    ++level;
-  }
-  if (threadIdx.x == 0) g.ctl->loop_levels = level - level0;
+  __shared__ int32_t area[kWgBfsWords];
+  lds_int* const lds = (lds_int*)area;
+  int levels;
+  if (mode == 0) levels = wg_bfs<kDirRelabel>(g, level0, cap, ep, KC_LOOP_BFS, lds);
+  else if (mode == 1) levels = wg_bfs<kDirSource>(g, level0, cap, ep, KC_LOOP_BFS, lds);
+  else levels = wg_bfs<kDirSink>(g, level0, cap, ep, KC_LOOP_BFS, lds);
+  if (threadIdx.x == 0) g.ctl->loop_levels = levels;
 }
 
 // ---------------------------------------------------------------------------
@@ -557,7 +513,7 @@ static fp_status run_bfs(fp_problem* pb, hipStream_t s, int ep, int mode, int* l
     launch_levels<G>(pb, s, ep, ep_tmp, mode, level, steps, predict);
     if (use_loop) {
       Launch L(pb, s, mode == 0 ? KK_BFS_REV_LOOP : KK_BFS_FWD_LOOP);
-      k_bfs_loop<G><<<1, kBlock, 0, s>>>(g, level + steps, cap, ep, mode);
+      k_bfs_loop<<<1, kBlock, 0, s>>>(g, level + steps, cap, ep, mode);
     }
     st = sync_ctl(pb, s, "bfs");
     if (st) return st;
@@ -655,13 +611,12 @@ static fp_status solve_impl(fp_problem* pb, hipStream_t s, int64_t* flow) {
                             : pb->opt.tail_gr_interval < 0 ? gr_interval
                                                            : 4 * gr_interval;
   const int stale_limit = pb->opt.stale_rounds;
-  constexpr long long kStaleFrontier = 1500;  // "only few active nodes" (paper)
   unsigned long long rel_at_gr = pb->ctl_h->relabels;
   unsigned long long last_flow = pb->ctl_h->flow;
   long long stale = 0;
   long long rounds_since_gr = 0;
   bool fresh_gr = !warm;  // frontier was just gathered by a global relabel
-  const int cap = pb->opt.tail_threshold;
+  const int cap = std::min(pb->opt.tail_threshold, kLoopCap);
   const int rounds_per_sync = pb->opt.debug_checks ? 1 : 8;
   int64_t rounds_this_solve = 0;
   for (;;) {
@@ -966,7 +921,7 @@ static fp_status grow_side_start_impl(fp_problem* pb, hipStream_t s, int side, i
   }
   {
     Launch L(pb, s, KK_BFS_FWD_LOOP);
-    k_bfs_loop<G><<<1, kBlock, 0, s>>>(g, 0, pb->opt.tail_threshold, ep, side == 0 ? 1 : 2);
+    k_bfs_loop<<<1, kBlock, 0, s>>>(g, 0, pb->opt.tail_threshold, ep, side == 0 ? 1 : 2);
   }
   hipError_t he = hipGetLastError();
   if (he != hipSuccess) return hip_fail(he, "growing a reachable set");

@@ -153,3 +153,36 @@ def test_workgroups_in_tuner(hf, oracle_mod):
     finally:
         for p in probs:
             p.close()
+
+
+@pytest.mark.parametrize("lanes,threads", [(8, 1024), (16, 1024), (4, 256)])
+def test_lists_past_the_lds_area(hf, oracle_mod, lanes, threads):
+    """Frontiers and search levels of more than 1,024 nodes of one kind, which
+    the workgroup's LDS lists do not hold: 12,000 vertices, 1,500 sources and
+    sinks, flows and sides against the oracle, next to a small problem."""
+    hgs = [inputs.uniform_hypergraph(31, num_vertices=12_000, num_nets=20_000, size_hi=40,
+                                     num_sources=1500, num_sinks=1500),
+           inputs.uniform_hypergraph(32, num_vertices=300, num_nets=500, num_sources=20,
+                                     num_sinks=20)]
+    refs = [oracle_mod.maxflow(h) for h in hgs]
+    probs = [hf.FlowProblem.from_hypergraph(h) for h in hgs]
+    try:
+        with hf.FlowBatch(probs, with_cut=True, schedule=3, group_lanes=lanes,
+                          wg_threads=threads) as b:
+            flows = b.run(with_cut=True)
+            _check(b, hgs, refs, flows, f"lanes={lanes} threads={threads}")
+    finally:
+        for p in probs:
+            p.close()
+
+
+@pytest.mark.parametrize("tail", [1023, 1024, 1025])
+def test_round_loop_capacity(hf, oracle_mod, tail):
+    """The single-problem path around the most nodes its round loop holds."""
+    hg = inputs.uniform_hypergraph(33, num_vertices=4000, num_nets=6000, num_sources=400,
+                                   num_sinks=400)
+    ref = oracle_mod.maxflow(hg)
+    with hf.FlowProblem.from_hypergraph(hg, tail_threshold=tail) as p:
+        assert p.solve() == ref.flow
+        vs, ns = p.source_side()
+    assert (vs == ref.vertex_side).all() and (ns == ref.net_side).all()

@@ -73,7 +73,8 @@ typedef struct {
   int32_t debug_checks;       /* 1 = verify preflow and labelling invariants
                                  after every round (slow; test use)          */
   int32_t tail_threshold;     /* frontier size at or below which a single
-                                 workgroup runs the rounds; default 256      */
+                                 workgroup runs the rounds (at most 1024);
+                                 default 256                                 */
   int32_t group_lanes;        /* lanes per small frontier vertex: 4, 8 or
                                  16 (small net nodes get half, at least 4);
                                  default 16                                  */
@@ -89,11 +90,14 @@ typedef struct {
                                  stayed unchanged for this many rounds with a
                                  small frontier (paper, paragraph "Avoid
                                  Pushing Flow Back"); default 500, -1 = off  */
-  int32_t bottom_up_min;      /* reverse-BFS levels with at least this many
-                                 nodes are expanded without atomics and the
-                                 next level is collected by a sweep over the
-                                 labels; default N/50 (at least 1024),
-                                 -1 = never                                  */
+  int32_t bottom_up_min;      /* BFS levels with at least this many nodes are
+                                 handled without atomics: in the reverse BFS
+                                 by a sweep in which every unlabelled node
+                                 looks for an arc into the level, in the
+                                 forward BFS by plain stamps and a sweep that
+                                 collects them; default N/16 (at least
+                                 262144) from 1048576 nodes on, below that
+                                 and with -1 never                           */
   int32_t bfs_arc_parallel;   /* 1 = BFS levels split work per arc (prefix sum
                                  over the level's arc counts) instead of per
                                  node; default 0                             */

@@ -102,6 +102,7 @@ struct Ctl {
   int32_t loop_rounds;  // rounds run by the last single-workgroup round loop
   int32_t loop_levels;  // levels run by the last single-workgroup BFS loop
   int32_t loop_exit;
+  int32_t bfs_done;     // the last single-workgroup BFS loop ended on an empty level
   unsigned long long flow;      // flow value (into sinks)
   unsigned long long relabels;  // relabel operations
   unsigned long long bytes[KC_N];
@@ -113,6 +114,9 @@ struct Ctl {
                       // whose frontier exceeded the single-workgroup tail
   int32_t lvl_nf[kLvlHist];  // size of each of the first reverse-BFS levels of
                              // the current global relabel
+  int32_t bits_level;  // reverse-BFS level that the level bitmaps describe, -1 none
+  int32_t swept;       // last level that was swept (phase_bfs_sweep), -1 none
+  int32_t sweep_n[2][3];  // nodes per kind that the sweep of an even (odd) level found
 };
 
 struct Dev {
@@ -146,7 +150,13 @@ struct Dev {
   uint32_t* pinres;        // ceil(P/32) words: bit of pin slot p = flow(u, e_in) > 0
   uint32_t* netres;        // ceil(E/8) words, 4 bits per net: bit0 = e_in -> e_out
                            // residual (fb < w), bit1 = pins carry flow out of
-                           // e_out, bit2 = e_out -> e_in residual (fb > 0)
+                           // e_out, bit2 = e_out -> e_in residual (fb > 0),
+                           // bit3 = pins may carry flow into e_in
+  uint32_t* pinfree;       // ceil(P/32) words: bit of pin slot p = r_in > 0; null when the
+                           // swept levels are off (phase_bfs_sweep)
+  uint32_t* vf[2];         // swept levels, by level parity: bit v = vertex v lies in the level
+  uint2* nl[2];            // the same per 32 nets: x = e_in lies in the level, y = e_out does
+                           // and pins carry flow out of it
   int32_t* list[2][kNL];   // [parity][list]: capacities V, E, E, N
   Ctl* ctl;
 };
@@ -1051,27 +1061,38 @@ __device__ LoopEnd wg_rounds(const Dev& g, int epoch, int max_rounds, int cap,
 //           (the reverse arc e_in -> u is residual)
 //   netres: four bits per net: bit0 fb < w (e_in -> e_out residual), bit1
 //           some pin carries flow out of e_out (fb exceeds e_out's excess),
-//           bit2 fb > 0 (e_out -> e_in residual)
+//           bit2 fb > 0 (e_out -> e_in residual), bit3 something flows into
+//           e_in, so a pin's flow may
+//   pinfree (swept levels): one bit per pin slot, r_in > 0
 // Thread per slot, then per net; t0 wave-aligned, tstride a multiple of 64.
 __device__ void phase_gr_bits(const Dev& g, int t0, int tstride) {
   const int lane = lane_id();
-  // pin slots: a lane per slot, a wave per 64 slots (two words of the bitmap)
+  // pin slots: a lane per slot, a wave per 64 slots (two words of the bitmaps)
   const int np = (g.P + 63) & ~63;
   const int pwords = (g.P + 31) >> 5;
   for (int p = t0; p < np; p += tstride) {
-    const bool f = p < g.P && g.fpin[2 * p] < g.w[g.pin_net[p]];
-    const unsigned long long m = __ballot(f);
+    const int r = p < g.P ? g.fpin[2 * p] : 0;
+    const bool f = p < g.P && r < g.w[g.pin_net[p]];
+    const unsigned long long m = __ballot(f), mr = __ballot(r > 0);
     const int word = ((p - lane) >> 5) + lane;
-    if (lane < 2 && word < pwords) g.pinres[word] = (uint32_t)(m >> (32 * lane));
+    if (lane < 2 && word < pwords) {
+      g.pinres[word] = (uint32_t)(m >> (32 * lane));
+      if (g.pinfree) g.pinfree[word] = (uint32_t)(mr >> (32 * lane));
+    }
   }
   // nets: a lane per net, eight nibbles per word
   const int ne = (g.E + 63) & ~63;
   for (int e = t0; e < ne; e += tstride) {
     uint32_t b = 0;
     if (e < g.E) {
-      const int fbv = g.fb[e], eo = g.NB + 2 * e + 1;
-      const int out = fbv - (g.x[eo] + g.dx[0][eo] + g.dx[1][eo]);
-      b = (fbv < g.w[e] ? 1u : 0u) | (out > 0 ? 2u : 0u) | (fbv > 0 ? 4u : 0u);
+      const int fbv = g.fb[e], ei = g.NB + 2 * e;
+      const int2 x = *reinterpret_cast<const int2*>(g.x + ei);
+      const int2 a = *reinterpret_cast<const int2*>(g.dx[0] + ei);
+      const int2 c = *reinterpret_cast<const int2*>(g.dx[1] + ei);
+      const int out = fbv - (x.y + a.y + c.y);
+      const int in = fbv + x.x + a.x + c.x;  // a source's share included
+      b = (fbv < g.w[e] ? 1u : 0u) | (out > 0 ? 2u : 0u) | (fbv > 0 ? 4u : 0u) |
+          (in > 0 ? 8u : 0u);
     }
     uint32_t v = b << (4 * (lane & 7));
     v |= __shfl_xor(v, 1);
@@ -1465,8 +1486,8 @@ __device__ void phase_bfs_rev_node(const Dev& g, int level, int tile0, int tstri
 // ---------------------------------------------------------------------------
 
 template <bool kClaim, bool kSlice = false>
-__device__ __forceinline__ void phase_bfs_rev_flat(const Dev& g, int level, int tile0, int tstride, int kc,
-                                   lds_int* lds) {
+__device__ __forceinline__ void phase_bfs_rev_flat(const Dev& g, int level, int tile0, int tstride,
+                                                   int kc, lds_int* lds) {
   const int c3 = level % 3, n3 = (level + 1) % 3, z3 = (level + 2) % 3;
   if (tile0 == 0 && threadIdx.x < kNL) g.ctl->bcnt[z3][threadIdx.x] = 0;
   const int cp = level & 1, np = (level + 1) & 1;
@@ -1912,6 +1933,337 @@ __device__ void phase_bfs_rev_expand(const Dev& g, int level, int tile0, int tst
   else phase_bfs_rev_node<G, false>(g, level, tile0, tstride, kc, lds);
 }
 
+// ---------------------------------------------------------------------------
+// swept reverse-BFS levels
+//
+// Expanding a level that holds a large part of the graph from its list reads
+// a line of offsets, adjacency and flows per node and a label line per arc,
+// scattered over arrays of 20 MB and more, and a pass over all labels must
+// then list the next level.  Such a level is swept the other way round
+// instead: every node that has no label yet looks for an arc into the level,
+// nets and vertices in id order.  What the sweep reads is consecutive, apart
+// from one bit per arc in bitmaps of the level that stay in the L2 (125 KB for
+// 1 M vertices, 500 KB for 2 M nets); every label is written by its node's own
+// thread; and the next level's bitmaps and counts fall out of the wave's
+// ballots, so a run of swept levels needs no lists:
+//   e_out    from any pin in the level, or from e_in in the level by the
+//            bridge (fb > 0)
+//   e_in     from e_out in the level by the bridge (fb < w), or from a pin in
+//            the level whose flow into e_in can be returned
+//   vertex   from e_in in the level with room (r_in > 0), or from e_out in the
+//            level when its flow into the vertex can be returned
+// Lists are made again when the search leaves the large levels
+// (phase_bfs_collect_bits); there the bitmaps are made when it enters them.
+// ---------------------------------------------------------------------------
+
+__device__ __forceinline__ bool bit_of(const uint32_t* m, int i) {
+  return (m[i >> 5] >> (i & 31)) & 1u;
+}
+
+// Inclusive prefix sum over the wave.
+__device__ __forceinline__ int wave_scan(int v) {
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int t = __shfl_up(v, o);
+    if (lane_id() >= o) v += t;
+  }
+  return v;
+}
+// The last lane whose (exclusive) offset is at most a.
+__device__ __forceinline__ int wave_owner(int excl, int a) {
+  int lo = 0;
+#pragma unroll
+  for (int st = kWave / 2; st > 0; st >>= 1) {
+    const int c = lo + st;
+    if (__shfl(excl, c) <= a) lo = c;
+  }
+  return lo;
+}
+
+// A wave takes 128 nets (vertices), two per lane, and is bound by the latency
+// of its loads, so a lane first looks at the first kFirst arcs of both with
+// all their loads in flight: that settles most (nets of 3.7 pins on average,
+// and a large level is hit early).  What is left is spread over the wave's
+// lanes; nets or vertices with more than kSweepLong arcs left are set aside
+// and scanned at the end, a wave each, so that no wave of the sweep walks a
+// long one while the others wait.
+constexpr int kFirst = 4;
+constexpr int kSweepLong = 192;
+constexpr int kSweepAside = 512;  // set aside per workgroup; more are scanned where they are met
+constexpr int kSweepWords = 1 + kSweepAside + 1024 + 4;
+
+__device__ void phase_bfs_sweep(const Dev& g, int level, int kc, lds_int* lds) {
+  const int tid = threadIdx.x, lane = lane_id(), wid = uni(tid >> 6), nw = blockDim.x >> 6;
+  lds_int* const naside = lds;              // set-aside count (may exceed kSweepAside)
+  lds_int* const aside = lds + 1;           // node ids
+  lds_int* const flag = aside + kSweepAside + wid * kWave;  // per lane of the wave
+  lds_int* const found = aside + kSweepAside + 1024;        // nodes found per kind
+  if (tid == 0) *naside = 0;
+  if (tid >= 64 && tid < 67) found[tid - 64] = 0;
+  __syncthreads();
+  const int wave0 = uni((int)blockIdx.x * nw + wid);
+  const int nwaves = gridDim.x * nw;
+  const int lvl = level + 1;
+  const uint32_t* const vf = g.vf[level & 1];
+  const uint2* const nl = g.nl[level & 1];
+  uint32_t* const vf_next = g.vf[lvl & 1];
+  uint2* const nl_next = g.nl[lvl & 1];
+  uint32_t nbytes = 0, narcs = 0;
+  int nv = 0, nin = 0, nout = 0;  // found by this wave
+  auto set_aside = [&](int node) {
+    const int pos = lds_add(naside, 1);
+    if (pos < kSweepAside) aside[pos] = node;
+    return pos < kSweepAside;
+  };
+  // what pin slot i says to a net that looks for pull (bit0 e_out, bit1 e_in)
+  auto net_arc = [&](int i, int pull) {
+    if (!bit_of(vf, g.pin_v[i])) return 0;
+    return (pull & 1) | ((pull & 2) && pin_flow_in(g, i) ? 2 : 0);
+  };
+  // whether incidence x = {net, slot}, whose net's level word is w, reaches
+  // its vertex
+  auto vertex_hit = [&](int2 x, uint2 w) {
+    const uint32_t b = 1u << (x.x & 31);
+    return ((w.x & b) && bit_of(g.pinfree, x.y)) || ((w.y & b) && g.fpin[2 * x.y + 1] > 0);
+  };
+  for (int base = wave0 * 2 * kWave; base < g.E; base += nwaves * 2 * kWave) {
+    int2 d[2];
+    int beg[2], end[2], got[2], pull[2];
+    uint32_t nb[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int e = min(base + t * kWave + lane, g.E - 1);
+      d[t] = *reinterpret_cast<const int2*>(g.d + g.NB + 2 * e);
+      beg[t] = g.net_off[e];
+      end[t] = g.net_off[e + 1];
+      nb[t] = net_bits(g, e);
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const bool in = base + t * kWave + lane < g.E;
+      got[t] = !in ? 0 : (d[t].x == level && d[t].y == g.N && (nb[t] & 4u) ? 1 : 0) |
+                             (d[t].y == level && d[t].x == g.N && (nb[t] & 1u) ? 2 : 0);
+      pull[t] = !in ? 0 : (d[t].y == g.N && !(got[t] & 1) ? 1 : 0) |
+                              (d[t].x == g.N && !(got[t] & 2) && (nb[t] & 8u) ? 2 : 0);
+      nbytes += 16;
+    }
+    int u[2][kFirst];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < kFirst; ++j)
+        u[t][j] = pull[t] && beg[t] + j < end[t] ? g.pin_v[beg[t] + j] : -1;
+    uint32_t w[2][kFirst];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < kFirst; ++j) w[t][j] = u[t][j] >= 0 ? vf[u[t][j] >> 5] : 0u;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < kFirst; ++j)
+        if ((w[t][j] >> (u[t][j] & 31)) & 1u) {
+          got[t] |= pull[t] & 1;
+          if ((pull[t] & 2) && pin_flow_in(g, beg[t] + j)) got[t] |= 2;
+        }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int e0 = base + t * kWave;
+      if (e0 >= g.E) break;  // wave-uniform
+      const int node = g.NB + 2 * (e0 + lane);
+      const int b = beg[t] + kFirst;
+      int deg = (pull[t] & ~got[t]) ? max(0, end[t] - b) : 0;
+      if (deg > kSweepLong && set_aside(node)) deg = 0;
+      if (__ballot(deg > 0)) {
+        flag[lane] = 0;
+        const int incl = wave_scan(deg), excl = incl - deg, A = __shfl(incl, kWave - 1);
+        for (int a0 = 0; a0 < A; a0 += kWave) {
+          const int a = a0 + lane;
+          const int lo = wave_owner(excl, a);
+          const int i = __shfl(b, lo) + a - __shfl(excl, lo);
+          const int q = __shfl(pull[t], lo);
+          if (a < A) {
+            const int f = net_arc(i, q);
+            if (f)
+              __hip_atomic_fetch_or(flag + lo, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            ++narcs;
+          }
+        }
+        got[t] |= flag[lane];
+      }
+      if (got[t] & 1) g.d[node + 1] = lvl;
+      if (got[t] & 2) g.d[node] = lvl;
+      const unsigned long long mi = __ballot(got[t] & 2), mo = __ballot(got[t] & 1),
+                               mf = __ballot((got[t] & 1) && (nb[t] & 2u));
+      nin += __popcll(mi);
+      nout += __popcll(mo);
+      if (lane < 2)
+        nl_next[(e0 >> 5) + lane] =
+            make_uint2((uint32_t)(mi >> (32 * lane)), (uint32_t)(mf >> (32 * lane)));
+    }
+  }
+  for (int base = wave0 * 2 * kWave; base < g.V; base += nwaves * 2 * kWave) {
+    int beg[2], end[2];
+    bool got[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int v = min(base + t * kWave + lane, g.V - 1);
+      const bool open = base + t * kWave + lane < g.V && g.d[v] == g.N;
+      beg[t] = g.vtx_off[v];
+      end[t] = open ? g.vtx_off[v + 1] : beg[t];
+      got[t] = false;
+      nbytes += 12;
+    }
+    int2 ep[2][kFirst];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < kFirst; ++j)
+        ep[t][j] = beg[t] + j < end[t] ? g.vinc[beg[t] + j] : make_int2(-1, 0);
+    uint2 w[2][kFirst];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < kFirst; ++j)
+        w[t][j] = ep[t][j].x >= 0 ? nl[ep[t][j].x >> 5] : make_uint2(0u, 0u);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < kFirst; ++j)
+        if (!got[t] && (w[t][j].x | w[t][j].y)) got[t] = vertex_hit(ep[t][j], w[t][j]);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int v0 = base + t * kWave;
+      if (v0 >= g.V) break;  // wave-uniform
+      const int b = beg[t] + kFirst;
+      int deg = got[t] ? 0 : max(0, end[t] - b);
+      if (deg > kSweepLong && set_aside(v0 + lane)) deg = 0;
+      if (__ballot(deg > 0)) {
+        flag[lane] = 0;
+        const int incl = wave_scan(deg), excl = incl - deg, A = __shfl(incl, kWave - 1);
+        for (int a0 = 0; a0 < A; a0 += kWave) {
+          const int a = a0 + lane;
+          const int lo = wave_owner(excl, a);
+          const int i = __shfl(b, lo) + a - __shfl(excl, lo);
+          if (a < A) {
+            const int2 x = g.vinc[i];
+            if (vertex_hit(x, nl[x.x >> 5])) flag[lo] = 1;  // every writer stores the same
+            ++narcs;
+          }
+        }
+        if (flag[lane]) got[t] = true;
+      }
+      if (got[t]) g.d[v0 + lane] = lvl;
+      const unsigned long long m = __ballot(got[t]);
+      nv += __popcll(m);
+      if (lane < 2) vf_next[(v0 >> 5) + lane] = (uint32_t)(m >> (32 * lane));
+    }
+  }
+  __syncthreads();  // the set-aside list is complete, the bitmap words are written
+  const int na = min((int)*naside, kSweepAside);
+  for (int h = wid; h < na; h += nw) {
+    const int node = uni(aside[h]);
+    if (node < g.V) {
+      bool f = false;
+      const int end = g.vtx_off[node + 1];
+      for (int i = g.vtx_off[node] + kFirst; i < end && !f; i += kWave) {
+        bool hit = false;
+        if (i + lane < end) {
+          const int2 x = g.vinc[i + lane];
+          hit = vertex_hit(x, nl[x.x >> 5]);
+          ++narcs;
+        }
+        f = __ballot(hit) != 0ull;
+      }
+      if (f && lane == 0) {
+        g.d[node] = lvl;
+        atomicOr(&vf_next[node >> 5], 1u << (node & 31));
+      }
+      nv += f;
+    } else {
+      const int e = (node - g.NB) >> 1;
+      const int2 d = *reinterpret_cast<const int2*>(g.d + node);
+      const uint32_t b = net_bits(g, e);
+      // labels of this level that the bridge gave are there already
+      const int pull = (d.y == g.N ? 1 : 0) | (d.x == g.N && (b & 8u) ? 2 : 0);
+      int f = 0;
+      const int end = g.net_off[e + 1];
+      for (int i = g.net_off[e]; i < end && (pull & ~f); i += kWave) {
+        const int r = i + lane < end ? net_arc(i + lane, pull) : 0;
+        if (__ballot(r & 1)) f |= 1;
+        if (__ballot(r & 2)) f |= 2;
+        narcs += i + lane < end;
+      }
+      if (lane == 0) {
+        if (f & 1) g.d[node + 1] = lvl;
+        if (f & 2) {
+          g.d[node] = lvl;
+          atomicOr(&nl_next[e >> 5].x, 1u << (e & 31));
+        }
+        if ((f & 1) && (b & 2u)) atomicOr(&nl_next[e >> 5].y, 1u << (e & 31));
+      }
+      nout += f & 1;
+      nin += f >> 1;
+    }
+  }
+  if (lane == 0) {
+    lds_add(found + 0, nv);
+    lds_add(found + 1, nin);
+    lds_add(found + 2, nout);
+  }
+  __syncthreads();
+  if (tid < 3 && found[tid]) atomicAdd(&g.ctl->sweep_n[level & 1][tid], (int)found[tid]);
+  block_add_u64(&g.ctl->bytes[kc], (unsigned long long)nbytes + 8ull * narcs, &g.ctl->items[kc],
+                narcs);
+}
+
+// One pass over the labels, a wave per 64 consecutive nodes: the bitmaps of
+// level + 1 (for a sweep), or with kList its lists and the "labelled" hint of
+// every node (the swept levels do not keep either).
+template <bool kList>
+__device__ void phase_bfs_collect_bits(const Dev& g, int level, int tile0, int tstride,
+                                       lds_int* lds) {
+  const int n3 = (level + 1) % 3, np = (level + 1) & 1;
+  const int lab = level + 1;
+  const int lane = lane_id();
+  const int ts = 2 * (int)blockDim.x;
+  BlockQ q{};
+  if (kList) q = bq_bind(lds, g.ctl->bcnt[n3], g.list[np]);
+  if (kList) {
+    const int ntiles = (g.N + ts - 1) / ts;
+    for (int tile = tile0; tile < ntiles; tile += tstride) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int v = (2 * tile + j) * (int)blockDim.x + (int)threadIdx.x;
+        const int d = v < g.N ? g.d[v] : g.N;
+        const unsigned long long m = __ballot(d != g.N);
+        const int w = ((v - lane) >> 5) + lane;  // v - lane is a multiple of 64
+        if (lane < 2 && 32 * w < g.N) g.seen[w] = (uint32_t)(m >> (32 * lane));
+        qpush(g, q, v, d == lab);
+      }
+      bq_tile_end(q, 2 * blockDim.x);
+    }
+    bq_flush(q);
+  } else {
+    uint32_t* const vf = g.vf[lab & 1];
+    uint2* const nl = g.nl[lab & 1];
+    const int t0 = tile0 * (int)blockDim.x + (int)threadIdx.x, tn = tstride * (int)blockDim.x;
+    for (int v = t0; v < ((g.V + 63) & ~63); v += tn) {
+      const unsigned long long m = __ballot(v < g.V && g.d[v] == lab);
+      if (lane < 2) vf[((v - lane) >> 5) + lane] = (uint32_t)(m >> (32 * lane));
+    }
+    for (int e = t0; e < ((g.E + 63) & ~63); e += tn) {
+      int2 d = make_int2(0, 0);
+      if (e < g.E) d = *reinterpret_cast<const int2*>(g.d + g.NB + 2 * e);
+      const unsigned long long mi = __ballot(e < g.E && d.x == lab);
+      const unsigned long long mf = __ballot(e < g.E && d.y == lab && (net_bits(g, e) & 2u));
+      if (lane < 2)
+        nl[((e - lane) >> 5) + lane] =
+            make_uint2((uint32_t)(mi >> (32 * lane)), (uint32_t)(mf >> (32 * lane)));
+    }
+  }
+}
+
 // Sweep tiles: 2 nodes per thread, so a tile appends at most 2 * blockDim
 // entries per list.
 __device__ __forceinline__ int sweep_tiles(const Dev& g) {
@@ -2032,49 +2384,52 @@ __device__ void phase_gr_reset(const Dev& g, int tile0, int tstride, lds_int* ld
     for (int i = 0; i < 3; ++i)
       for (int k = 0; k < kNL; ++k) c->fcnt[i][k] = 0;
     c->big_last = -1;
+    c->bits_level = -1;
+    c->swept = -1;
   }
+  // vertices, with the sinks listed and the labelled hint a word per half
+  // wave (sinks, sources and padding start labelled); then the nets, which
+  // only need their labels and hint words written
   const BlockQ q = bq_bind(lds, g.ctl->bcnt[0], g.list[0]);
-  const int ntiles = sweep_tiles(g);
+  const int lane = lane_id();
+  const int ts = 2 * (int)blockDim.x;
+  const int nvr = (g.NB + 63) & ~63;
+  const int ntiles = (nvr + ts - 1) / ts;
   for (int tile = tile0; tile < ntiles; tile += tstride) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int v = (2 * tile + j) * blockDim.x + threadIdx.x;
+      const int v = (2 * tile + j) * (int)blockDim.x + (int)threadIdx.x;
       bool seed = false;
-      if (v < g.N) {
-        int lab = g.N;
+      int lab = g.N;
+      if (v < g.NB) {
+        lab = g.N + 1;
         if (v < g.V) {
           const int r = g.role[v];
           lab = r == 1 ? g.N + 1 : (r == 2 ? 0 : g.N);
           seed = r == 2;
-        } else if (v < g.NB) {
-          lab = g.N + 1;
         }
         g.d[v] = lab;
         if (g.lev) g.lev[v] = lab == g.N ? 0 : 2;
       }
+      const unsigned long long m = __ballot(lab != g.N);
+      const int w = ((v - lane) >> 5) + lane;
+      if (lane < 2 && v - lane < nvr && 32 * w < g.N) g.seen[w] = (uint32_t)(m >> (32 * lane));
       qpush(g, q, v, seed);
     }
     bq_tile_end(q, 2 * blockDim.x);
   }
   bq_flush(q);
-  // labelled hint: sinks, sources and padding start labelled
-  const int words = (g.N + 31) >> 5;
-  for (int w = tile0 * blockDim.x + threadIdx.x; w < words; w += tstride * blockDim.x) {
-    uint32_t m = 0;
-    const int v0 = w << 5;
-    if (v0 < g.NB) {
-      for (int b = 0; b < 32; ++b) {
-        const int v = v0 + b;
-        if (v >= g.V ? v < g.NB : g.role[v] != 0) m |= 1u << b;
-      }
-    }
-    g.seen[w] = m;
+  const int t0 = tile0 * (int)blockDim.x + (int)threadIdx.x, tn = tstride * (int)blockDim.x;
+  for (int e = t0; e < g.E; e += tn) {
+    *reinterpret_cast<int2*>(g.d + g.NB + 2 * e) = make_int2(g.N, g.N);
+    if (g.lev) g.lev[g.NB + 2 * e] = g.lev[g.NB + 2 * e + 1] = 0;
   }
+  for (int w = nvr / 32 + t0; w < (g.N + 31) >> 5; w += tn) g.seen[w] = 0u;
 }
 
 // Global relabel, step 3: fold outstanding excess deltas; frontier =
-// non-terminal nodes with excess and a label below N; stale relabel
-// candidates dropped.  BFS counters are cleared for the next BFS.
+// non-terminal nodes with excess and a label below N.  BFS counters are
+// cleared for the next BFS.
 __device__ void phase_gather(const Dev& g, int epoch, int tile0, int tstride, lds_int* lds) {
   const int c3 = epoch % 3, cp = epoch & 1;
   if (tile0 == 0 && threadIdx.x == 0) {
@@ -2097,7 +2452,6 @@ __device__ void phase_gather(const Dev& g, int epoch, int tile0, int tstride, ld
           g.dx[0][v] = 0;
           g.dx[1][v] = 0;
         }
-        if (g.cand[v] >= 0) g.cand[v] = -1;
         if (v >= g.NB || (v < g.V && g.role[v] == 0)) act = xv > 0 && g.d[v] < g.N;
       }
       qpush(g, q, v, act);

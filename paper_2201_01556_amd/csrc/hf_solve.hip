@@ -44,13 +44,12 @@ __device__ __forceinline__ int gthreads() { return gridDim.x * blockDim.x; }
 
 __global__ void __launch_bounds__(kThreads) k_init(Dev g) { phase_init(g, gthread(), gthreads()); }
 
-__global__ void __launch_bounds__(kThreads) k_gr_bits(Dev g) {
-  phase_gr_bits(g, gthread(), gthreads());
-}
-
+// Labels, hint and sinks, and the residual bits, which do not depend on them:
+// 52 us in one launch at 7.4M pins.
 __global__ void __launch_bounds__(kBlock) k_gr_reset(Dev g) {
   HF_QUEUE_LDS;
   phase_gr_reset(g, blockIdx.x, gridDim.x, lds);
+  phase_gr_bits(g, gthread(), gthreads());
 }
 
 // One level of the reverse BFS.  A level holding at least `big_min` nodes
@@ -95,9 +94,49 @@ k_bfs_rev_flat(Dev g, int level, int big_min, int pull_min, int tail) {
   if (nf >= pull_min)
     phase_bfs_rev_pull(g, level, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x,
                        KC_BFS_REV);
-  else if (nf >= big_min)
+  else if (g.pinfree && nf >= big_min && g.ctl->bits_level == level) {
+    // left to k_bfs_sweep: the count of the level after next is cleared here
+    if (blockIdx.x == 0 && threadIdx.x < kNL) g.ctl->bcnt[(level + 2) % 3][threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 3) g.ctl->sweep_n[level & 1][threadIdx.x] = 0;
+  } else if (!g.pinfree && nf >= big_min)
     phase_bfs_rev_flat<false>(g, level, blockIdx.x, gridDim.x, KC_BFS_REV, lds);
   else phase_bfs_rev_node<G, true>(g, level, blockIdx.x, gridDim.x, KC_BFS_REV, lds);
+}
+
+// A large level whose bitmaps are there.  Bound by the first-touch loads of the
+// unlabelled nodes' offsets, pins and incidences: 94 us for the first one of a
+// 7.4M-pin relabel and 42 for the last, where expanding from the lists and
+// collecting the next level took 80 to 210.
+__global__ void __launch_bounds__(kBlock) HF_TWO_WORKGROUPS_PER_CU
+k_bfs_sweep(Dev g, int level, int big_min) {
+  __shared__ int32_t area[kSweepWords];
+  if (count_all(g.ctl->bcnt[level % 3]) < big_min || g.ctl->bits_level != level) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) g.ctl->swept = level;
+  phase_bfs_sweep(g, level, KC_BFS_REV, (lds_int*)area);
+}
+
+// After a level that may have been swept.  next_min: from how many nodes on
+// the next level's launch sweeps.  A swept level left the next one's bitmaps
+// and counts: they are enough if it is swept too, else it is listed.  A level
+// that was claimed left lists: bitmaps are added if the next one is to be
+// swept.
+__global__ void __launch_bounds__(kBlock) k_bfs_turn(Dev g, int level, int next_min) {
+  HF_QUEUE_LDS;
+  const int n3 = (level + 1) % 3;
+  const int32_t* const sn = g.ctl->sweep_n[level & 1];
+  const bool swept = g.ctl->swept == level;
+  // a swept level appended nothing, so its counts are read where nothing is
+  // written below
+  const int next = swept ? sn[0] + sn[1] + sn[2] : count_all(g.ctl->bcnt[n3]);
+  const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+  if (next >= next_min) {
+    if (lead) g.ctl->bits_level = level + 1;
+    if (!swept) phase_bfs_collect_bits<false>(g, level, blockIdx.x, gridDim.x, lds);
+    else if (lead)
+      for (int k = 0; k < 3; ++k) g.ctl->bcnt[n3][k] = sn[k];
+  } else if (swept && next > 0) {
+    phase_bfs_collect_bits<true>(g, level, blockIdx.x, gridDim.x, lds);
+  }
 }
 
 // As k_bfs_rev_flat, with expanded levels split in two (XCD-local labels):
@@ -140,8 +179,11 @@ __global__ void __launch_bounds__(kBlock) k_bfs_collect(Dev g, int level, int bi
 
 __global__ void k_clear_frontiers(Dev g) { phase_clear_frontiers(g); }
 
-__global__ void __launch_bounds__(kBlock) k_gather(Dev g, int epoch) {
+// after_bfs: launched behind a batch of BFS levels without knowing whether the
+// search has ended; does nothing if it has not.
+__global__ void __launch_bounds__(kBlock) k_gather(Dev g, int epoch, int after_bfs) {
   HF_QUEUE_LDS;
+  if (after_bfs && !g.ctl->bfs_done) return;
   phase_gather(g, epoch, blockIdx.x, gridDim.x, lds);
 }
 
@@ -313,7 +355,11 @@ __global__ void __launch_bounds__(kBlock) k_bfs_loop(Dev g, int level0, int cap,
   if (mode == 0) levels = wg_bfs<kDirRelabel>(g, level0, cap, ep, KC_LOOP_BFS, lds);
   else if (mode == 1) levels = wg_bfs<kDirSource>(g, level0, cap, ep, KC_LOOP_BFS, lds);
   else levels = wg_bfs<kDirSink>(g, level0, cap, ep, KC_LOOP_BFS, lds);
-  if (threadIdx.x == 0) g.ctl->loop_levels = levels;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    g.ctl->loop_levels = levels;
+    g.ctl->bfs_done = count_all_vol(g.ctl->bcnt[(level0 + levels) % 3]) == 0;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -410,30 +456,41 @@ static fp_status sync_ctl(fp_problem* pb, hipStream_t s, const char* what = "") 
 // Device-wide BFS levels level .. level+steps-1 of the given mode.  With
 // `predict`, a reverse-BFS level that the previous global relabel also
 // reached is sized from that relabel's level and its two neighbours: a level
-// expected to be small runs on a smaller grid (128 workgroups at least) and
+// expected to be small runs on a smaller grid (32 workgroups at least) and
 // may not expand (it claims, so no collect sweep is launched for it).  Both
 // choices change only the schedule: any grid covers any level, and claiming
-// is correct at every size.
+// is correct at every size.  `small`: the search has left its large levels
+// behind (the host knows the current level's size), so none of these is swept.
 template <int G>
 static void launch_levels(fp_problem* pb, hipStream_t s, int ep, int ep_tmp, int mode, int level,
-                          int steps, bool predict) {
+                          int steps, bool predict, bool small) {
   Dev& g = pb->dev;
   const int cap = pb->opt.tail_threshold;
   const int big_min = pb->opt.bottom_up_min > 0 ? pb->opt.bottom_up_min : (1 << 30);
   const int pull_min = pb->opt.pull_min > 0 ? pb->opt.pull_min : (1 << 30);
   const int off = 1 << 30;
+  // largest size expected of a level, from the previous relabel; -1 unknown
+  auto expected = [&](int lv) {
+    if (small) return 0ll;
+    if (!predict || lv >= pb->gr_hist_levels) return -1ll;
+    long long p = 0;
+    for (int j = lv - 1; j <= lv + 1; ++j)
+      if (j >= 0 && j < pb->gr_hist_levels) p = std::max<long long>(p, pb->gr_hist[j]);
+    return p;
+  };
+  auto bound = [&](int lv, int min_nodes) {
+    const long long p = expected(lv);
+    return p >= 0 && 2 * p < min_nodes ? off : min_nodes;
+  };
   for (int i = 0; i < steps; ++i) {
     const int lv = level + i;
     if (mode == 0) {
-      int grid = kMaxFrontierBlocks, bmin = big_min, pmin = pull_min;
-      if (predict && lv < pb->gr_hist_levels) {
-        long long p = 0;
-        for (int j = lv - 1; j <= lv + 1; ++j)
-          if (j >= 0 && j < pb->gr_hist_levels) p = std::max<long long>(p, pb->gr_hist[j]);
-        grid = (int)std::min<long long>(kMaxFrontierBlocks, std::max<long long>(128, (2 * p + 63) / 64));
-        if (2 * p < big_min) bmin = off;
-        if (2 * p < pull_min) pmin = off;
-      }
+      int grid = kMaxFrontierBlocks;
+      const long long p = expected(lv);
+      if (small) grid = kMaxFrontierBlocks / 2;
+      else if (p >= 0)
+        grid = (int)std::min<long long>(kMaxFrontierBlocks, std::max<long long>(32, (2 * p + 63) / 64));
+      const int bmin = bound(lv, big_min), pmin = bound(lv, pull_min);
       const bool xcd = g.xbuf && g.bfs_flat && !g.bfs_arc;
       if (xcd) launch_timed(pb, s, k_bfs_rev_xflat<G>, dim3(grid), dim3(kBlock), g, lv, bmin, pmin, cap);
       else if (g.bfs_flat && !g.bfs_arc)
@@ -443,7 +500,17 @@ static void launch_levels(fp_problem* pb, hipStream_t s, int ep, int ep_tmp, int
         Launch L(pb, s, KK_BFS_REV);
         k_bfs_slices<<<kSlices * 64, kBlock, 0, s>>>(g, lv, bmin, pmin, grid);
       }
-      if (bmin != off || pmin != off) {
+      if (g.pinfree) {
+        const int next_min = i + 1 < steps ? bound(lv + 1, big_min) : off;
+        if (bmin != off) {
+          Launch L(pb, s, KK_BFS_REV);
+          k_bfs_sweep<<<kMaxFrontierBlocks, kBlock, 0, s>>>(g, lv, bmin);
+        }
+        if (bmin != off || next_min != off) {
+          Launch L(pb, s, KK_BFS_COLLECT);
+          k_bfs_turn<<<sweep_blocks(g.N), kBlock, 0, s>>>(g, lv, next_min);
+        }
+      } else if (bmin != off || pmin != off) {
         Launch L(pb, s, KK_BFS_COLLECT);
         k_bfs_collect<<<sweep_blocks(g.N), kBlock, 0, s>>>(g, lv, bmin, pmin);
       }
@@ -509,11 +576,20 @@ static fp_status run_bfs(fp_problem* pb, hipStream_t s, int ep, int mode, int* l
       steps = 8;
       if (mode == 0 && first && use_loop) steps = pb->gr_batch;
     }
+    // a relabel's later batches: the size is known, and a level that is not
+    // large after the large ones is followed by smaller ones
+    const bool small = mode == 0 && !first && use_loop &&
+                       (pb->opt.bottom_up_min <= 0 || nf < pb->opt.bottom_up_min);
+    if (small) steps = std::min(steps, 4);
     first = false;
-    launch_levels<G>(pb, s, ep, ep_tmp, mode, level, steps, predict);
+    launch_levels<G>(pb, s, ep, ep_tmp, mode, level, steps, predict, small);
     if (use_loop) {
       Launch L(pb, s, mode == 0 ? KK_BFS_REV_LOOP : KK_BFS_FWD_LOOP);
       k_bfs_loop<<<1, kBlock, 0, s>>>(g, level + steps, cap, ep, mode);
+    }
+    if (mode == 0 && use_loop) {  // the usual end of a relabel, in the same round trip
+      Launch L(pb, s, KK_GATHER);
+      k_gather<<<sweep_blocks(g.N), kBlock, 0, s>>>(g, pb->epoch, 1);
     }
     st = sync_ctl(pb, s, "bfs");
     if (st) return st;
@@ -539,18 +615,18 @@ static fp_status global_relabel(fp_problem* pb, hipStream_t s) {
   Dev& g = pb->dev;
   {
     Launch L(pb, s, KK_GR_RESET);
-    k_gr_reset<<<sweep_blocks(g.N), kBlock, 0, s>>>(g);
-    k_gr_bits<<<sweep_grid(std::max(g.P, g.E)), kThreads, 0, s>>>(g);
+    k_gr_reset<<<sweep_blocks(std::max(g.N, g.P)), kBlock, 0, s>>>(g);
   }
   int levels = 0;
   fp_status st = run_bfs<G>(pb, s, -1, 0, &levels);
   if (st) return st;
-  {
-    Launch L(pb, s, KK_GATHER);
-    k_gather<<<sweep_blocks(g.N), kBlock, 0, s>>>(g, pb->epoch);
-  }
   pb->st.global_relabels++;
   pb->st.bfs_levels += levels;
+  if (!pb->opt.debug_checks) return FP_OK;  // gathered behind the last levels
+  {
+    Launch L(pb, s, KK_GATHER);
+    k_gather<<<sweep_blocks(g.N), kBlock, 0, s>>>(g, pb->epoch, 0);
+  }
   return sync_ctl(pb, s, "gather");
 }
 
@@ -591,7 +667,7 @@ static fp_status solve_impl(fp_problem* pb, hipStream_t s, int64_t* flow) {
     {
       Launch L(pb, s, KK_GATHER);
       k_clear_frontiers<<<1, 64, 0, s>>>(g);
-      k_gather<<<sweep_blocks(g.N), kBlock, 0, s>>>(g, pb->epoch);
+      k_gather<<<sweep_blocks(g.N), kBlock, 0, s>>>(g, pb->epoch, 0);
     }
     st = sync_ctl(pb, s, "gather");
   } else {

@@ -167,6 +167,47 @@ def test_labels_and_preflow_certificate(hf, oracle_mod, opts):
     assert oracle_mod.cut_weight(hg, vs.astype(bool)) == F
 
 
+def _swept(seed, V, E, long_nets, hubs):
+    """Nets of 2..9 pins, the first `long_nets` with 195..205 of them, every
+    net of the first half with one of `hubs` vertices as well."""
+    rng = np.random.default_rng(seed)
+    nets = []
+    for e in range(E):
+        n = int(rng.integers(195, 206)) if e < long_nets else int(rng.integers(2, 10))
+        pins = set(rng.choice(V, size=n, replace=False).tolist())
+        if hubs and e < E // 2:
+            pins.add(V - 1 - int(rng.integers(hubs)))
+        nets.append(sorted(pins))
+    who = rng.permutation(V - hubs)[:40]
+    return inputs.hypergraph_from_nets(V, nets, rng.integers(1, 5, E), who[:20], who[20:])
+
+
+@pytest.mark.parametrize("V,E,long_nets,hubs", [
+    (1023, 2047, 0, 0), (1024, 2048, 1, 0), (1025, 2049, 3, 0), (1089, 2113, 4, 2),
+    (2049, 2048, 2, 5), (9000, 8001, 620, 3)], ids=str)
+def test_swept_levels(hf, oracle_mod, V, E, long_nets, hubs):
+    """Every multi-kernel reverse-BFS level swept: nets and vertices around
+    the 128 of a wave and the 2,048 of a workgroup, around the arcs a lane
+    looks at itself and those it sets aside, more set aside in a workgroup
+    than it has room for.  Labels, preflow and sides are whole numbers."""
+    hg = _swept(V + E, V, E, long_nets, hubs)
+    _say(f"swept levels V={V} E={E}")
+    r = oracle_mod.maxflow(hg)
+    with hf.FlowProblem.from_hypergraph(hg, bottom_up_min=1, tail_threshold=1) as p:
+        F = p.solve()
+        vs, ns = p.source_side()
+        s = p.export_state(hg.num_pins)
+    assert_same(hg, r, F, vs.astype(bool), ns, f"swept {V} {E}")
+    errs = oracle_mod.check_preflow(hg, s["f_in"], s["f_out"], s["f_b"], F)
+    assert not errs, errs
+    N = ((V + 1) & ~1) + 2 * E
+    dv, din, dout = oracle_mod.residual_labels(hg, s["f_in"], s["f_out"], s["f_b"])
+    lab = s["labels"].astype(np.int64)
+    assert (lab[:V] == np.where(dv == -1, N, np.where(dv == -2, N + 1, dv))).all()
+    assert (lab[V::2] == np.where(din == -1, N, din)).all()
+    assert (lab[V + 1::2] == np.where(dout == -1, N, dout)).all()
+
+
 def test_device_memory_inputs_and_outputs(hf, oracle_mod):
     import torch
     hg = inputs.uniform_hypergraph(42)

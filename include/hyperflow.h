@@ -84,7 +84,7 @@ typedef struct {
                                  2 = only the reverse-BFS level kernel (see
                                  flow_problem_kernel_times)                  */
   int32_t gr_interval;        /* also relabel globally after this many rounds
-                                 since the last global relabel; default 16,
+                                 since the last global relabel; default 10,
                                  -1 = only by relabel count and stale flow  */
   int32_t stale_rounds;       /* also relabel globally once the flow value
                                  stayed unchanged for this many rounds with a
@@ -107,7 +107,7 @@ typedef struct {
                                  (stops at the first); 0 = never            */
   int32_t tail_gr_interval;   /* rounds between global relabels while the
                                  frontier fits the single-workgroup loop
-                                 (tail_threshold); default 4 * gr_interval,
+                                 (tail_threshold); default 5/2 of gr_interval,
                                  -1 = gr_interval                            */
   int32_t bfs_flat;           /* expanded reverse-BFS levels spread the arcs
                                  of a wave's 64 nodes over its lanes; 1 = on

@@ -269,7 +269,14 @@ fp_options resolve_options(const fp_options* o) {
   if (r.tail_threshold <= 0) r.tail_threshold = 256;
   if (r.group_lanes != 4 && r.group_lanes != 8 && r.group_lanes != 16) r.group_lanes = 16;
   if (r.big_degree <= 0) r.big_degree = 32;
-  if (r.gr_interval == 0) r.gr_interval = 16;
+  // Rounds between global relabels, and 2.5 times as many in the
+  // single-workgroup loop, whose rounds cost microseconds.  Intervals 16 (64 in
+  // the loop) / 10 (24) / 8 (24), means over eight seeds in us: V = 2k
+  // 2121 / 2123 / 2087, 12k 3840 / 3681 / 3524, 40k 5475 / 4831 / 4892, 100k
+  // 7166 / 6412 / 6517, 300k 9894 / 8764 / 9430, 1M 15671 / 15330 / 16403,
+  // region problems of 5k, 20k and 40k vertices 2505 / 2489 / 2470,
+  // 2771 / 2574 / 2474, 3729 / 3264 / 3754.
+  if (r.gr_interval == 0) r.gr_interval = 10;
   if (r.gr_interval < 0) r.gr_interval = 0;
   if (r.stale_rounds == 0) r.stale_rounds = 500;
   if (r.stale_rounds < 0) r.stale_rounds = 0;

@@ -117,6 +117,11 @@ struct Ctl {
   int32_t bits_level;  // reverse-BFS level that the level bitmaps describe, -1 none
   int32_t swept;       // last level that was swept (phase_bfs_sweep), -1 none
   int32_t sweep_n[2][3];  // nodes per kind that the sweep of an even (odd) level found
+  int32_t fc_done;        // iterations that the last FlowCutter loop finished
+  int32_t fc_why;         // why it ended (FcExit)
+  int32_t fc_side;        // side that it pierced last or was to pierce next
+  int32_t fc_levels;      // levels of its finished growths
+  int32_t fc_new[2];      // vertices of S_r and T_r listed as not pierced yet
 };
 
 struct Dev {
@@ -292,6 +297,7 @@ constexpr int lds_words(int block) {
 __device__ __forceinline__ int bq_words() { return kNL * kQPerThread * (int)blockDim.x + 2 * kNL; }
 
 typedef __attribute__((address_space(3))) int32_t lds_int;
+typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 
 struct BlockQ {
   lds_int* buf;         // [kNL][cap]
@@ -2685,8 +2691,24 @@ __device__ __forceinline__ void wg_drop_l1() {
 constexpr int kBfsTile = 1024;  // nodes per tile at most (the largest workgroup)
 constexpr int kWgBfsWords = 2 * kNL * kLoopCap + 3 * kBfsTile + 16 + 3 * kNL;
 
-template <int kDir>
-__device__ int wg_bfs(const Dev& g, int level0, int cap, int ep, int kc, lds_int* lds) {
+// With kGrow (the growths of a FlowCutter loop) level0 is 0 and its nodes and
+// counts are in the area already, the vertices reached are listed and weighed,
+// the statistics are left to the caller, and the level reached is written back
+// only if it holds nodes.
+struct Growth {
+  const int32_t* cw;             // vertex weights
+  int32_t* fresh;                // vertices reached, after the *nfresh that are there
+  lds_int* nfresh;
+  lds_u64* weight;
+  uint32_t* next;                // vertices next to the side (bits), those outside both sides at least
+  int other;                     // the other side's stamp
+  unsigned long long nbytes = 0, narcs = 0;
+  int left = 0;                  // nodes of the level reached
+};
+
+template <int kDir, bool kGrow = false>
+__device__ __forceinline__ int wg_bfs(const Dev& g, int level0, int cap, int ep, int kc, lds_int* lds,
+                      Growth* grow = nullptr) {
   lds_int* const buf = lds;  // [2][kNL][kLoopCap]
   lds_int* const t_node = lds + 2 * kNL * kLoopCap;
   lds_int* const t_beg = t_node + kBfsTile;
@@ -2695,7 +2717,7 @@ __device__ int wg_bfs(const Dev& g, int level0, int cap, int ep, int kc, lds_int
   lds_int* const cnt = wsum + 16;  // [3][kNL]
   const int tid = threadIdx.x, lane = lane_id(), wid = uni(tid >> 6), nw = blockDim.x >> 6;
   int level = level0;
-  {
+  if (!kGrow) {
     const int c3 = level % 3, cp = level & 1;
     const Quad n{uni(ld_vol(&g.ctl->bcnt[c3][0])), uni(ld_vol(&g.ctl->bcnt[c3][1])),
                  uni(ld_vol(&g.ctl->bcnt[c3][2])), uni(ld_vol(&g.ctl->bcnt[c3][3]))};
@@ -2742,6 +2764,11 @@ __device__ int wg_bfs(const Dev& g, int level0, int cap, int ep, int kc, lds_int
           if (g.lev) g.lev[v] = 2;
         }
         append(v, word);
+        if (kGrow && v < g.V) {
+          grow->fresh[lds_add(grow->nfresh, 1)] = v;
+          __hip_atomic_fetch_add(grow->weight, (unsigned long long)grow->cw[v], __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
       }
     };
     auto open = [&](int v) {  // not reached yet, as far as a plain load tells
@@ -2827,8 +2854,16 @@ __device__ int wg_bfs(const Dev& g, int level0, int cap, int ep, int kc, lds_int
             if (kDir == kDirRelabel) {
               if ((in ? fp.x : fp.y) > 0 && open(u)) claim(u);
             } else if (kDir == kDirSource) {
-              if (in) {
-                if (g.w[e] - fp.x > 0 && open(u)) claim(u);  // e_in -> u reverse
+              if (in) {  // e_in -> u reverse
+                const bool arc = g.w[e] - fp.x > 0;
+                if (kGrow) {
+                  const int st = g.stamp[u];
+                  if (arc && st != ep) claim(u);
+                  else if (!arc && st != ep && st != grow->other)
+                    atomicOr(&grow->next[u >> 5], 1u << (u & 31));
+                } else if (arc && open(u)) {
+                  claim(u);
+                }
               } else {
                 const int r = g.role[u];  // e_out -> u infinite
                 if (r == 2) hit_sink = true;
@@ -2837,6 +2872,9 @@ __device__ int wg_bfs(const Dev& g, int level0, int cap, int ep, int kc, lds_int
             } else if (in || fp.y > 0) {  // u -> e_in uncapped, u -> e_out by flow
               if (g.role[u] == 1) hit_source = true;
               else if (open(u)) claim(u);
+            } else if (kGrow) {
+              const int st = g.stamp[u];
+              if (st != ep && st != grow->other) atomicOr(&grow->next[u >> 5], 1u << (u & 31));
             }
           }
         }
@@ -2848,6 +2886,15 @@ __device__ int wg_bfs(const Dev& g, int level0, int cap, int ep, int kc, lds_int
   }
   // the level reached back to the global lists
   const int c3 = level % 3, cp = level & 1;
+  if (kGrow) {
+    if (hit_sink) atomicOr(&g.ctl->err, ERR_SINK_REACHED);
+    if (hit_source) atomicOr(&g.ctl->err, ERR_SOURCE_REACHED);
+    grow->nbytes += nbytes_all;
+    grow->narcs += narcs;
+    grow->left = uni(cnt[c3 * kNL]) + uni(cnt[c3 * kNL + 1]) + uni(cnt[c3 * kNL + 2]) +
+                 uni(cnt[c3 * kNL + 3]);
+    if (grow->left == 0) return level - level0;
+  }
 #pragma unroll
   for (int k = 0; k < kNL; ++k) {
     const int c = min((int)cnt[c3 * kNL + k], kLoopCap);
@@ -2856,6 +2903,7 @@ __device__ int wg_bfs(const Dev& g, int level0, int cap, int ep, int kc, lds_int
   }
   if (tid < 3 * kNL)
     g.ctl->bcnt[tid / kNL][tid % kNL] = tid / kNL == c3 ? (int)cnt[tid] : 0;
+  if (kGrow) return level - level0;
   if (hit_sink) atomicOr(&g.ctl->err, ERR_SINK_REACHED);
   if (hit_source) atomicOr(&g.ctl->err, ERR_SOURCE_REACHED);
   block_add_u64(&g.ctl->bytes[kc], nbytes_all + 12ull * narcs, &g.ctl->items[kc], narcs);
@@ -3159,6 +3207,297 @@ __device__ void phase_pierce_sinks(const Dev& g, int ep_t, int t0, int tstride) 
     for (int i = g.vtx_off[v]; i < g.vtx_off[v + 1]; ++i) atomicOr(&g.nflag[g.vinc[i].x], 2);
   }
   block_add_u64(&g.ctl->flow, gained);
+}
+
+// ---------------------------------------------------------------------------
+// FlowCutter iterations inside one workgroup
+//
+// An iteration that pierces a vertex outside S_r and T_r changes no flow: it
+// grows the side pierced last from a few seeds, weighs the sides, picks a
+// vertex and pierces.  Each of these steps touches some tens of nodes, so as
+// launches (eight and a round trip an iteration) it is all start-up and gaps.
+// One workgroup runs them one after another here, until an iteration needs
+// something else: an augmenting path, an end of the run, or work for more
+// than one workgroup.  The steps give what the device-wide ones give: weights
+// are sums, kept up to date by the vertices a growth reaches; a pick is the
+// smallest vertex of its kind, found in a bitmap of the vertices next to the
+// side, in which every growth sets the pins of the net nodes it reaches; a
+// pierce turns the vertices reached since the side's last pierce into
+// terminals, from a list instead of a sweep over all vertices.  Bound by the
+// latency of some 25 dependent accesses and as many barriers an iteration: 17
+// us on a region of 50k vertices and 370k pins, against 41 us of kernels and
+// 56 us in all with launches; a run of 3,500 iterations 193 -> 63 ms.
+// ---------------------------------------------------------------------------
+
+// The bits of the free pins of every net cut by a side (net_cut_flags), into
+// cleared bitmaps.  Lanes take one net each; the cut ones are then scanned by
+// the whole wave.
+__device__ void phase_fc_next(const Dev& g, int ep_s, int ep_t, uint32_t* next_s, uint32_t* next_t,
+                              int t0, int tstride) {
+  const int lane = lane_id();
+  for (int base = t0 - lane; base < g.E; base += tstride) {
+    const int e = base + lane;
+    bool2_t cut{false, false};
+    if (e < g.E) cut = net_cut_flags(g, e, ep_s, ep_t);
+    const unsigned long long ms = __ballot(cut.a);
+    for (unsigned long long m = ms | __ballot(cut.b); m; m &= m - 1) {
+      const int k = __ffsll(m) - 1;
+      const bool of_s = (ms >> k) & 1ull;
+      const bool of_t = __shfl((int)cut.b, k);
+      const int end = g.net_off[base + k + 1];
+      for (int i = g.net_off[base + k] + lane; i < end; i += kWave) {
+        const int u = g.pin_v[i];
+        const int st = g.stamp[u];
+        if (st == ep_s || st == ep_t) continue;
+        if (of_s) atomicOr(&next_s[u >> 5], 1u << (u & 31));
+        if (of_t) atomicOr(&next_t[u >> 5], 1u << (u & 31));
+      }
+    }
+  }
+}
+
+enum FcExit {
+  kFcGrow = 1,    // a growth reached a level too large for the workgroup
+  kFcPick = 2,    // no vertex is outside both sides
+  kFcDecide = 3,  // the iteration stands as if weighed and picked device-wide
+};
+
+struct FcStep {  // one finished iteration
+  long long cs, ct;
+  int32_t p, pad;
+};
+
+struct FcLoop {
+  const int32_t* cw;
+  int32_t* fresh[2];   // vertices of S_r and T_r that are not terminals yet
+  int32_t nfresh[2];   // how many; -1: not listed, they are found by their stamps
+  uint32_t* next[2];   // vertices next to S_r and T_r (bits)
+  FcStep* steps;
+  uint8_t* best;       // most balanced side so far (most_balanced)
+  long long cs, ct;    // weights before the pending growth
+  long long max_src, max_snk, total, best_heavier;
+  int32_t ep_s, ep_t;
+  int32_t side, p;     // pending growth; level 0 of side 0 is in the global lists
+  int32_t lo;          // no vertex below is outside both sides
+  int32_t most_balanced, max_iters, cap;
+};
+
+constexpr int kFcLanes = 16;   // lanes per vertex of a pierce
+constexpr int kFcWide = 512;   // more vertices to pierce are left to a device-wide pierce
+constexpr int kFcWords = kWgBfsWords + kBfsTile + 32;
+
+__device__ void fc_loop(const Dev& g, FcLoop a, lds_int* lds, lds_u64* weight) {
+  lds_int* const buf = lds;
+  lds_int* const cnt = lds + kWgBfsWords - 3 * kNL;  // as wg_bfs lays them out
+  lds_int* const cand = lds + kWgBfsWords;           // a chunk's vertices outside both sides
+  lds_int* const wcnt = cand + kBfsTile;             // per wave
+  lds_int* const best = wcnt + 16;
+  lds_int* const nfresh = wcnt + 17;                 // [2]
+  const int tid = threadIdx.x, lane = lane_id(), wid = uni(tid >> 6), nw = blockDim.x >> 6;
+  const int group = tid / kFcLanes, glane = tid % kFcLanes, ngroups = blockDim.x / kFcLanes;
+  Growth gr{a.cw, nullptr, nullptr, weight, nullptr, 0};
+  // Stamps and bits are set by atomics, and what plain loads of the growths
+  // brought into the vector cache may be older.
+  auto now = [](auto* at) {
+    return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  int listed = (a.nfresh[0] >= 0 ? 1 : 0) | (a.nfresh[1] >= 0 ? 2 : 0);  // bit per side
+  int side = a.side, p = a.p, lo = a.lo, levels = 0, iter = 0, why = 0;
+  int first_free = kInf, pick = kInf;
+  unsigned long long gained = 0;
+  if (tid < 2) nfresh[tid] = max(0, tid == 0 ? a.nfresh[0] : a.nfresh[1]);
+  if (tid < 3 * kNL) cnt[tid] = tid < kNL && side == 0 ? ld_vol(&g.ctl->bcnt[0][tid]) : 0;
+  __syncthreads();
+  if (side == 0) {
+#pragma unroll
+    for (int k = 0; k < kNL; ++k)
+      for (int i = tid; i < min((int)cnt[k], kLoopCap); i += blockDim.x)
+        buf[k * kLoopCap + i] = g.list[0][k][i];
+  } else if (tid == 0) {
+    const int k = list_of(g, p);
+    buf[k * kLoopCap] = p;
+    cnt[k] = 1;
+  }
+  for (;; ++iter) {
+    // ---- growth of `side`
+    if (tid == 0) *weight = 0ull;
+    __syncthreads();
+    gr.fresh = side == 0 ? a.fresh[0] : a.fresh[1];
+    gr.nfresh = nfresh + side;
+    gr.next = side == 0 ? a.next[0] : a.next[1];
+    gr.other = side == 0 ? a.ep_t : a.ep_s;
+    const int lv = side == 0 ? wg_bfs<kDirSource, true>(g, 0, a.cap, a.ep_s, 0, lds, &gr)
+                             : wg_bfs<kDirSink, true>(g, 0, a.cap, a.ep_t, 0, lds, &gr);
+    if (gr.left > 0) {
+      if (tid == 0) g.ctl->loop_levels = lv;
+      listed &= ~(1 << side);  // the rest of the growth is not listed
+      why = kFcGrow;
+      break;
+    }
+    levels += lv;
+    const long long grown = (long long)*weight + a.cw[p];
+    if (side == 0) a.cs += grown;
+    else a.ct += grown;
+    // ---- pick, for the lighter side: the words of its bitmap from `lo` on that
+    // are not empty, in order, then a lane per bit
+    side = a.cs <= a.ct ? 0 : 1;
+    const int want = side == 0 ? a.ep_s : a.ep_t;
+    uint32_t* const next = side == 0 ? a.next[0] : a.next[1];
+    const int words = (g.V + 31) >> 5;
+    first_free = kInf;
+    pick = kInf;
+    if (tid == 0) *best = kInf;
+    // entries of a chunk in order: their number, for those with `in` the place
+    auto ordered = [&](bool in, int value) {
+      const unsigned long long m = __ballot(in);
+      if (lane == 0) wcnt[wid] = __popcll(m);
+      __syncthreads();
+      int before = 0, n = 0;
+      for (int w = 0; w < nw; ++w) {
+        const int t = wcnt[w];
+        if (w < wid) before += t;
+        n += t;
+      }
+      if (in) cand[before + __popcll(m & lanemask_lt())] = value;
+      __syncthreads();
+      return uni(n);
+    };
+    for (int base = lo >> 5; base < words && pick == kInf; base += blockDim.x) {
+      const int w = base + tid;
+      const int n = ordered(w < words && now(next + w) != 0u, w);
+      for (int i0 = 0; i0 < n && pick == kInf; i0 += (int)blockDim.x / 32) {
+        const int i = i0 + tid / 32;
+        const int at = i < n ? (int)cand[i] : 0;
+        const uint32_t bits = i < n ? now(next + at) : 0u;
+        const int u = 32 * at + (tid & 31);
+        bool out = false;
+        if ((bits >> (tid & 31)) & 1u) {
+          const int st = now(g.stamp + u);
+          out = st != a.ep_s && st != a.ep_t;
+        }
+        if (out) __hip_atomic_fetch_min(best, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const uint32_t left = (uint32_t)(__ballot(out) >> (lane & 32));
+        if ((tid & 31) == 0 && left != bits) next[at] = left;  // the others are in a side now
+        __syncthreads();
+        pick = uni(*best);
+        __syncthreads();
+      }
+    }
+    for (; pick == kInf && first_free == kInf && lo < g.V; lo += blockDim.x) {
+      const int u = lo + tid;
+      const int st = u < g.V ? now(g.stamp + u) : a.ep_s;
+      const int n = ordered(st != a.ep_s && st != a.ep_t, u);
+      if (n > 0) first_free = uni(cand[0]);
+      if (n > 0) break;
+    }
+    if (first_free != kInf) lo = first_free;
+    if (pick == kInf && first_free == kInf) {
+      why = kFcPick;
+      break;
+    }
+    // ---- what the iteration does next
+    const bool bal0 = a.cs <= a.max_src && a.total - a.cs <= a.max_snk;
+    const bool bal1 = a.total - a.ct <= a.max_src && a.ct <= a.max_snk;
+    if ((!a.most_balanced && (bal0 || bal1)) || iter + 1 == a.max_iters) {
+      why = kFcDecide;
+      break;
+    }
+    int32_t* const fresh = side == 0 ? a.fresh[0] : a.fresh[1];
+    if (!((listed >> side) & 1)) {
+      if (tid == 0) nfresh[side] = 0;
+      __syncthreads();
+      for (int v = tid; v < g.V; v += blockDim.x)
+        if (now(g.stamp + v) == want && g.role[v] == 0) fresh[lds_add(nfresh + side, 1)] = v;
+      __syncthreads();
+      listed |= 1 << side;
+    }
+    int n = uni(nfresh[side]);
+    if (n > kFcWide) {
+      why = kFcDecide;
+      break;
+    }
+    if (a.most_balanced && (bal0 || bal1))
+      for (int kind = 0; kind < 2; ++kind) {
+        if (!(kind == 0 ? bal0 : bal1)) continue;
+        const long long src = kind == 0 ? a.cs : a.total - a.ct;
+        const long long heavier = max(src, a.total - src);
+        if (a.best_heavier >= 0 && heavier >= a.best_heavier) continue;
+        a.best_heavier = heavier;
+        const int ep = kind == 0 ? a.ep_s : a.ep_t;
+        for (int v = tid; v < g.V; v += blockDim.x)
+          a.best[v] = (uint8_t)((now(g.stamp + v) == ep) != (kind != 0));
+      }
+    p = pick != kInf ? pick : first_free;
+    if (tid == 0) {
+      a.steps[iter] = FcStep{a.cs, a.ct, p, 0};
+      g.stamp[p] = want;
+      fresh[n] = p;
+    }
+    if (tid < 3 * kNL) cnt[tid] = 0;
+    ++n;
+    __syncthreads();  // the list is complete, the stamps have been read
+    // ---- pierce
+    for (int i = group; i < n; i += ngroups) {
+      const int v = fresh[i];
+      if (g.role[v] != 0) continue;
+      const int end = g.vtx_off[v + 1];
+      if (side == 0) {
+        if (glane == 0) {
+          g.role[v] = 1;
+          g.d[v] = g.N + 1;
+        }
+        for (int j = g.vtx_off[v] + glane; j < end; j += kFcLanes) {
+          const int2 ef = cancel_source_pin(g, j);
+          const int ein = g.NB + 2 * ef.x;
+          auto seed = [&](int node) {
+            const int k = list_of(g, node);
+            const int pos = lds_add(cnt + k, 1);
+            if (pos < kLoopCap) buf[k * kLoopCap + pos] = node;
+            else g.list[0][k][pos] = node;
+          };
+          if (stamp_first(g, ein, a.ep_s)) seed(ein);
+          if (ef.y > 0 && stamp_first(g, ein + 1, a.ep_s)) seed(ein + 1);
+        }
+      } else {
+        if (glane == 0) {
+          g.role[v] = 2;
+          const int xv = g.x[v];
+          if (xv > 0) {
+            gained += (unsigned long long)xv;
+            g.x[v] = 0;
+          }
+        }
+        for (int j = g.vtx_off[v] + glane; j < end; j += kFcLanes)
+          atomicOr(&g.nflag[g.vinc[j].x], 2);
+      }
+    }
+    if (tid == 0) {
+      nfresh[side] = 0;
+      if (side == 1) {
+        const int k = list_of(g, p);
+        buf[k * kLoopCap] = p;
+        cnt[k] = 1;
+      }
+    }
+  }
+  __syncthreads();
+  if (why != kFcGrow && tid < 3 * kNL) g.ctl->bcnt[tid / kNL][tid % kNL] = 0;
+  if (tid == 0) {
+    Ctl* const c = g.ctl;
+    c->side_weight[0] = (unsigned long long)a.cs;
+    c->side_weight[1] = (unsigned long long)a.ct;
+    for (int i = 0; i < 5; ++i) c->pierce[i] = kInf;
+    c->pierce[2] = first_free != kInf || why == kFcPick ? first_free : lo;  // from here on
+    c->pierce[3 * side] = pick;
+    c->fc_done = iter;
+    c->fc_why = why;
+    c->fc_side = side;
+    c->fc_levels = levels;
+    for (int i = 0; i < 2; ++i) c->fc_new[i] = (listed >> i) & 1 ? (int)nfresh[i] : -1;
+  }
+  block_add_u64(&g.ctl->flow, gained);
+  block_add_u64(&g.ctl->bytes[KC_LOOP_BFS], gr.nbytes + 12ull * gr.narcs, &g.ctl->items[KC_LOOP_BFS],
+                gr.narcs);
 }
 
 // Stamp the given vertices with ep; a vertex that is a terminal of kind

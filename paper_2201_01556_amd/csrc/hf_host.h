@@ -62,9 +62,13 @@ struct FcRun {
   long long pend_before = 0, pend_count = 0, pend_goal = -1;
   // reachable sets kept across a pierce without augmenting path
   int prev_ep_s = -1, prev_ep_t = -1, grow = -1, grow_vertex = -1;
-  bool seeded = false;
+  // vertices of S_r and T_r that are listed as not pierced yet (-1: not
+  // listed), and a bound below which every vertex is in one of the sides
+  int32_t fresh[2] = {-1, -1};
+  int32_t lo = 0;
+  bool next_known = false;  // the bitmaps of the vertices next to S_r and T_r are up to date
   int64_t last_F = 0;
-  long long last_cs = 0;
+  long long last_cs = 0, last_ct = 0;
   int out_ep = -1, out_invert = 0;
 };
 
@@ -90,7 +94,7 @@ struct fp_problem {
   bool warm_labels = false;  // the labels are valid for the next solve (after a source pierce)
   bool labels_exact = false;  // the labels are exact distances of the current flow (a solve ended)
   int32_t* cw = nullptr;     // vertex weights of the last FlowCutter run (device)
-  void* fc_mem = nullptr;    // FlowCutter scratch: candidate flags, tile counts, best side
+  void* fc_mem = nullptr;    // FlowCutter scratch (FcMem)
   hf::FcRun fc;
   fp_stats st{};
   // profiling

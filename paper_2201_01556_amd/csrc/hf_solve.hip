@@ -362,6 +362,22 @@ __global__ void __launch_bounds__(kBlock) k_bfs_loop(Dev g, int level0, int cap,
   }
 }
 
+__global__ void __launch_bounds__(kThreads) k_zero_words(uint32_t* w, int n) {
+  for (int i = gthread(); i < n; i += gthreads()) w[i] = 0u;
+}
+
+__global__ void __launch_bounds__(kThreads) k_fc_next(Dev g, int ep_s, int ep_t, uint32_t* next_s,
+                                                      uint32_t* next_t) {
+  phase_fc_next(g, ep_s, ep_t, next_s, next_t, gthread(), gthreads());
+}
+
+// FlowCutter iterations inside one workgroup (fc_loop) until one needs more.
+__global__ void __launch_bounds__(kBlock) k_fc_loop(Dev g, FcLoop a) {
+  __shared__ int32_t area[kFcWords];
+  __shared__ unsigned long long weight;
+  fc_loop(g, a, (lds_int*)area, (lds_u64*)&weight);
+}
+
 // ---------------------------------------------------------------------------
 // host orchestration
 // ---------------------------------------------------------------------------
@@ -980,30 +996,7 @@ static fp_status grow_side(fp_problem* pb, hipStream_t s, int side, int ep, int 
   }
 }
 
-// The same growth without host round trips, for the common case of a small
-// one: seeds, then the single-workgroup loop from level 0, nothing read back.
-// The caller launches its side-weight and candidate kernels behind it, reads
-// everything in one round trip, and calls grow_side_finish when the loop
-// stopped at a level too large for it (its count is then nonzero).
-template <int G>
-static fp_status grow_side_start_impl(fp_problem* pb, hipStream_t s, int side, int ep, int p,
-                                      bool seeded) {
-  Dev& g = pb->dev;
-  if (!seeded) {  // else the source pierce listed level 0 (apply_pierce)
-    k_reset_bfs<<<1, 64, 0, s>>>(g);
-    if (side == 0) k_cut_seed<<<sweep_blocks(g.N), kBlock, 0, s>>>(g, ep, 1);
-    else k_seed_vertex<<<1, 64, 0, s>>>(g, p);
-  }
-  {
-    Launch L(pb, s, KK_BFS_FWD_LOOP);
-    k_bfs_loop<<<1, kBlock, 0, s>>>(g, 0, pb->opt.tail_threshold, ep, side == 0 ? 1 : 2);
-  }
-  hipError_t he = hipGetLastError();
-  if (he != hipSuccess) return hip_fail(he, "growing a reachable set");
-  return FP_OK;
-}
-
-// Finish a growth that grow_side_start left at `level` (nf nodes) with
+// Finish a growth that a FlowCutter loop left at `level` (nf nodes) with
 // device-wide levels, and clear the BFS counters and FlowCutter outputs.
 template <int G>
 static fp_status grow_side_finish_impl(fp_problem* pb, hipStream_t s, int side, int ep, int level,
@@ -1014,15 +1007,6 @@ static fp_status grow_side_finish_impl(fp_problem* pb, hipStream_t s, int side, 
   pb->st.bfs_levels += levels - level;
   k_reset_bfs<<<1, 64, 0, s>>>(pb->dev);
   return FP_OK;
-}
-
-static fp_status grow_side_start(fp_problem* pb, hipStream_t s, int side, int ep, int p,
-                                 bool seeded) {
-  switch (pb->opt.group_lanes) {
-    case 4: return grow_side_start_impl<4>(pb, s, side, ep, p, seeded);
-    case 16: return grow_side_start_impl<16>(pb, s, side, ep, p, seeded);
-    default: return grow_side_start_impl<8>(pb, s, side, ep, p, seeded);
-  }
 }
 
 static fp_status grow_side_finish(fp_problem* pb, hipStream_t s, int side, int ep, int level,
@@ -1061,9 +1045,9 @@ fp_status sink_side_problem(fp_problem* pb, hipStream_t s, int32_t mem_kind, uin
 }
 
 // Turn S_r (side 0) or T_r (side 1), stamped ep, plus the stamped piercing
-// vertices into terminals.  With seed_growth (a source pierce that avoids
-// augmenting paths, whose S_r the next iteration grows) the pierce also lists
-// the growth's level 0, after clearing the BFS counters and FlowCutter outputs.
+// vertices into terminals.  With seed_growth (a pierce that avoids augmenting
+// paths, whose side the next iteration grows) a source pierce also lists the
+// growth's level 0, after clearing the BFS counters and FlowCutter outputs.
 static fp_status apply_pierce(fp_problem* pb, hipStream_t s, int side, int ep,
                               bool seed_growth = false) {
   Dev& g = pb->dev;
@@ -1159,6 +1143,39 @@ static void fc_side_stats(fp_problem* pb, hipStream_t s, int ep_s, int ep_t) {
   k_fc_pick<<<grid, kThreads, 0, s>>>(pb->dev, ep_s, ep_t);
 }
 
+// Iterations of one FlowCutter loop at most.
+constexpr int kFcSteps = 512;
+
+// FlowCutter scratch of a handle.
+struct FcMem {
+  size_t bytes = 0;
+  FcStep* steps = nullptr;         // a loop's finished iterations
+  int32_t* fresh[2] = {};          // per side: vertices not pierced yet
+  uint32_t* next[2] = {};          // per side: bits of the vertices next to it
+  int words = 0;                   // of each of the two, which lie side by side
+  uint8_t* flags = nullptr;        // candidates of a bulk pierce
+  int32_t* tile_counts = nullptr;
+  uint8_t* best_side = nullptr;    // most balanced side so far
+  int ntiles = 0;
+  FcMem(void* mem, int32_t V) {
+    ntiles = (V + kBlock - 1) / kBlock;
+    char* const base = static_cast<char*>(mem);
+    auto take = [&](size_t n) {
+      char* const at = base + bytes;
+      bytes += (n + 7) & ~(size_t)7;
+      return at;
+    };
+    steps = reinterpret_cast<FcStep*>(take(kFcSteps * sizeof(FcStep)));
+    for (int i = 0; i < 2; ++i) fresh[i] = reinterpret_cast<int32_t*>(take(4 * (size_t)V));
+    words = (V + 31) / 32;
+    next[0] = reinterpret_cast<uint32_t*>(take(8 * (size_t)words));
+    next[1] = next[0] + words;
+    flags = reinterpret_cast<uint8_t*>(take((size_t)V));
+    tile_counts = reinterpret_cast<int32_t*>(take(4 * ((size_t)ntiles + 1)));
+    best_side = reinterpret_cast<uint8_t*>(take((size_t)V));
+  }
+};
+
 // Up to `slice` more iterations of the FlowCutter run held in pb->fc (see
 // flowcutter_problem); trace[0 .. slice) receives this call's iterations.
 static fp_status flowcutter_run(fp_problem* pb, int32_t slice, hipStream_t s, int32_t mem_kind,
@@ -1176,18 +1193,36 @@ static fp_status flowcutter_run(fp_problem* pb, int32_t slice, hipStream_t s, in
   const int64_t max_src = f.max_src, max_snk = f.max_snk;
   const int32_t bulk_percent = f.bulk_percent, most_balanced = f.most_balanced;
   hipError_t he = hipSuccess;
-  const int ntiles = (pb->V + kBlock - 1) / kBlock;
-  const size_t flag_bytes = ((size_t)pb->V + 3) & ~(size_t)3;
-  const size_t count_bytes = 4 * ((size_t)ntiles + 1);
-  // [flags: V bytes][tile counts][most balanced side so far: V bytes]
-  uint8_t* flags = static_cast<uint8_t*>(pb->fc_mem);
-  int32_t* tile_counts = flags ? reinterpret_cast<int32_t*>(flags + flag_bytes) : nullptr;
-  uint8_t* best_side = flags ? flags + flag_bytes + count_bytes : nullptr;
+  const FcMem mem(pb->fc_mem, pb->V);
+  const int ntiles = mem.ntiles;
+  uint8_t* const flags = mem.flags;
+  int32_t* const tile_counts = mem.tile_counts;
+  uint8_t* const best_side = mem.best_side;
   uint8_t* vs = mem_kind == 0 ? reinterpret_cast<uint8_t*>(pb->dev.list[1][kBigList]) : vside;
   fp_cutter_result& r = f.r;
   r.status = 2;  // iteration limit unless a branch below decides
   int32_t done_here = 0;
   bool side_written = false;  // the limit's result side, written before the last pierce
+  // iterations that a loop on the device has finished and the host has not
+  // booked yet; then the one at which it ended
+  std::vector<FcStep> steps;
+  size_t next_step = 0;
+  bool loop_ended = false;
+  f.fresh[0] = f.fresh[1] = -1;
+  // pierce side by vertex p, outside S_r and T_r; a booked one is done
+  auto pierce_free = [&](int side, int p, bool booked) -> fp_status {
+    f.grow = side;
+    f.grow_vertex = p;
+    pb->labels_exact = false;
+    pb->solved = false;
+    if (booked) return FP_OK;
+    const int ep = side == 0 ? f.prev_ep_s : f.prev_ep_t;
+    k_stamp_vertex<<<1, 64, 0, s>>>(g, p, ep);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "marking the piercing vertex");
+    f.fresh[side] = 0;
+    return apply_pierce(pb, s, side, ep, !pb->opt.debug_checks);
+  };
   for (int32_t n = 0; n < slice; ++n) {
     const int32_t it = ++f.it;
     ++done_here;
@@ -1209,44 +1244,102 @@ static fp_status flowcutter_run(fp_problem* pb, int32_t slice, hipStream_t s, in
       }
     }
     f.last_F = F;
-    int ep_s = 0, ep_t = 0;
-    const int grown = f.grow;
-    const bool spec = f.grow >= 0 && !pb->opt.debug_checks;  // growth without round trips
-    f.seeded = f.seeded && spec;
-    if (f.grow >= 0) {
-      ep_s = f.prev_ep_s;
-      ep_t = f.prev_ep_t;
-      const int ep = f.grow == 0 ? ep_s : ep_t;
-      st = spec ? grow_side_start(pb, s, f.grow, ep, f.grow_vertex, f.seeded)
-                : grow_side(pb, s, f.grow, ep, f.grow_vertex);
+    int ep_s = f.prev_ep_s, ep_t = f.prev_ep_t;
+    const FcStep* booked = nullptr;  // the device has done this iteration's steps
+    if (f.grow >= 0 && !pb->opt.debug_checks) {
+      if (!loop_ended) {
+        FcLoop a{};
+        a.cw = pb->cw;
+        for (int i = 0; i < 2; ++i) {
+          a.fresh[i] = mem.fresh[i];
+          a.nfresh[i] = f.fresh[i];
+          a.next[i] = mem.next[i];
+        }
+        if (!f.next_known) {
+          k_zero_words<<<sweep_grid(2ll * mem.words), kThreads, 0, s>>>(mem.next[0], 2 * mem.words);
+          k_fc_next<<<sweep_grid(pb->E), kThreads, 0, s>>>(g, ep_s, ep_t, mem.next[0], mem.next[1]);
+        }
+        a.steps = mem.steps;
+        a.best = best_side;
+        a.cs = f.last_cs;
+        a.ct = f.last_ct;
+        a.max_src = max_src;
+        a.max_snk = max_snk;
+        a.total = total;
+        a.best_heavier = f.best_heavier;
+        a.ep_s = ep_s;
+        a.ep_t = ep_t;
+        a.side = f.grow;
+        a.p = f.grow_vertex;
+        a.lo = f.lo;
+        a.most_balanced = most_balanced;
+        a.max_iters = std::min(slice - n, kFcSteps);
+        a.cap = pb->opt.tail_threshold;
+        {
+          Launch L(pb, s, KK_BFS_FWD_LOOP);
+          k_fc_loop<<<1, kBlock, 0, s>>>(g, a);
+        }
+        st = sync_ctl(pb, s);
+        if (st) return st;
+        const Ctl& c = *pb->ctl_h;
+        if (c.fc_done < 0 || c.fc_done >= a.max_iters) {
+          set_error("internal check: a FlowCutter loop of %d iterations reports %d", a.max_iters,
+                    c.fc_done);
+          return FP_ERR_DEVICE;
+        }
+        pb->st.bfs_levels += c.fc_levels;
+        for (int i = 0; i < 2; ++i) f.fresh[i] = c.fc_new[i];
+        f.next_known = c.fc_why != kFcGrow;  // the rest of the growth does not set bits
+        steps.resize((size_t)c.fc_done);
+        next_step = 0;
+        loop_ended = true;
+        if (c.fc_done > 0) {
+          he = hipMemcpyAsync(steps.data(), mem.steps, steps.size() * sizeof(FcStep),
+                              hipMemcpyDeviceToHost, s);
+          if (he == hipSuccess) he = hipStreamSynchronize(s);
+          if (he != hipSuccess) return hip_fail(he, "reading the FlowCutter iterations");
+        }
+      }
+      if (next_step < steps.size()) {
+        booked = &steps[next_step++];
+      } else {  // the iteration at which the loop ended
+        loop_ended = false;
+        if (pb->ctl_h->fc_why == kFcGrow) {  // the growth outgrew the workgroup
+          const int lv = pb->ctl_h->loop_levels, side = pb->ctl_h->fc_side;
+          pb->st.bfs_levels += lv;
+          st = grow_side_finish(pb, s, side, side == 0 ? ep_s : ep_t, lv,
+                                host_count(pb->ctl_h->bcnt[lv % 3]));
+          if (st) return st;
+        } else if (pb->ctl_h->fc_why == kFcPick) {
+          k_reset_bfs<<<1, 64, 0, s>>>(g);
+        }
+        if (pb->ctl_h->fc_why != kFcDecide) {
+          fc_side_stats(pb, s, ep_s, ep_t);
+          st = sync_ctl(pb, s);
+          if (st) return st;
+        }
+      }
     } else {
-      st = sides(pb, s, 3, &ep_s, &ep_t);
+      if (f.grow >= 0)
+        st = grow_side(pb, s, f.grow, f.grow == 0 ? ep_s : ep_t, f.grow_vertex);
+      else st = sides(pb, s, 3, &ep_s, &ep_t);
+      if (st) return st;
+      f.fresh[0] = f.fresh[1] = -1;
+      f.next_known = false;
+      fc_side_stats(pb, s, ep_s, ep_t);
+      st = sync_ctl(pb, s);
+      if (st) return st;
     }
-    if (st) return st;
     f.grow = -1;
     f.prev_ep_s = ep_s;
     f.prev_ep_t = ep_t;
-    fc_side_stats(pb, s, ep_s, ep_t);
-    st = sync_ctl(pb, s);
-    if (st) return st;
-    if (spec) {
-      const int lv = pb->ctl_h->loop_levels;
-      const long long nf = host_count(pb->ctl_h->bcnt[lv % 3]);
-      pb->st.bfs_levels += lv;
-      if (nf > 0) {  // the growth outgrew the single-workgroup loop
-        st = grow_side_finish(pb, s, grown, grown == 0 ? ep_s : ep_t, lv, nf);
-        if (st) return st;
-        fc_side_stats(pb, s, ep_s, ep_t);
-        st = sync_ctl(pb, s);
-        if (st) return st;
-      }
-    }
     if (pb->ctl_h->err & (ERR_SINK_REACHED | ERR_SOURCE_REACHED)) {
       set_error("internal check: a pierce without augmenting path connected a source and a sink");
       return FP_ERR_DEVICE;
     }
-    const long long cs = (long long)pb->ctl_h->side_weight[0];
-    const long long ct = (long long)pb->ctl_h->side_weight[1];
+    const long long cs = booked ? booked->cs : (long long)pb->ctl_h->side_weight[0];
+    const long long ct = booked ? booked->ct : (long long)pb->ctl_h->side_weight[1];
+    if (!booked) f.lo = pb->ctl_h->pierce[2];
     if (f.pend_side >= 0) {  // gain of the side pierced last iteration
       const int ps = f.pend_side;
       const long long gain = std::max(0ll, (ps == 0 ? cs : ct) - f.pend_before);
@@ -1259,6 +1352,7 @@ static fp_status flowcutter_run(fp_problem* pb, int32_t slice, hipStream_t s, in
     r.flow = F;
     f.out_ep = ep_s;  // the iteration limit reports this iteration's S_r
     f.last_cs = cs;
+    f.last_ct = ct;
     fp_cutter_step step{};
     step.flow = F;
     step.source_weight = cs;
@@ -1302,13 +1396,15 @@ static fp_status flowcutter_run(fp_problem* pb, int32_t slice, hipStream_t s, in
         f.best_src = src;
         f.best_snk = total - src;
         f.best_F = F;
+        if (booked) continue;
         k_side_out<<<sweep_grid(pb->V), kThreads, 0, s>>>(g, kind == 0 ? ep_s : ep_t, kind,
                                                           best_side);
         he = hipGetLastError();
         if (he != hipSuccess) return hip_fail(he, "keeping the most balanced cut");
       }
       const int side = cs <= ct ? 0 : 1;
-      int p = pb->ctl_h->pierce[3 * side];  // a free boundary pin, else any free vertex
+      // a free boundary pin, else any free vertex
+      int p = booked ? booked->p : pb->ctl_h->pierce[3 * side];
       if (p == kInf) p = pb->ctl_h->pierce[2];
       if (p == kInf) {
         r.status = 0;  // finished: the best cut kept is the result, nothing to resume
@@ -1317,19 +1413,13 @@ static fp_status flowcutter_run(fp_problem* pb, int32_t slice, hipStream_t s, in
         step.side = side;
         step.node = p;
         step.count = 1;
-        f.grow = side;
-        f.grow_vertex = p;
-        k_stamp_vertex<<<1, 64, 0, s>>>(g, p, side == 0 ? ep_s : ep_t);
-        he = hipGetLastError();
-        if (he != hipSuccess) return hip_fail(he, "marking the piercing vertex");
-        f.seeded = side == 0 && !pb->opt.debug_checks;
-        st = apply_pierce(pb, s, side, side == 0 ? ep_s : ep_t, f.seeded);
+        st = pierce_free(side, p, booked != nullptr);
         if (st) return st;
       }
     } else {
       const int side = cs <= ct ? 0 : 1;
       // a free boundary pin, else any free vertex, else an augmenting pin
-      int p = pb->ctl_h->pierce[3 * side];
+      int p = booked ? booked->p : pb->ctl_h->pierce[3 * side];
       bool aug = false;
       if (p == kInf) p = pb->ctl_h->pierce[2];
       if (p == kInf) {
@@ -1366,10 +1456,6 @@ static fp_status flowcutter_run(fp_problem* pb, int32_t slice, hipStream_t s, in
           side_written = true;
         }
         if (aug) r.augmenting++;
-        else {
-          f.grow = side;
-          f.grow_vertex = p;
-        }
         const int ep = side == 0 ? ep_s : ep_t;
         const long long weight = side == 0 ? cs : ct;
         long long k = 1, goal = -1;
@@ -1382,7 +1468,7 @@ static fp_status flowcutter_run(fp_problem* pb, int32_t slice, hipStream_t s, in
         long long count = 1;
         if (k > 1) {
           // the k smallest-id augmenting candidates of this side
-          he = hipMemsetAsync(flags, 0, flag_bytes, s);
+          he = hipMemsetAsync(flags, 0, (size_t)pb->V, s);
           if (he != hipSuccess) return hip_fail(he, "clearing the candidate flags");
           k_fc_mark_augmenting<<<sweep_grid(pb->E), kThreads, 0, s>>>(g, side, ep_s, ep_t, flags);
           k_count_flags<<<ntiles, kBlock, 0, s>>>(flags, pb->V, tile_counts);
@@ -1396,7 +1482,7 @@ static fp_status flowcutter_run(fp_problem* pb, int32_t slice, hipStream_t s, in
           if (he == hipSuccess) he = hipStreamSynchronize(s);
           if (he != hipSuccess) return hip_fail(he, "selecting the piercing vertices");
           count = std::min<long long>(k, found);
-        } else {
+        } else if (aug) {
           k_stamp_vertex<<<1, 64, 0, s>>>(g, p, ep);
           he = hipGetLastError();
           if (he != hipSuccess) return hip_fail(he, "marking the piercing vertex");
@@ -1407,14 +1493,17 @@ static fp_status flowcutter_run(fp_problem* pb, int32_t slice, hipStream_t s, in
         f.pend_before = weight;
         f.pend_count = count;
         f.pend_goal = goal;
-        f.seeded = !aug && side == 0 && !pb->opt.debug_checks;
-        st = apply_pierce(pb, s, side, ep, f.seeded);
+        st = aug ? apply_pierce(pb, s, side, ep) : pierce_free(side, p, booked != nullptr);
         if (st) return st;
         // an augmenting source pierce is followed by a solve that keeps the labels
         pb->warm_labels = aug && side == 0;
       }
     }
     if (trace) trace[n] = step;
+    if (done && booked) {
+      set_error("internal check: a FlowCutter loop ran past the end of its run");
+      return FP_ERR_DEVICE;
+    }
     if (done) break;
   }
   if (f.grow >= 0) {
@@ -1424,7 +1513,6 @@ static fp_status flowcutter_run(fp_problem* pb, int32_t slice, hipStream_t s, in
     // and a continued run re-derives its sides (a warm solve, same result)
     k_reset_bfs<<<1, 64, 0, s>>>(g);
     f.grow = -1;
-    f.seeded = false;
   }
   fp_cutter_result out = r;
   out.first_balanced = f.first_balanced;
@@ -1493,11 +1581,8 @@ fp_status flowcutter_problem(fp_problem* pb, const int32_t* vw, int64_t max_src,
   }
   he = hipMemcpyAsync(pb->cw, vw, (size_t)pb->V * sizeof(int32_t), hipMemcpyHostToDevice, s);
   if (he != hipSuccess) return hip_fail(he, "copying vertex weights");
-  if ((bulk_percent > 0 || most_balanced) && !pb->fc_mem) {
-    const int ntiles = (pb->V + kBlock - 1) / kBlock;
-    const size_t flag_bytes = ((size_t)pb->V + 3) & ~(size_t)3;
-    const size_t count_bytes = 4 * ((size_t)ntiles + 1);
-    he = hipMalloc(&pb->fc_mem, 2 * flag_bytes + count_bytes);
+  if (!pb->fc_mem) {
+    he = hipMalloc(&pb->fc_mem, FcMem(nullptr, pb->V).bytes);
     if (he != hipSuccess) {
       pb->fc_mem = nullptr;
       return hip_fail(he, "allocating the FlowCutter scratch");

@@ -465,3 +465,28 @@ def test_flowcutter_zipf_checkpoints_vs_oracle(hf, oracle_mod, bulk):
     assert ref.status == "balanced"
     assert (x.astype(bool) == ref.vertex_side.astype(bool)).all()
     assert oracle_mod.cut_weight(hg, x.astype(bool)) == res["flow"]
+
+
+@pytest.mark.parametrize("V,E,star,opts", [
+    (31, 12, 0, {}), (32, 12, 0, {}), (33, 12, 0, {}), (63, 40, 0, {}), (65, 40, 9, {}),
+    (1023, 300, 0, {}), (1025, 900, 40, dict(tail_threshold=8)), (1700, 300, 0, {}),
+    (2500, 1200, 700, {}), (2500, 1200, 700, dict(tail_threshold=4096))], ids=str)
+@pytest.mark.parametrize("most_balanced", [False, True])
+def test_flowcutter_loop_edges_vs_oracle(hf, oracle_mod, V, E, star, opts, most_balanced):
+    """Iterations run inside one workgroup: sparse networks, where most
+    vertices are next to neither side and the pick falls back to the smallest
+    vertex outside both; sizes around the words of the bitmaps; more iterations
+    than one loop books; one net with many pins, whose growth is too large for
+    the loop, or fits it and leaves more vertices to pierce than it takes."""
+    rng = np.random.default_rng(V + E + star)
+    nets = [sorted(rng.choice(V, size=int(rng.integers(2, 4)), replace=False).tolist())
+            for _ in range(E)]
+    if star:
+        nets[E // 2] = sorted(rng.choice(V, size=star, replace=False).tolist())
+    who = rng.permutation(V)[:6]
+    hg = inputs.hypergraph_from_nets(V, nets, rng.integers(1, 4, E), who[:3], who[3:])
+    c = rng.integers(1, 4, V)
+    L = balance_limit(c.sum())
+    _say(f"loop edges V={V} star={star} {opts} most_balanced={most_balanced}")
+    _compare_cutter(hf, oracle_mod, hg, c, L, L, 4000, f"loop edges {V} {star}",
+                    most_balanced=most_balanced, **opts)

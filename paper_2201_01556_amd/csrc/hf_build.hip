@@ -20,13 +20,16 @@ namespace hf {
 
 // ---------------------------------------------------------------------------
 // Reuse of released device pools and pinned control blocks.  A handle's pool
-// is one hipMalloc (hundreds of MB for large problems) and its control block
+// is one hipMalloc (hundreds of MB for large problems), the scratch memory of a
+// region build a few of them (hf_regions.hip), and a handle's control block
 // one pinned host allocation; creating and destroying handles in a loop
 // would otherwise pay both every time.  Released blocks are kept per device
 // (at most kCachedPoolBytes of pools and kCachedCtl control blocks) and
 // reused for a request they cover without wasting more than half of them.
-// Handles are destroyed only after their device work has finished, so a
-// cached block is idle.
+// Handles are destroyed only after their device work has finished, and scratch
+// memory is released behind a synchronization of its stream, so a cached block
+// is idle.  A request that the device refuses empties the cache and is tried
+// again.
 // ---------------------------------------------------------------------------
 
 constexpr size_t kCachedPoolBytes = 4ull << 30;
@@ -42,7 +45,7 @@ static std::mutex g_cache_mu;
 static std::vector<CachedPool> g_pools;
 static std::vector<void*> g_ctls;
 
-static hipError_t pool_acquire(int device, size_t bytes, void** out, size_t* got) {
+hipError_t pool_acquire(int device, size_t bytes, void** out, size_t* got) {
   {
     std::lock_guard<std::mutex> lock(g_cache_mu);
     int best = -1;
@@ -59,10 +62,27 @@ static hipError_t pool_acquire(int device, size_t bytes, void** out, size_t* got
     }
   }
   *got = bytes;
-  return hipMalloc(out, bytes);
+  hipError_t e = hipMalloc(out, bytes);
+  if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
+    // what the cache holds may be what is missing
+    std::vector<void*> drop;
+    {
+      std::lock_guard<std::mutex> lock(g_cache_mu);
+      for (size_t i = g_pools.size(); i-- > 0;)
+        if (g_pools[i].device == device) {
+          drop.push_back(g_pools[i].ptr);
+          g_pools.erase(g_pools.begin() + i);
+        }
+    }
+    if (drop.empty()) return e;
+    (void)hipGetLastError();
+    for (void* p : drop) (void)hipFree(p);
+    e = hipMalloc(out, bytes);
+  }
+  return e;
 }
 
-static void pool_release(int device, void* ptr, size_t bytes) {
+void pool_release(int device, void* ptr, size_t bytes) {
   if (!ptr) return;
   std::vector<void*> drop;
   {

@@ -182,6 +182,10 @@ fp_status terminals_problem(fp_problem* pb, hipStream_t s, int32_t mem_kind, uin
 fp_status export_state(fp_problem* pb, hipStream_t s, int32_t* f_in, int32_t* f_out,
                        int32_t* f_b, int32_t* labels, int32_t* excess);
 void release_problem(fp_problem* pb);
+// A block of device memory of at least `bytes` (its size in *got), from the
+// cache of released ones or newly allocated, and its return once no work uses it.
+hipError_t pool_acquire(int device, size_t bytes, void** out, size_t* got);
+void pool_release(int device, void* ptr, size_t bytes);
 // free the device pools and pinned control blocks kept for reuse
 void release_cached_memory();
 

@@ -996,18 +996,51 @@ int rg_grid(long long n, int threads = 256) {
   return (int)b;
 }
 
-// Device allocations released together when the build returns.
+// Device memory for the work of one call on one stream, released together when
+// the call returns.  A build takes some 60 pieces; as allocations of their own
+// their release took 8.4 ms of a 26 ms refinement round (320k vertices, 1.6 M
+// pins, 120 pairs), so they are cut from a few blocks that double in size, and
+// the blocks come from the cache of released pools and go back there.
 struct Scratch {
-  std::vector<void*> ptrs;
+  static constexpr size_t kFirstBlock = 32ull << 20, kLastBlock = 512ull << 20;
+  struct Block {
+    void* ptr;
+    size_t bytes;
+  };
+  const int device;
+  const hipStream_t stream;
+  std::vector<Block> blocks;
+  size_t used = 0;  // of the last block
+  Scratch(int device_, hipStream_t s) : device(device_), stream(s) {}
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
   ~Scratch() {
-    for (void* p : ptrs) (void)hipFree(p);
+    if (blocks.empty()) return;
+    (void)hipStreamSynchronize(stream);  // a call that failed may have left work behind
+    for (const Block& b : blocks) pool_release(device, b.ptr, b.bytes);
+  }
+  hipError_t take(size_t bytes, void** out) {
+    if (blocks.empty() || blocks.back().bytes - used < bytes) {
+      const size_t next = std::min(kLastBlock, kFirstBlock << std::min<size_t>(blocks.size(), 8));
+      Block b{nullptr, 0};
+      hipError_t e = pool_acquire(device, std::max(next, bytes), &b.ptr, &b.bytes);
+      if (e != hipSuccess && bytes < next) {  // then only what is asked for
+        (void)hipGetLastError();
+        e = pool_acquire(device, bytes, &b.ptr, &b.bytes);
+      }
+      if (e != hipSuccess) return e;
+      blocks.push_back(b);
+      used = 0;
+    }
+    *out = static_cast<char*>(blocks.back().ptr) + used;
+    used += bytes;
+    return hipSuccess;
   }
   template <class T>
   hipError_t get(size_t count, T** out) {
     void* p = nullptr;
-    const hipError_t e = hipMalloc(&p, rg_align(count * sizeof(T) + 1));
+    const hipError_t e = take(rg_align(count * sizeof(T) + 1), &p);
     if (e != hipSuccess) return e;
-    ptrs.push_back(p);
     *out = static_cast<T*>(p);
     return hipSuccess;
   }
@@ -1050,9 +1083,9 @@ fp_status regions_build(int32_t V, int32_t E, const int32_t* off_in, const int32
                         const int32_t* w_in, const int32_t* cv_in, const int32_t* block_in,
                         int32_t k, int32_t npairs, const int32_t* pairs, const int64_t* caps,
                         int32_t flags, int32_t mem_kind, hipStream_t s, fp_regions** out) {
-  Scratch sc;
   int dev = 0;
   RG_TRY(hipGetDevice(&dev), "hipGetDevice");
+  Scratch sc(dev, s);
   // inputs on the device
   int32_t P = 0;
   const int32_t *off = off_in, *pins = pins_in, *w = w_in, *cv = cv_in, *block = block_in;
@@ -1479,7 +1512,9 @@ fp_status regions_solve(fp_regions* r, const uint8_t* skip, hipStream_t s, int64
     for (int q = 0; q < npairs; ++q) nb += r->nloc[q] + 2;
     RG_TRY(hipMalloc(&r->sides, (size_t)nb + 1), "allocating the source sides");
   }
-  Scratch sc;
+  int dev = 0;
+  RG_TRY(hipGetDevice(&dev), "hipGetDevice");
+  Scratch sc(dev, s);
   long long *nbase_d, *pbase_d, *vbase_d;
   RG_TRY(sc.get((size_t)npairs, &nbase_d), "allocating");
   RG_TRY(sc.get((size_t)npairs, &pbase_d), "allocating");

@@ -310,3 +310,50 @@ def test_regions_solve_union(hf, oracle_mod):
             ref = oracle_mod.maxflow(h)
             assert flows[q] == ref.flow, q
             assert (rg.source_side(q).astype(bool) == ref.vertex_side[:n].astype(bool)).all(), q
+
+
+def test_regions_scratch_reused_by_threads(hf):
+    """Builds of two sizes from two threads, each on a stream of its own and
+    again on scratch memory that the others have written: every result equals
+    the first one, bit for bit; so does one after the cache was emptied."""
+    import threading
+    import torch
+    sets = []
+    for seed, V, target in ((3, 2000, 9000), (4, 9000, 60000)):
+        hg, block = _instance(seed, V, 6, target, 40)
+        pairs, cuts = _heaviest_pairs(hg, block, 6, 6)
+        bw = np.bincount(block, weights=hg.vertex_weights, minlength=6).astype(np.int64)
+        sets.append((hg, block, pairs, inputs.region_caps(bw, pairs, cuts)))
+
+    def build(i, stream=None):
+        hg, block, pairs, caps = sets[i]
+        with hf.FlowRegions(hg.num_vertices, hg.net_offsets, hg.pins, hg.net_weights,
+                            hg.vertex_weights, block, 6, pairs, caps, stream=stream) as r:
+            flows = [int(x) for x in r.solve()]
+            return flows, [r.export(q) for q in range(len(pairs))]
+
+    def same(a, b):
+        return a[0] == b[0] and all(
+            set(x) == set(y) and all(np.array_equal(x[n], y[n]) for n in x)
+            for x, y in zip(a[1], b[1]))
+
+    first = [build(i) for i in range(2)]
+    bad = []
+
+    def work(t):
+        stream = torch.cuda.Stream()
+        for n in range(6):
+            i = (n + t) % 2
+            if not same(build(i, stream), first[i]):
+                bad.append((t, n))
+        stream.synchronize()
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(2)]
+    _say("regions from two threads")
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
+    hf.load_library().flow_release_cached_memory()
+    assert all(same(build(i), first[i]) for i in range(2))

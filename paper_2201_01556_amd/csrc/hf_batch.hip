@@ -320,20 +320,58 @@ __global__ void __launch_bounds__(256) k_union_pins(const Dev* devs, UnionMap m,
 
 // Terminal lists of the union from the problems' current roles (piercing
 // included); list order does not matter.
+// The union's sources and sinks.  A workgroup counts those of 2,048 vertices,
+// reserves their places with one atomic per kind and writes them: with an
+// atomic per terminal the two counters, one address each, took 611 us for 512
+// problems (49k terminals).
+constexpr int kUnionTile = 8;  // vertices per thread
 __global__ void __launch_bounds__(256) k_union_terminals(const Dev* devs, UnionMap m, int32_t V,
                                                          int32_t* src, int32_t* snk,
                                                          int32_t* counts) {
-  const int t0 = blockIdx.x * blockDim.x + threadIdx.x, ts = gridDim.x * blockDim.x;
-  for (int v = t0; v < V; v += ts) {
-    const int i = union_part(m.voff, m.n, v);
-    const int r = devs[m.ids[i]].role[v - m.voff[i]];
-    if (r == 1) src[atomicAdd(&counts[0], 1)] = v;
-    else if (r == 2) snk[atomicAdd(&counts[1], 1)] = v;
+  __shared__ int wave_sum[4], base[2];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int tile = kUnionTile * 256;
+  for (int v0 = blockIdx.x * tile; v0 < V; v0 += gridDim.x * tile) {
+    int role[kUnionTile];
+    int mine = 0;  // sources in the low half, sinks in the high half
+#pragma unroll
+    for (int j = 0; j < kUnionTile; ++j) {
+      const int v = v0 + j * 256 + tid;
+      role[j] = 0;
+      if (v < V) {
+        const int i = union_part(m.voff, m.n, v);
+        role[j] = devs[m.ids[i]].role[v - m.voff[i]];
+      }
+      mine += role[j] == 1 ? 1 : role[j] == 2 ? 1 << 16 : 0;
+    }
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) wave_sum[wid] = incl;
+    __syncthreads();
+    int before = incl - mine, total = 0;
+    for (int w = 0; w < 4; ++w) {
+      if (w < wid) before += wave_sum[w];
+      total += wave_sum[w];
+    }
+    if (tid < 2) {
+      const int n = tid == 0 ? total & 0xffff : total >> 16;
+      base[tid] = n ? atomicAdd(&counts[tid], n) : 0;
+    }
+    __syncthreads();
+    int at_src = base[0] + (before & 0xffff), at_snk = base[1] + (before >> 16);
+#pragma unroll
+    for (int j = 0; j < kUnionTile; ++j) {
+      const int v = v0 + j * 256 + tid;
+      if (role[j] == 1) src[at_src++] = v;
+      else if (role[j] == 2) snk[at_snk++] = v;
+    }
   }
 }
 
-// Flow value of kept problem blockIdx.x: weight of its nets with e_in on the
-// source side and e_out not (bit0 set, bit1 clear).
 __global__ void __launch_bounds__(256) k_union_flows(UnionMap m, const int32_t* w,
                                                      const uint8_t* nside,
                                                      unsigned long long* flows) {
@@ -449,7 +487,8 @@ static fp_status union_chunk(fp_batch* b, const std::vector<int32_t>& ids, int32
   if (he != hipSuccess) return hip_fail(he, "staging the union map");
   k_union_nets<<<union_grid(E + 1), 256, 0, s>>>(b->devs_d, m, (int32_t)E, noff_u, w_u);
   if (P) k_union_pins<<<union_grid(P), 256, 0, s>>>(b->devs_d, m, (int32_t)P, pins_u);
-  k_union_terminals<<<union_grid(V), 256, 0, s>>>(b->devs_d, m, (int32_t)V, src, snk, cnt);
+  k_union_terminals<<<union_grid((V + kUnionTile - 1) / kUnionTile), 256, 0, s>>>(
+      b->devs_d, m, (int32_t)V, src, snk, cnt);
   int32_t counts[2] = {0, 0};
   he = hipGetLastError();
   if (he == hipSuccess) he = hipMemcpyAsync(counts, cnt, 8, hipMemcpyDeviceToHost, s);

@@ -376,3 +376,25 @@ def test_batch_full_block_pairs_vs_oracle(hf, oracle_mod):
     finally:
         for p in probs:
             p.close()
+
+
+@pytest.mark.parametrize("sizes,share", [((2047,), 2), (((2048,)), 2), ((2049,), 2),
+                                         ((1000, 1048, 2047, 3), 3), ((4, 4095, 5), 50)], ids=str)
+def test_batch_union_terminal_tiles(hf, oracle_mod, sizes, share):
+    """Unions whose vertices end around the 2,048 that a workgroup collects
+    the terminals of, with all (share 2) or few of them terminals."""
+    hgs = []
+    for i, V in enumerate(sizes):
+        n = max(1, V // share)
+        hgs.append(inputs.uniform_hypergraph(40 + i, num_vertices=V, num_nets=max(2, V),
+                                             size_hi=min(6, V), num_sources=n, num_sinks=n))
+    refs = _oracle_all(oracle_mod, hgs)
+    probs = [hf.FlowProblem.from_hypergraph(h) for h in hgs]
+    _say(f"union terminals {sizes}")
+    try:
+        with hf.FlowBatch(probs, with_cut=True, schedule=1) as plan:
+            assert list(plan.run(with_cut=True)) == [r.flow for r in refs]
+            _check_sides(plan, hgs, refs, f"terminals {sizes}")
+    finally:
+        for p in probs:
+            p.close()

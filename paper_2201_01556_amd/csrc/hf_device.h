@@ -328,30 +328,6 @@ __device__ __forceinline__ BlockQ bq_bind(lds_int* lds, int32_t* gcnt, int32_t* 
   return q;
 }
 
-// Called by all active lanes of a wave.
-__device__ __forceinline__ void bq_push1(const BlockQ& q, int k, int v, bool pred) {
-  const unsigned long long m = __ballot(pred);
-  if (m == 0ull) return;
-  const int cnt = __popcll(m);
-  const int leader = __builtin_ctzll(m);
-  int pos = 0;
-  if (lane_id() == leader) pos = lds_add(q.n + k, cnt);
-  pos = __shfl(pos, leader);
-  const int rank = __popcll(m & lanemask_lt());
-  const int room = max(0, q.cap - pos);
-  if (cnt <= room) {
-    if (pred) q.buf[k * q.cap + pos + rank] = v;
-    return;
-  }
-  int gb = 0;
-  if (lane_id() == leader) gb = atomicAdd(&q.gcnt[k], cnt - room);
-  gb = __shfl(gb, leader);
-  if (pred) {
-    if (rank < room) q.buf[k * q.cap + pos + rank] = v;
-    else q.dst[k][gb + rank - room] = v;
-  }
-}
-
 __device__ __forceinline__ bool is_big(const Dev& g, int v) {
   return (g.bigbits[v >> 5] >> (v & 31)) & 1u;
 }
@@ -365,11 +341,34 @@ __device__ __forceinline__ int list_of(const Dev& g, int v) {
   return v < g.V ? 0 : 1 + ((v - g.NB) & 1);
 }
 
+// Stage v into list k (if pred).  Called by all active lanes.  A lane at a time,
+// which is the shorter code than a sum over the wave per list: a small level or
+// frontier runs each instruction once, from a cold instruction cache (flows of
+// 2k to 300k vertices 4 to 6 % faster).  What a hub's arcs reach past the
+// staging area is counted per wave, since the global counters are few.
+__device__ __forceinline__ void bq_push(const BlockQ& q, int k, int v, bool pred) {
+  const int pos = pred ? lds_add(q.n + k, 1) : 0;
+  const bool over = pos >= q.cap;
+  if (pred && !over) q.buf[k * q.cap + pos] = v;
+  for (unsigned long long m = __ballot(over); m;) {
+    const int leader = __builtin_ctzll(m);
+    const int list = __shfl(k, leader);
+    const unsigned long long same = __ballot(over && k == list);
+    int at = 0;
+    if (lane_id() == leader) at = atomicAdd(&q.gcnt[list], __popcll(same));
+    at = __shfl(at, leader);
+    if (over && k == list) {
+      int32_t* const dst =
+          list == 0 ? q.dst[0] : list == 1 ? q.dst[1] : list == 2 ? q.dst[2] : q.dst[3];
+      dst[at + __popcll(same & lanemask_lt())] = v;
+    }
+    m &= ~same;
+  }
+}
+
 // Stage v (if pred) into its list.  Called by all active lanes.
 __device__ __forceinline__ void qpush(const Dev& g, const BlockQ& q, int v, bool pred) {
-  const int k = pred ? list_of(g, v) : -1;
-#pragma unroll
-  for (int j = 0; j < kNL; ++j) bq_push1(q, j, v, k == j);
+  bq_push(q, pred ? list_of(g, v) : 0, v, pred);
 }
 
 // Block-uniform: move the staged entries to the global lists.
@@ -1287,120 +1286,37 @@ __device__ __forceinline__ bool fwd_visit(const Dev& g, int v, int ep, int ep_tm
 //   e_in:      e_in -> e_out when fb < w, e_in -> u when flow(u, e_in) > 0
 //   e_out:     e_out -> e_in when fb > 0, e_out -> u always (a sink reached
 //              is an internal error: the flow would not be maximum)
-template <bool kClaim>
-__device__ __forceinline__ void bfs_fwd_node(const Dev& g, const BlockQ& q, int x, bool has,
-                                             int gl, int stride, int ep, int ep_tmp,
-                                             uint32_t& nbytes) {
-  const bool isv = has && x < g.V;
-  const bool isnet = has && x >= g.NB;
-  if (!has || isv) {
-    int beg = 0, end = 0;
-    if (isv) {
-      beg = g.vtx_off[x];
-      end = g.vtx_off[x + 1];
+__device__ __forceinline__ void bfs_fwd_node(const Dev& g, int x, bool has, int gl, int stride,
+                                             int ep, int ep_tmp, uint32_t& nbytes) {
+  if (has && x < g.V) {
+    const int end = g.vtx_off[x + 1];
+    for (int i = g.vtx_off[x] + gl; i < end; i += stride) {
+      const int2 ep2 = g.vinc[i];
+      const int t1 = g.NB + 2 * ep2.x;
+      nbytes += 12;
+      fwd_visit<false>(g, t1, ep, ep_tmp);
+      if (g.fpin[2 * ep2.y + 1] > 0) fwd_visit<false>(g, t1 + 1, ep, ep_tmp);
     }
-    for (int base = beg; base < end; base += stride) {
-      const int i = base + gl;
-      bool vin = false, vout = false;
-      int t1 = 0;
-      if (i < end) {
-        const int2 ep2 = g.vinc[i];
-        t1 = g.NB + 2 * ep2.x;
-        nbytes += 12;
-        vin = fwd_visit<kClaim>(g, t1, ep, ep_tmp);
-        if (g.fpin[2 * ep2.y + 1] > 0) vout = fwd_visit<kClaim>(g, t1 + 1, ep, ep_tmp);
-      }
-      if (kClaim) {
-        qpush(g, q, t1, vin);
-        qpush(g, q, t1 + 1, vout);
-      }
-    }
-  } else if (isnet) {
+  } else if (has && x >= g.NB) {
     const int e = (x - g.NB) >> 1;
     const bool in = ((x - g.NB) & 1) == 0;
-    const int beg = g.net_off[e], end = g.net_off[e + 1];
+    const int end = g.net_off[e + 1];
     const int we = g.w[e];
-    bool vb = false;
     if (gl == 0) {
       const int fbv = g.fb[e];
       nbytes += 16;
-      if (in ? fbv < we : fbv > 0) vb = fwd_visit<kClaim>(g, in ? x + 1 : x - 1, ep, ep_tmp);
+      if (in ? fbv < we : fbv > 0) fwd_visit<false>(g, in ? x + 1 : x - 1, ep, ep_tmp);
     }
-    if (kClaim) qpush(g, q, in ? x + 1 : x - 1, vb);
-    for (int base = beg; base < end; base += stride) {
-      const int i = base + gl;
-      bool vu = false;
-      int u = 0;
-      if (i < end) {
-        u = g.pin_v[i];
-        nbytes += 8;
-        if (in) {
-          if (we - g.fpin[2 * i] > 0) vu = fwd_visit<kClaim>(g, u, ep, ep_tmp);
-        } else {
-          const int r = g.role[u];
-          if (r == 2) atomicOr(&g.ctl->err, ERR_SINK_REACHED);
-          else if (r == 0) vu = fwd_visit<kClaim>(g, u, ep, ep_tmp);
-        }
+    for (int i = g.net_off[e] + gl; i < end; i += stride) {
+      const int u = g.pin_v[i];
+      nbytes += 8;
+      if (in) {
+        if (we - g.fpin[2 * i] > 0) fwd_visit<false>(g, u, ep, ep_tmp);
+      } else {
+        const int r = g.role[u];
+        if (r == 2) atomicOr(&g.ctl->err, ERR_SINK_REACHED);
+        else if (r == 0) fwd_visit<false>(g, u, ep, ep_tmp);
       }
-      if (kClaim) qpush(g, q, u, vu);
-    }
-  }
-}
-
-// Node-grouped reverse BFS of the uncapped residual network (maximal sink
-// side), claiming by exchange on the stamp ep: node x's residual in-arcs.
-//   vertex x:  from e_out always, from e_in when flow(x, e_in) > 0
-//   e_in:      from e_out when fb > 0, from every pin (uncapped)
-//   e_out:     from e_in when fb < w, from pins u with flow(e_out, u) > 0
-// A source reached is an internal error (the flow would not be maximum).
-__device__ __forceinline__ void bfs_sink_node(const Dev& g, const BlockQ& q, int x, bool has,
-                                              int gl, int stride, int ep, uint32_t& nbytes) {
-  const bool isv = has && x < g.V;
-  const bool isnet = has && x >= g.NB;
-  if (!has || isv) {
-    int beg = 0, end = 0;
-    if (isv) {
-      beg = g.vtx_off[x];
-      end = g.vtx_off[x + 1];
-    }
-    for (int base = beg; base < end; base += stride) {
-      const int i = base + gl;
-      bool vin = false, vout = false;
-      int t1 = 0;
-      if (i < end) {
-        const int2 ep2 = g.vinc[i];
-        t1 = g.NB + 2 * ep2.x;
-        nbytes += 12;
-        vout = stamp_first(g, t1 + 1, ep);                                       // e_out -> x
-        if (g.w[ep2.x] - g.fpin[2 * ep2.y] > 0) vin = stamp_first(g, t1, ep);  // e_in -> x
-      }
-      qpush(g, q, t1, vin);
-      qpush(g, q, t1 + 1, vout);
-    }
-  } else if (isnet) {
-    const int e = (x - g.NB) >> 1;
-    const bool in = ((x - g.NB) & 1) == 0;
-    const int beg = g.net_off[e], end = g.net_off[e + 1];
-    bool vb = false;
-    if (gl == 0) {
-      const int fbv = g.fb[e];
-      nbytes += 16;
-      if (in ? fbv > 0 : fbv < g.w[e]) vb = stamp_first(g, in ? x + 1 : x - 1, ep);
-    }
-    qpush(g, q, in ? x + 1 : x - 1, vb);
-    for (int base = beg; base < end; base += stride) {
-      const int i = base + gl;
-      bool vu = false;
-      int u = 0;
-      if (i < end) {
-        u = g.pin_v[i];
-        nbytes += 8;
-        if (in || g.fpin[2 * i + 1] > 0) {  // u -> e_in always, u -> e_out by flow
-          if (g.role[u] == 1) atomicOr(&g.ctl->err, ERR_SOURCE_REACHED);
-          else vu = stamp_first(g, u, ep);
-        }
-      }
-      qpush(g, q, u, vu);
     }
   }
 }
@@ -1408,6 +1324,132 @@ __device__ __forceinline__ void bfs_sink_node(const Dev& g, const BlockQ& q, int
 constexpr int kDirRelabel = 0;  // reverse BFS of a global relabel (capped network)
 constexpr int kDirSource = 1;   // forward BFS of the source side (uncapped)
 constexpr int kDirSink = 2;     // reverse BFS of the sink side (uncapped)
+
+// One node of a level whose arcs claim: the reverse BFS of a global relabel
+// (labels val), the forward BFS of the source side or the reverse BFS of the
+// sink side (stamps val).  A claiming level is bound by the latency of one
+// node's chain of cold accesses, so what does not depend on each other is in
+// flight together: a net's bridge with its first pins, the claims of a net's
+// two nodes, and each claim with the word that tells the list of the node.
+// That leaves five accesses in a row (range, arc, label or stamp, claim, place
+// in the list) where the bridge before the pins, one claim after the other and
+// the list word after the claim made it ten or eleven.  A level of a 740k-pin
+// flow 15.3 -> 14.0 us on average, of a 13k-pin one 9.0 -> 8.1.
+template <int kDir>
+__device__ __forceinline__ void bfs_claim_node(const Dev& g, const BlockQ& q, int x, bool has,
+                                               int gl, int stride, int val, uint32_t& nbytes) {
+  auto claim = [&](bool want, int t, uint32_t& word) {  // the value before, val if not wanted
+    int old = val;
+    if (want) {
+      word = g.bigbits[t >> 5];
+      if (kDir == kDirRelabel) old = atomicCAS(&g.d[t], g.N, val);
+      else old = atomicExch(&g.stamp[t], val);
+    }
+    return old;
+  };
+  auto first = [&](int old) { return kDir == kDirRelabel ? old == g.N : old != val; };
+  auto mark = [&](int t, uint32_t bits) {  // labelled: the hint of node t (and t + 1)
+    if (kDir == kDirRelabel && bits) {
+      g.seen[t >> 5] |= bits << (t & 31);
+      if (g.lev && (bits & 1u)) g.lev[t] = 2;
+      if (g.lev && (bits & 2u)) g.lev[t + 1] = 2;
+    }
+  };
+  auto push = [&](int t, bool won, uint32_t word) {
+    bq_push(q, (word >> (t & 31)) & 1u ? kBigList : t < g.V ? 0 : 1 + (t & 1), t, won);
+  };
+  if (has && x < g.V) {
+    const int beg = g.vtx_off[x], end = g.vtx_off[x + 1];
+    for (int base = beg; base < end; base += stride) {
+      const int i = base + gl;
+      bool want_in = false, want_out = false;
+      int t = 0;  // e_in; e_out = t + 1, their bits share a word
+      if (i < end) {
+        const int2 a = g.vinc[i];
+        t = g.NB + 2 * a.x;
+        nbytes += 12;
+        if (kDir == kDirRelabel) {  // e_out -> x infinite, e_in -> x reverse
+          const uint32_t sw = g.seen[t >> 5] >> (t & 31);
+          const bool flow = pin_flow_in(g, a.y);
+          want_out = !(sw & 2u);
+          want_in = !(sw & 1u) && flow;
+        } else {
+          const int2 st = *reinterpret_cast<const int2*>(g.stamp + t);
+          const int2 fp = *reinterpret_cast<const int2*>(g.fpin + 2 * a.y);
+          want_in = st.x != val;
+          want_out = st.y != val;
+          if (kDir == kDirSource) want_out = want_out && fp.y > 0;  // x -> e_in uncapped
+          else want_in = want_in && g.w[a.x] - fp.x > 0;            // e_out -> x infinite
+        }
+      }
+      uint32_t word = 0;
+      const int old_out = claim(want_out, t + 1, word);
+      const int old_in = claim(want_in, t, word);
+      const bool won_out = first(old_out), won_in = first(old_in);
+      mark(t, (won_in ? 1u : 0u) | (won_out ? 2u : 0u));
+      push(t, won_in, word);
+      push(t + 1, won_out, word);
+    }
+  } else if (has && x >= g.NB) {
+    const int e = (x - g.NB) >> 1;
+    const bool in = ((x - g.NB) & 1) == 0;
+    const int b = in ? x + 1 : x - 1;  // over the bridge
+    const int beg = g.net_off[e];
+    int end = g.net_off[e + 1], we = 0;
+    bool want_b = false;
+    if (kDir == kDirRelabel) {
+      const uint32_t nb = net_bits(g, e);
+      // in-arcs of e_out from pins carry flow(e_out, u) > 0; their sum is the
+      // outflow fb - excess(e_out), so a net without outflow skips its pins
+      if (!in && !(nb & 2u)) end = beg;
+      // e_out -> e_in residual fb, e_in -> e_out residual w - fb
+      if (gl == 0) want_b = (nb & (in ? 4u : 1u)) && !seen_bit(g, b);
+    } else {
+      we = g.w[e];
+      if (gl == 0) {
+        const int fbv = g.fb[e], st = g.stamp[b];
+        want_b = (in == (kDir == kDirSource) ? fbv < we : fbv > 0) && st != val;
+      }
+    }
+    if (gl == 0) nbytes += 16;
+    bool bridge = true;
+    for (int base = beg; bridge || base < end; base += stride, bridge = false) {
+      const int i = base + gl;
+      bool want = false;
+      int u = 0;
+      if (i < end) {
+        u = g.pin_v[i];
+        nbytes += 12;
+        if (kDir == kDirRelabel) {  // r_in (u -> e_in) or f_out (u -> e_out)
+          const int f = g.fpin[2 * i + (in ? 0 : 1)];
+          want = f > 0 && !seen_bit(g, u);
+        } else {
+          const int2 fp = *reinterpret_cast<const int2*>(g.fpin + 2 * i);
+          const int st = g.stamp[u], r = g.role[u];
+          if (kDir == kDirSource) {  // e_in -> u reverse, e_out -> u infinite
+            want = (in ? we - fp.x > 0 : r == 0) && st != val;
+            if (!in && r == 2) atomicOr(&g.ctl->err, ERR_SINK_REACHED);
+          } else {  // u -> e_in always, u -> e_out by flow
+            const bool arc = in || fp.y > 0;
+            want = arc && r != 1 && st != val;
+            if (arc && r == 1) atomicOr(&g.ctl->err, ERR_SOURCE_REACHED);
+          }
+        }
+      }
+      uint32_t word_b = 0, word = 0;
+      int old_b = val;
+      if (bridge) old_b = claim(want_b, b, word_b);
+      const int old = claim(want, u, word);
+      if (bridge) {
+        mark(b, first(old_b) ? 1u : 0u);
+        push(b, first(old_b), word_b);
+      }
+      mark(u, first(old) ? 1u : 0u);
+      push(u, first(old), word);
+    }
+  }
+}
+
 
 // One BFS level, node-grouped: the reverse BFS of a global relabel (labels
 // level+1), the forward BFS of the source side (stamp ep, provisional stamp
@@ -1458,10 +1500,10 @@ __device__ void phase_bfs_node(const Dev& g, int level, int ep, int ep_tmp, int 
       stride = blockDim.x;
     }
     nitems += has && gl == 0;
-    if constexpr (kDir == kDirSource)
-      bfs_fwd_node<kClaim>(g, q, v, has, gl, stride, ep, ep_tmp, nbytes);
-    else if constexpr (kDir == kDirSink)
-      bfs_sink_node(g, q, v, has, gl, stride, ep, nbytes);
+    if constexpr (kClaim)
+      bfs_claim_node<kDir>(g, q, v, has, gl, stride, kDir == kDirRelabel ? level + 1 : ep, nbytes);
+    else if constexpr (kDir == kDirSource)
+      bfs_fwd_node(g, v, has, gl, stride, ep, ep_tmp, nbytes);
     else bfs_rev_node<kClaim>(g, q, v, has, gl, stride, level + 1, nbytes);
     if (kClaim) bq_tile_end(q, q.cap / 2);
   }
@@ -2706,7 +2748,7 @@ struct Growth {
   int left = 0;                  // nodes of the level reached
 };
 
-template <int kDir, bool kGrow = false>
+template <int kDir, bool kGrow = false, int kArcs = 1>
 __device__ __forceinline__ int wg_bfs(const Dev& g, int level0, int cap, int ep, int kc, lds_int* lds,
                       Growth* grow = nullptr) {
   lds_int* const buf = lds;  // [2][kNL][kLoopCap]
@@ -2771,9 +2813,6 @@ __device__ __forceinline__ int wg_bfs(const Dev& g, int level0, int cap, int ep,
         }
       }
     };
-    auto open = [&](int v) {  // not reached yet, as far as a plain load tells
-      return kDir == kDirRelabel ? g.d[v] == g.N : g.stamp[v] != ep;
-    };
     for (int first = 0; first < pre.total; first += blockDim.x) {
       const int nt = min((int)blockDim.x, pre.total - first);
       int deg = 0, beg = 0, v = 0;
@@ -2809,76 +2848,125 @@ __device__ __forceinline__ int wg_bfs(const Dev& g, int level0, int cap, int ep,
       t_beg[tid] = beg;
       t_off[tid] = base + incl - deg;
       __syncthreads();
-      for (int a = tid; a < A; a += blockDim.x) {
-        int lo = 0, hi = nt;  // t_off[lo] <= a, and a lies before entry hi
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (t_off[mid] <= a) lo = mid;
-          else hi = mid;
+      // kArcs arcs a thread at a time, their loads in flight together: the
+      // entry by bisection, the arc's other end, its label or stamp and flow,
+      // then the claims
+      const int* const mark = kDir == kDirRelabel ? g.d : g.stamp;
+      const int unreached = g.N;
+      int top = 1;
+      while (2 * top < nt) top *= 2;
+      for (int a0 = tid; a0 < A; a0 += kArcs * (int)blockDim.x) {
+        int lo[kArcs], j[kArcs], t[kArcs];
+        int2 fp[kArcs], st[kArcs];
+        bool in_range[kArcs], vtx[kArcs];
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) {
+          lo[q] = 0;
+          in_range[q] = a0 + q * (int)blockDim.x < A;
         }
-        const int x = t_node[lo], j = a - t_off[lo], b = t_beg[lo];
-        if (x < g.V) {
-          const int2 ep2 = g.vinc[b + j];
-          const int t1 = g.NB + 2 * ep2.x;  // e_in; e_out = t1 + 1
-          const int2 fp = *reinterpret_cast<const int2*>(g.fpin + 2 * ep2.y);
-          const int2 st = *reinterpret_cast<const int2*>((kDir == kDirRelabel ? g.d : g.stamp) + t1);
-          const bool o1 = kDir == kDirRelabel ? st.x == g.N : st.x != ep;
-          const bool o2 = kDir == kDirRelabel ? st.y == g.N : st.y != ep;
-          nbytes += 24;
-          bool c1, c2;
-          if (kDir == kDirSource) {  // x -> e_in uncapped, x -> e_out reverse
-            c1 = o1;
-            c2 = o2 && fp.y > 0;
-          } else {  // e_out -> x infinite, e_in -> x reverse
-            c1 = o1 && g.w[ep2.x] - fp.x > 0;
-            c2 = o2;
+        for (int step = top; step > 0; step >>= 1)  // t_off[lo] <= a
+#pragma unroll
+          for (int q = 0; q < kArcs; ++q) {
+            const int c = lo[q] + step;
+            if (c < nt && t_off[c] <= a0 + q * (int)blockDim.x) lo[q] = c;
           }
-          if (c1) claim(t1);
-          if (c2) claim(t1 + 1);
-        } else {
-          const int e = (x - g.NB) >> 1;
-          const bool in = ((x - g.NB) & 1) == 0;
-          if (j == 0) {  // bridge
-            const int fbv = g.fb[e], we = g.w[e];
-            const int t1 = in ? x + 1 : x - 1;
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) {
+          const int x = t_node[lo[q]];
+          j[q] = a0 + q * (int)blockDim.x - t_off[lo[q]];
+          vtx[q] = x < g.V;
+          lo[q] = t_beg[lo[q]] + j[q];  // the arc's place, from here on
+          t[q] = x;
+        }
+        // a vertex's arc: net and slot in fp; a bridge: fb and w in fp; a pin
+        // arc: the vertex in st.x, the flows in fp
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) {
+          if (!in_range[q]) continue;
+          if (vtx[q]) {
+            fp[q] = g.vinc[lo[q]];
+          } else if (j[q] == 0) {
+            const int e = (t[q] - g.NB) >> 1;
+            fp[q] = make_int2(g.fb[e], g.w[e]);
+          } else {
+            st[q].x = g.pin_v[lo[q] - 1];
+            fp[q] = *reinterpret_cast<const int2*>(g.fpin + 2 * (lo[q] - 1));
+          }
+        }
+        int cap_or_role[kArcs];  // w(e) where it is needed, a pin's role
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) {
+          if (!in_range[q]) continue;
+          if (vtx[q]) {
+            const int2 ep = fp[q];
+            t[q] = g.NB + 2 * ep.x;  // e_in; e_out = t + 1
+            fp[q] = *reinterpret_cast<const int2*>(g.fpin + 2 * ep.y);
+            st[q] = *reinterpret_cast<const int2*>(mark + t[q]);
+            if (kDir != kDirSource) cap_or_role[q] = g.w[ep.x];
+            nbytes += 24;
+          } else if (j[q] == 0) {
+            const bool in = ((t[q] - g.NB) & 1) == 0;
+            st[q].x = mark[in ? t[q] + 1 : t[q] - 1];
             nbytes += 8;
+          } else {
+            const int u = st[q].x;
+            st[q] = make_int2(u, mark[u]);
+            const bool in = ((t[q] - g.NB) & 1) == 0;
+            if (kDir == kDirSource) cap_or_role[q] = in ? g.w[(t[q] - g.NB) >> 1] : g.role[u];
+            if (kDir == kDirSink) cap_or_role[q] = g.role[u];
+            nbytes += 12;
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) {
+          if (!in_range[q]) continue;
+          ++narcs;
+          if (vtx[q]) {
+            const bool o1 = kDir == kDirRelabel ? st[q].x == unreached : st[q].x != ep;
+            const bool o2 = kDir == kDirRelabel ? st[q].y == unreached : st[q].y != ep;
+            bool c1, c2;
+            if (kDir == kDirSource) {  // x -> e_in uncapped, x -> e_out reverse
+              c1 = o1;
+              c2 = o2 && fp[q].y > 0;
+            } else {  // e_out -> x infinite, e_in -> x reverse
+              c1 = o1 && cap_or_role[q] - fp[q].x > 0;
+              c2 = o2;
+            }
+            if (c1) claim(t[q]);
+            if (c2) claim(t[q] + 1);
+            continue;
+          }
+          const bool in = ((t[q] - g.NB) & 1) == 0;
+          if (j[q] == 0) {
             // into e_in from e_out by fb, into e_out from e_in by w - fb; the
             // forward search the other way
             const bool by_fb = in == (kDir != kDirSource);
-            if ((by_fb ? fbv > 0 : fbv < we) && open(t1)) claim(t1);
-          } else {
-            const int i = b + j - 1;
-            const int u = g.pin_v[i];
-            const int2 fp = *reinterpret_cast<const int2*>(g.fpin + 2 * i);
-            nbytes += 12;
-            if (kDir == kDirRelabel) {
-              if ((in ? fp.x : fp.y) > 0 && open(u)) claim(u);
-            } else if (kDir == kDirSource) {
-              if (in) {  // e_in -> u reverse
-                const bool arc = g.w[e] - fp.x > 0;
-                if (kGrow) {
-                  const int st = g.stamp[u];
-                  if (arc && st != ep) claim(u);
-                  else if (!arc && st != ep && st != grow->other)
-                    atomicOr(&grow->next[u >> 5], 1u << (u & 31));
-                } else if (arc && open(u)) {
-                  claim(u);
-                }
-              } else {
-                const int r = g.role[u];  // e_out -> u infinite
-                if (r == 2) hit_sink = true;
-                else if (r == 0 && open(u)) claim(u);
-              }
-            } else if (in || fp.y > 0) {  // u -> e_in uncapped, u -> e_out by flow
-              if (g.role[u] == 1) hit_source = true;
-              else if (open(u)) claim(u);
-            } else if (kGrow) {
-              const int st = g.stamp[u];
-              if (st != ep && st != grow->other) atomicOr(&grow->next[u >> 5], 1u << (u & 31));
+            const bool open = kDir == kDirRelabel ? st[q].x == unreached : st[q].x != ep;
+            if ((by_fb ? fp[q].x > 0 : fp[q].x < fp[q].y) && open) claim(in ? t[q] + 1 : t[q] - 1);
+            continue;
+          }
+          const int u = st[q].x;
+          const bool open = kDir == kDirRelabel ? st[q].y == unreached : st[q].y != ep;
+          bool arc;
+          if (kDir == kDirRelabel) {
+            arc = (in ? fp[q].x : fp[q].y) > 0;
+          } else if (kDir == kDirSource) {
+            // e_in -> u reverse; e_out -> u infinite, into free vertices only
+            arc = in ? cap_or_role[q] - fp[q].x > 0 : cap_or_role[q] == 0;
+            if (!in && cap_or_role[q] == 2) hit_sink = true;
+          } else {  // u -> e_in uncapped, u -> e_out by flow
+            arc = in || fp[q].y > 0;
+            if (arc && cap_or_role[q] == 1) {
+              hit_source = true;
+              continue;
             }
           }
+          if (open && arc) claim(u);
+          // the growing side's neighbours: pins of e_in (source side) or of
+          // e_out (sink side) that it does not reach
+          if (kGrow && open && !arc && in == (kDir == kDirSource) && st[q].y != grow->other)
+            atomicOr(&grow->next[u >> 5], 1u << (u & 31));
         }
-        ++narcs;
       }
       __syncthreads();  // the tile is rewritten, the next level's list complete
     }
@@ -3326,8 +3414,8 @@ __device__ void fc_loop(const Dev& g, FcLoop a, lds_int* lds, lds_u64* weight) {
     gr.nfresh = nfresh + side;
     gr.next = side == 0 ? a.next[0] : a.next[1];
     gr.other = side == 0 ? a.ep_t : a.ep_s;
-    const int lv = side == 0 ? wg_bfs<kDirSource, true>(g, 0, a.cap, a.ep_s, 0, lds, &gr)
-                             : wg_bfs<kDirSink, true>(g, 0, a.cap, a.ep_t, 0, lds, &gr);
+    const int lv = side == 0 ? wg_bfs<kDirSource, true, 2>(g, 0, a.cap, a.ep_s, 0, lds, &gr)
+                             : wg_bfs<kDirSink, true, 2>(g, 0, a.cap, a.ep_t, 0, lds, &gr);
     if (gr.left > 0) {
       if (tid == 0) g.ctl->loop_levels = lv;
       listed &= ~(1 << side);  // the rest of the growth is not listed

@@ -344,6 +344,8 @@ __global__ void __launch_bounds__(kLoopBlock) k_round_loop(Dev g, int epoch0, in
   }
 }
 
+constexpr int kLoopArcs = 4;  // arcs a thread has in flight
+
 // BFS levels inside one workgroup (wg_bfs): mode 0 the global relabel
 // (reverse, capped), 1 the source side (forward, uncapped), 2 the sink side
 // (reverse, uncapped).
@@ -351,10 +353,11 @@ __global__ void __launch_bounds__(kBlock) k_bfs_loop(Dev g, int level0, int cap,
                                                      int mode) {
   __shared__ int32_t area[kWgBfsWords];
   lds_int* const lds = (lds_int*)area;
+  constexpr int kc = KC_LOOP_BFS;
   int levels;
-  if (mode == 0) levels = wg_bfs<kDirRelabel>(g, level0, cap, ep, KC_LOOP_BFS, lds);
-  else if (mode == 1) levels = wg_bfs<kDirSource>(g, level0, cap, ep, KC_LOOP_BFS, lds);
-  else levels = wg_bfs<kDirSink>(g, level0, cap, ep, KC_LOOP_BFS, lds);
+  if (mode == 0) levels = wg_bfs<kDirRelabel, false, kLoopArcs>(g, level0, cap, ep, kc, lds);
+  else if (mode == 1) levels = wg_bfs<kDirSource, false, kLoopArcs>(g, level0, cap, ep, kc, lds);
+  else levels = wg_bfs<kDirSink, false, kLoopArcs>(g, level0, cap, ep, kc, lds);
   __syncthreads();
   if (threadIdx.x == 0) {
     g.ctl->loop_levels = levels;

@@ -208,6 +208,29 @@ def test_swept_levels(hf, oracle_mod, V, E, long_nets, hubs):
     assert (lab[V + 1::2] == np.where(dout == -1, N, dout)).all()
 
 
+@pytest.mark.parametrize("side", ["source", "sink", "free"])
+@pytest.mark.parametrize("opts", [{}, dict(tail_threshold=1), dict(group_lanes=4)], ids=str)
+def test_hub_claims_past_the_staging_area(hf, oracle_mod, side, opts):
+    """One vertex on 20,000 nets: a level's only node reaches more nodes than a
+    workgroup stages for one list, in the relabel (a sink or a free hub), the
+    source side (a source) and the sink side."""
+    rng = np.random.default_rng(11)
+    V, E = 600, 20_000
+    nets = [[0] + sorted((1 + rng.choice(V - 1, size=int(rng.integers(1, 3)), replace=False)).tolist())
+            for _ in range(E)]
+    S = [0, 1, 2] if side == "source" else [1, 2]
+    T = [0, 3, 4] if side == "sink" else [3, 4]
+    hg = inputs.hypergraph_from_nets(V, nets, rng.integers(1, 4, E), S, T)
+    _say(f"hub {side} {opts}")
+    r = oracle_mod.maxflow(hg, sink_side=True)
+    with hf.FlowProblem.from_hypergraph(hg, **opts) as p:
+        F = p.solve()
+        vs, ns = p.source_side()
+        ts = p.sink_side()
+    assert_same(hg, r, F, vs.astype(bool), ns, f"hub {side}")
+    assert (ts.astype(bool) == r.sink_side.astype(bool)).all()
+
+
 def test_device_memory_inputs_and_outputs(hf, oracle_mod):
     import torch
     hg = inputs.uniform_hypergraph(42)

@@ -22,6 +22,7 @@
 //
 // Parameter layout (row-major): W1 [64 x 12], b1 [64], W2 [64 x 64], b2 [64],
 // W3 [64], b3.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -62,21 +63,45 @@ __global__ void k_log1p(const int64_t* __restrict__ f, int n, double* __restrict
 // order of the sums is fixed, so the twelve waves keep their serial chains;
 // the logarithms, which were most of the time, come from k_log1p on the whole
 // chip (12,000 samples: 289 -> 40 us for both kernels).
+//
+// The samples come in chunks of at most kFitChunk, so that the logarithms'
+// buffer is bounded and k_log1p's indices fit 32 bits at any number of
+// samples.  kFitChunk is a multiple of 64: every lane goes on with its own
+// sums, which wait in acc (sum, squares per lane) between the chunks, and the
+// results are those of one chunk.  pass: 1 the sums, 2 the squared
+// differences, 3 both (all samples in one chunk).
+constexpr int kFitChunk = 1 << 22;
+static_assert(kFitChunk % 64 == 0 && (long long)kFitChunk * kIn < (1ll << 31), "chunk of samples");
+
 __global__ void __launch_bounds__(kIn * 64) k_norm_stats(const double* __restrict__ lg, int n,
+                                                         int total, int pass, int first, int last,
+                                                         double* __restrict__ acc,
                                                          double* __restrict__ ms) {
   const int col = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const double* row = lg + (size_t)col * n;
-  double s = 0.0;
+  double s = 0.0, mean = 0.0;
+  if (pass & 1) {
+    if (!first) s = acc[threadIdx.x];
 #pragma unroll 16
-  for (int i = lane; i < n; i += 64) s += row[i];
-  const double mean = wave_sum_f64(s) / (double)n;
-  double q = 0.0;
+    for (int i = lane; i < n; i += 64) s += row[i];
+    acc[threadIdx.x] = s;
+    mean = wave_sum_f64(s) / (double)total;
+  } else {
+    mean = wave_sum_f64(acc[threadIdx.x]) / (double)total;
+  }
+  if (!(pass & 2)) return;
+  double* const squares = acc + kIn * 64;
+  double q = first ? 0.0 : squares[threadIdx.x];
 #pragma unroll 16
   for (int i = lane; i < n; i += 64) {
     const double d = row[i] - mean;
     q += d * d;
   }
-  const double sd = sqrt(wave_sum_f64(q) / (double)n);
+  if (!last) {
+    squares[threadIdx.x] = q;
+    return;
+  }
+  const double sd = sqrt(wave_sum_f64(q) / (double)total);
   if (lane == 0) {
     ms[col] = mean;
     ms[kIn + col] = sd > 1e-9 ? sd : 1.0;
@@ -85,9 +110,9 @@ __global__ void __launch_bounds__(kIn * 64) k_norm_stats(const double* __restric
 
 __global__ void k_norm_apply(const int64_t* __restrict__ f, int n, const double* __restrict__ ms,
                              float* __restrict__ x) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n * kIn) return;
-  const int col = i % kIn;
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= (size_t)n * kIn) return;
+  const int col = (int)(i % kIn);
   x[i] = (float)((log1p((double)f[i]) - ms[col]) / ms[kIn + col]);
 }
 
@@ -432,30 +457,34 @@ struct Staged {
   float* prob = nullptr;
   float* losses = nullptr;
   double* lg = nullptr;
+  double* acc = nullptr;
   ~Staged() {
     if (mem) (void)hipFree(mem);
   }
 };
 
+// want_fit: the buffers of the feature statistics
 static fp_status stage(const int64_t* f, const float* y, int n, int mem_kind, int tiles,
-                       bool want_part, bool want_prob, int loss_slots, hipStream_t s, Staged* st,
-                       bool want_log = false) {
+                       bool want_x, bool want_part, bool want_prob, int loss_slots, hipStream_t s,
+                       Staged* st, bool want_fit = false) {
   const size_t fb = (size_t)n * kIn * sizeof(int64_t);
   const size_t yb = y ? (size_t)n * sizeof(float) : 0;
-  size_t total = al((size_t)n * kIn * sizeof(float));
+  const size_t xb = want_x ? (size_t)n * kIn * sizeof(float) : 0;
+  size_t total = al(xb);
   if (mem_kind == 0) total += al(fb) + al(yb);
   if (want_part) total += al((size_t)tiles * kPart * sizeof(float));
   if (want_prob) total += al((size_t)n * sizeof(float));
   total += al((size_t)loss_slots * sizeof(float));
-  if (want_log) total += al((size_t)n * kIn * sizeof(double));
-  hipError_t he = hipMalloc(&st->mem, total);
+  const size_t lb = (size_t)std::min(n, kFitChunk) * kIn * sizeof(double);
+  if (want_fit) total += al(lb) + al(2 * kIn * 64 * sizeof(double));
+  hipError_t he = total ? hipMalloc(&st->mem, total) : hipSuccess;
   if (he != hipSuccess) {
     st->mem = nullptr;
     return hip_fail(he, "allocating scorer buffers");
   }
   char* p = static_cast<char*>(st->mem);
-  st->x = reinterpret_cast<float*>(p);
-  p += al((size_t)n * kIn * sizeof(float));
+  if (want_x) st->x = reinterpret_cast<float*>(p);
+  p += al(xb);
   if (mem_kind == 0) {
     int64_t* fd = reinterpret_cast<int64_t*>(p);
     p += al(fb);
@@ -482,16 +511,24 @@ static fp_status stage(const int64_t* f, const float* y, int n, int mem_kind, in
   }
   st->losses = reinterpret_cast<float*>(p);
   p += al((size_t)loss_slots * sizeof(float));
-  if (want_log) st->lg = reinterpret_cast<double*>(p);
+  if (want_fit) {
+    st->lg = reinterpret_cast<double*>(p);
+    st->acc = reinterpret_cast<double*>(p + al(lb));
+  }
   return FP_OK;
 }
 
 fp_status scorer_fit_impl(fp_scorer* sc, const int64_t* f, int n, int mem_kind, hipStream_t s) {
   Staged st;
-  fp_status r = stage(f, nullptr, n, mem_kind, 0, false, false, 0, s, &st, true);
+  fp_status r = stage(f, nullptr, n, mem_kind, 0, false, false, false, 0, s, &st, true);
   if (r) return r;
-  k_log1p<<<(n * kIn + 255) / 256, 256, 0, s>>>(st.f, n, st.lg);
-  k_norm_stats<<<1, kIn * 64, 0, s>>>(st.lg, n, sc->ms);
+  const bool one = n <= kFitChunk;
+  for (int pass = one ? 3 : 1; pass <= (one ? 3 : 2); ++pass)
+    for (long long at = 0; at < n; at += kFitChunk) {
+      const int m = (int)std::min<long long>(kFitChunk, n - at);
+      k_log1p<<<(m * kIn + 255) / 256, 256, 0, s>>>(st.f + at * kIn, m, st.lg);
+      k_norm_stats<<<1, kIn * 64, 0, s>>>(st.lg, m, n, pass, at == 0, at + m == n, st.acc, sc->ms);
+    }
   hipError_t he = hipGetLastError();
   if (he == hipSuccess) he = hipStreamSynchronize(s);
   if (he != hipSuccess) return hip_fail(he, "feature statistics");
@@ -510,9 +547,9 @@ static fp_status run_steps(fp_scorer* sc, const int64_t* f, const float* y, int 
   }
   const int tiles = (n + kTile - 1) / kTile;
   Staged st;
-  fp_status r = stage(f, y, n, mem_kind, tiles, true, false, steps, s, &st);
+  fp_status r = stage(f, y, n, mem_kind, tiles, true, true, false, steps, s, &st);
   if (r) return r;
-  k_norm_apply<<<(n * kIn + 255) / 256, 256, 0, s>>>(st.f, n, sc->ms, st.x);
+  k_norm_apply<<<(unsigned)(((size_t)n * kIn + 255) / 256), 256, 0, s>>>(st.f, n, sc->ms, st.x);
   const float inv_n = 1.f / (float)n;
   const double b1 = 0.9, b2 = 0.999;
   for (int t = 0; t < steps; ++t) {
@@ -557,7 +594,7 @@ fp_status scorer_predict_impl(fp_scorer* sc, const int64_t* f, int n, int mem_ki
   }
   const int tiles = (n + kTile - 1) / kTile;
   Staged st;
-  fp_status r = stage(f, nullptr, n, mem_kind, tiles, false, mem_kind == 0, 0, s, &st);
+  fp_status r = stage(f, nullptr, n, mem_kind, tiles, false, false, mem_kind == 0, 0, s, &st);
   if (r) return r;
   float* out = mem_kind == 0 ? st.prob : prob;
   k_fwd_bwd<false><<<tiles, kMlpThreads, 0, s>>>(sc->prm, nullptr, st.f, sc->ms, nullptr, n, 0.f,

@@ -90,6 +90,48 @@ def test_tile_edges_vs_oracle(hf, mlp, n):
     assert np.max(np.abs(p - mlp.predict(theta.astype(np.float64), xn))) <= 1e-5
 
 
+# Samples of a chunk of the feature statistics, and the numbers of samples from
+# which on 12 n no longer fits 31 bits and wraps around to a small number.
+@pytest.mark.parametrize("n", [(1 << 22) - 1, 1 << 22, (1 << 22) + 1, (1 << 23) + 65,
+                               178_956_971, 357_913_942])
+def test_normalization_of_many_samples(hf, n):
+    """Feature statistics over more samples than one chunk, and than 32-bit
+    element counts hold, in device memory, against float64 sums in chunks.
+    Either side adds at most n / 64 + 2^22 terms one after another, each
+    rounded by 2^-53 relatively; the deviation, a root, halves that of its
+    squares and takes the mean's error once."""
+    import ctypes
+    import torch
+    if torch.cuda.mem_get_info()[0] < n * 12 * 8 + (8 << 30):
+        pytest.skip("needs more free device memory")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    f = torch.empty((n, 12), dtype=torch.int64, device="cuda")
+    step = 1 << 22
+    for a in range(0, n, step):
+        part = f[a:a + step]
+        part.copy_(torch.randint(0, 200_000, part.shape, generator=g, device="cuda"))
+        part[:, 7] = 3  # a constant column
+        part[:, 2] += a // step  # another distribution in every chunk
+    torch.cuda.synchronize()
+    _say(f"normalization of {n} samples")
+    with hf.Scorer(inputs.scorer_init_params(0)) as sc:
+        st = hf.load_library().scorer_fit_normalization(
+            sc.handle, ctypes.c_void_p(f.data_ptr()), n, 1, None)
+        assert st == 0, hf.fp_last_error()
+        ms = sc.params()[1]
+    logs = [torch.log1p(f[a:a + step].double()).sum(0).cpu().numpy() for a in range(0, n, step)]
+    mean = np.sum(logs, 0) / n
+    m = torch.from_numpy(mean).cuda()
+    sq = [((torch.log1p(f[a:a + step].double()) - m) ** 2).sum(0).cpu().numpy()
+          for a in range(0, n, step)]
+    std = np.sqrt(np.sum(sq, 0) / n)
+    std[7] = 1.0
+    tol = 2 * (n / 64 + step) * 2.0 ** -53
+    assert np.max(np.abs(ms[:12] - mean) / mean) <= tol
+    assert np.max(np.abs(ms[12:] - std) / std) <= 2 * tol
+
+
 def test_training_tracks_oracle(hf, mlp):
     f, y = _data(1200, 5)
     theta = inputs.scorer_init_params(5)

@@ -1059,6 +1059,19 @@ __device__ LoopEnd wg_rounds(const Dev& g, int epoch, int max_rounds, int cap,
 // reverse residual BFS from the sinks (global relabel) over the capped network
 // ---------------------------------------------------------------------------
 
+// Residual bits of a net (netres, below) with bridge flow fb; x, dx0, dx1 hold the excess and
+// the pushes not folded yet of {e_in, e_out}, none of them negative.  What
+// flows into e_in (a source's share included) is fb plus the excess of e_in:
+// a preflow may send the same units over the bridge and back by a pin, so the
+// sum can pass INT32_MAX and its terms are looked at one by one; what leaves
+// e_out lies in [0, fb].
+__host__ __device__ __forceinline__ uint32_t net_residual_bits(int fb, int w, int2 x, int2 dx0,
+                                                               int2 dx1) {
+  const int out = fb - (x.y + dx0.y + dx1.y);
+  const bool in = (fb | x.x | dx0.x | dx1.x) != 0;
+  return (fb < w ? 1u : 0u) | (out > 0 ? 2u : 0u) | (fb > 0 ? 4u : 0u) | (in ? 8u : 0u);
+}
+
 // Global relabel, step 2: residual bits that the reverse BFS tests, so that
 // its checks of an arc hit two small bitmaps instead of scattered flows.
 // The flow state does not change during a global relabel.
@@ -1094,10 +1107,7 @@ __device__ void phase_gr_bits(const Dev& g, int t0, int tstride) {
       const int2 x = *reinterpret_cast<const int2*>(g.x + ei);
       const int2 a = *reinterpret_cast<const int2*>(g.dx[0] + ei);
       const int2 c = *reinterpret_cast<const int2*>(g.dx[1] + ei);
-      const int out = fbv - (x.y + a.y + c.y);
-      const int in = fbv + x.x + a.x + c.x;  // a source's share included
-      b = (fbv < g.w[e] ? 1u : 0u) | (out > 0 ? 2u : 0u) | (fbv > 0 ? 4u : 0u) |
-          (in > 0 ? 8u : 0u);
+      b = net_residual_bits(fbv, g.w[e], x, a, c);
     }
     uint32_t v = b << (4 * (lane & 7));
     v |= __shfl_xor(v, 1);

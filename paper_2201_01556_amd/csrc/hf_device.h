@@ -207,6 +207,16 @@ __device__ void block_add_u64(unsigned long long* d0, unsigned long long v0,
   __syncthreads();  // part may be written again by a later call
 }
 
+// Between the lanes of one wave that write LDS and those that read it: the
+// wave's LDS accesses execute in order, so this costs no instruction, but
+// without it the compiler may keep a lane's own value in a register where
+// another lane has written since.  Called by all active lanes.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Workgroup minima of two per-thread values, folded into the global values
 // by thread 0 (atomic min).  Block-uniform, as block_add_u64.
 __device__ void block_min_i32(int32_t* d0, int v0, int32_t* d1, int v1) {
@@ -2134,6 +2144,7 @@ __device__ void phase_bfs_sweep(const Dev& g, int level, int kc, lds_int* lds) {
       if (deg > kSweepLong && set_aside(node)) deg = 0;
       if (__ballot(deg > 0)) {
         flag[lane] = 0;
+        wave_lds_sync();
         const int incl = wave_scan(deg), excl = incl - deg, A = __shfl(incl, kWave - 1);
         for (int a0 = 0; a0 < A; a0 += kWave) {
           const int a = a0 + lane;
@@ -2147,6 +2158,7 @@ __device__ void phase_bfs_sweep(const Dev& g, int level, int kc, lds_int* lds) {
             ++narcs;
           }
         }
+        wave_lds_sync();
         got[t] |= flag[lane];
       }
       if (got[t] & 1) g.d[node + 1] = lvl;
@@ -2198,6 +2210,7 @@ __device__ void phase_bfs_sweep(const Dev& g, int level, int kc, lds_int* lds) {
       if (deg > kSweepLong && set_aside(v0 + lane)) deg = 0;
       if (__ballot(deg > 0)) {
         flag[lane] = 0;
+        wave_lds_sync();
         const int incl = wave_scan(deg), excl = incl - deg, A = __shfl(incl, kWave - 1);
         for (int a0 = 0; a0 < A; a0 += kWave) {
           const int a = a0 + lane;
@@ -2205,10 +2218,12 @@ __device__ void phase_bfs_sweep(const Dev& g, int level, int kc, lds_int* lds) {
           const int i = __shfl(b, lo) + a - __shfl(excl, lo);
           if (a < A) {
             const int2 x = g.vinc[i];
-            if (vertex_hit(x, nl[x.x >> 5])) flag[lo] = 1;  // every writer stores the same
+            if (vertex_hit(x, nl[x.x >> 5]))
+              __hip_atomic_store(flag + lo, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             ++narcs;
           }
         }
+        wave_lds_sync();
         if (flag[lane]) got[t] = true;
       }
       if (got[t]) g.d[v0 + lane] = lvl;

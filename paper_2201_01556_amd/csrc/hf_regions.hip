@@ -184,6 +184,7 @@ __global__ void __launch_bounds__(256) k_rg_pins(int E, const int32_t* off, cons
     const int e = base + lane;
     const int end = off[min(e, E - 1) + 1], first = off[base];
     mine[lane] = 0ull;
+    wave_lds_sync();
     const int last = __shfl(end, 63);
     for (int p0 = first; p0 < last; p0 += 64) {
       const int p = p0 + lane;
@@ -198,6 +199,7 @@ __global__ void __launch_bounds__(256) k_rg_pins(int E, const int32_t* off, cons
         atomicOr(&mine[lo], 1ull << block[pins[p]]);
       }
     }
+    wave_lds_sync();
     if (e < E) mask[e] = mine[lane];
   }
 }
@@ -567,6 +569,7 @@ __global__ void __launch_bounds__(kFlatBlock) k_rg_count_flat(RgGraph g, RgSide 
     const RgWaveItem it = rg_wave_item(g, t, base);
     cnt[lane] = 0;
     flg[lane] = 0;
+    wave_lds_sync();
     for (int a0 = 0; a0 < it.A; a0 += 64) {
       const int a = a0 + lane;
       const int lo = rg_owner(it.excl, a);
@@ -585,6 +588,7 @@ __global__ void __launch_bounds__(kFlatBlock) k_rg_count_flat(RgGraph g, RgSide 
         }
       }
     }
+    wave_lds_sync();
     bool keep = false, cut = false;
     if (it.k < t.nt) {
       const int f = flg[lane];
@@ -626,6 +630,7 @@ __global__ void __launch_bounds__(kFlatBlock) k_rg_write_flat(RgGraph g, RgSide 
     const long long pos0 = keep ? o.opos[it.k] : 0;
     cnt[lane] = 0;
     flg[lane] = 0;
+    wave_lds_sync();
     for (int a0 = 0; a0 < it.A; a0 += 64) {
       const int a = a0 + lane;
       const int lo = rg_owner(it.excl, a);
@@ -646,6 +651,7 @@ __global__ void __launch_bounds__(kFlatBlock) k_rg_write_flat(RgGraph g, RgSide 
       if (c == 1) atomicAdd(&cnt[lo], 1);
       if (c == 2) atomicOr(&flg[lo], 1);
       if (c == 3) atomicOr(&flg[lo], 2);
+      wave_lds_sync();
     }
     if (keep) {
       const int K = o.kidx[it.k];

@@ -1,6 +1,8 @@
-"""Device helpers that are plain arithmetic, compiled for the host with hipcc
-and compared with exact integers (no GPU needed)."""
+"""What can be checked of the device code without a GPU: helpers that are plain
+arithmetic, compiled for the host with hipcc and compared with exact integers,
+and the compiler's intermediate code of the kernels for gfx950."""
 import os
+import re
 import subprocess
 
 import pytest
@@ -52,3 +54,29 @@ def test_net_residual_bits_at_the_ends_of_int(tmp_path):
         x_in, x_out = c[2] + c[4] + c[6], c[3] + c[5] + c[7]
         want = (fb < w) | (fb - x_out > 0) << 1 | (fb > 0) << 2 | (fb + x_in > 0) << 3
         assert int(got) == want, c
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="hipcc not available")
+@pytest.mark.parametrize("source,exchanges", [
+    ("hf_solve.hip", {"k_bfs_sweep": 4}),
+    ("hf_regions.hip", {"k_rg_pins": 2, "k_rg_count_flat": 2, "k_rg_write_flat": 2}),
+], ids=lambda x: x if isinstance(x, str) else "")
+def test_lds_exchanges_of_a_wave_are_ordered(tmp_path, source, exchanges):
+    """Kernels whose lanes hand values to each other through LDS inside a wave
+    order the accesses by wavefront fences around a wave barrier: nothing else
+    keeps the compiler from using a lane's own last value.  Two exchanges (the
+    clearing and the reading) per LDS tally."""
+    out = tmp_path / "kernels.ll"
+    flags = [f for f in build.FLAGS if f not in ("-O3", "-fPIC")]
+    r = subprocess.run([build.HIPCC, *flags, "-O1", "-w", "--cuda-device-only", "-emit-llvm", "-S",
+                        os.path.join(build.CSRC, source), "-o", str(out)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    text = out.read_text()
+    for kernel, least in exchanges.items():
+        body = re.search(r"^define [^\n]*\d" + kernel + r"[A-Z][^\n]*\{\n(.*?)^\}", text, re.S | re.M)
+        assert body, kernel
+        found = re.findall(r'fence syncscope\("wavefront"\) release\s+'
+                           r"(?:tail )?call void @llvm.amdgcn.wave.barrier\(\)[^\n]*\s+"
+                           r'fence syncscope\("wavefront"\) acquire', body.group(1))
+        assert len(found) >= least, (kernel, len(found))

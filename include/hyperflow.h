@@ -84,8 +84,11 @@ typedef struct {
                                  2 = only the reverse-BFS level kernel (see
                                  flow_problem_kernel_times)                  */
   int32_t gr_interval;        /* also relabel globally after this many rounds
-                                 since the last global relabel; default 10,
-                                 -1 = only by relabel count and stale flow  */
+                                 since the last global relabel; default 10
+                                 (16 for networks of 1048576 nodes or more
+                                 whose levels are not swept, see
+                                 bottom_up_min), -1 = only by relabel count
+                                 and stale flow                              */
   int32_t stale_rounds;       /* also relabel globally once the flow value
                                  stayed unchanged for this many rounds with a
                                  small frontier (paper, paragraph "Avoid
@@ -95,9 +98,15 @@ typedef struct {
                                  by a sweep in which every unlabelled node
                                  looks for an arc into the level, in the
                                  forward BFS by plain stamps and a sweep that
-                                 collects them; default N/16 (at least
-                                 262144) from 1048576 nodes on, below that
-                                 and with -1 never                           */
+                                 collects them.  Where reverse levels are not
+                                 swept (other forms of a level chosen below,
+                                 or nets with far more pins than there are
+                                 nodes), they are expanded and collected.
+                                 Default from 1048576 nodes on: N/16 (at least
+                                 262144) if swept, else N/50; with fewer
+                                 nodes N/50 (at least 1024) from 2097152 pins
+                                 and 16 pins per node on, else never; -1 =
+                                 never                                       */
   int32_t bfs_arc_parallel;   /* 1 = BFS levels split work per arc (prefix sum
                                  over the level's arc counts) instead of per
                                  node; default 0                             */
@@ -107,7 +116,8 @@ typedef struct {
                                  (stops at the first); 0 = never            */
   int32_t tail_gr_interval;   /* rounds between global relabels while the
                                  frontier fits the single-workgroup loop
-                                 (tail_threshold); default 5/2 of gr_interval,
+                                 (tail_threshold); default 5/2 of gr_interval
+                                 (4 times where gr_interval's is 16),
                                  -1 = gr_interval                            */
   int32_t bfs_flat;           /* expanded reverse-BFS levels spread the arcs
                                  of a wave's 64 nodes over its lanes; 1 = on

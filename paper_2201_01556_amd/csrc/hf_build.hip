@@ -289,15 +289,6 @@ fp_options resolve_options(const fp_options* o) {
   if (r.tail_threshold <= 0) r.tail_threshold = 256;
   if (r.group_lanes != 4 && r.group_lanes != 8 && r.group_lanes != 16) r.group_lanes = 16;
   if (r.big_degree <= 0) r.big_degree = 32;
-  // Rounds between global relabels, and 2.5 times as many in the
-  // single-workgroup loop, whose rounds cost microseconds.  Intervals 16 (64 in
-  // the loop) / 10 (24) / 8 (24), means over eight seeds in us: V = 2k
-  // 2121 / 2123 / 2087, 12k 3840 / 3681 / 3524, 40k 5475 / 4831 / 4892, 100k
-  // 7166 / 6412 / 6517, 300k 9894 / 8764 / 9430, 1M 15671 / 15330 / 16403,
-  // region problems of 5k, 20k and 40k vertices 2505 / 2489 / 2470,
-  // 2771 / 2574 / 2474, 3729 / 3264 / 3754.
-  if (r.gr_interval == 0) r.gr_interval = 10;
-  if (r.gr_interval < 0) r.gr_interval = 0;
   if (r.stale_rounds == 0) r.stale_rounds = 500;
   if (r.stale_rounds < 0) r.stale_rounds = 0;
   if (r.bfs_flat == 0) r.bfs_flat = 1;
@@ -346,16 +337,7 @@ fp_status build_problem(fp_problem* pb, const int32_t* net_offsets, const int32_
     set_error("network too large for 31-bit ids (V=%d E=%d P=%d)", V, E, P);
     return FP_ERR_OVERFLOW;
   }
-  // Where a reverse-BFS level is swept instead of claimed: sweeping costs two
-  // more launches a level and a pass over the unlabelled nodes, so it needs
-  // levels of some hundred thousand nodes.  Swept from N/50, N/16 and N/8 on
-  // and never, a 7.4M-pin flow (N = 5 M, levels of 0.5-1.3 M) takes 19.5, 19.0,
-  // 19.1 and 23.1 ms; one of 740k pins (N = 500k, levels of up to 130k) 7.9,
-  // 7.5, 7.4 and 7.0 ms, and a region problem (N = 100k) 3.4 ms against 3.0
-  // never.
-  if (pb->opt.bottom_up_min == 0)
-    pb->opt.bottom_up_min = N >= (1 << 20) ? (int32_t)std::max<long long>(N / 16, 262144) : -1;
-  if (pb->opt.bottom_up_min < 0) pb->opt.bottom_up_min = 0;
+  resolve_by_size(&pb->opt, V, E, P, N);
   pb->P = P;
   pb->NB = (int32_t)NB;
   pb->N = (int32_t)N;
@@ -469,29 +451,14 @@ fp_status build_problem(fp_problem* pb, const int32_t* net_offsets, const int32_
   g.netres = c.take<uint32_t>((E + 7) / 8);
   uint8_t* lev = c.take<uint8_t>(N);
   g.lev = pb->opt.bfs_marks > 0 ? lev : nullptr;
-  // The bitmaps of swept reverse-BFS levels lie in the memory of the byte
-  // marks, which only another form of a level uses; N bytes hold them unless
-  // nets have far more pins than there are nodes (the levels are then expanded
-  // from their lists).
   {
-    const size_t vf_b = align_up(((size_t)V + 63) / 64 * 8),
-                 nl_b = align_up(((size_t)E + 63) / 64 * 16),
-                 free_b = align_up(((size_t)P + 31) / 32 * 4);
-    const bool fits = 2 * vf_b + 2 * nl_b + free_b <= (size_t)N;
-    const bool flat = pb->opt.bfs_flat > 0 && pb->opt.bfs_arc_parallel == 0 &&
-                      pb->opt.bfs_marks <= 0 && pb->opt.bfs_xcd <= 0 && pb->opt.pull_min <= 0;
-    g.pinfree = nullptr;
+    const SweepMaps m(V, E, P, N);
+    const bool swept = levels_swept(pb->opt, m);
     for (int i = 0; i < 2; ++i) {
-      g.vf[i] = nullptr;
-      g.nl[i] = nullptr;
+      g.vf[i] = swept ? reinterpret_cast<uint32_t*>(lev + i * m.vf) : nullptr;
+      g.nl[i] = swept ? reinterpret_cast<uint2*>(lev + 2 * m.vf + i * m.nl) : nullptr;
     }
-    if (fits && flat) {
-      for (int i = 0; i < 2; ++i) {
-        g.vf[i] = reinterpret_cast<uint32_t*>(lev + i * vf_b);
-        g.nl[i] = reinterpret_cast<uint2*>(lev + 2 * vf_b + i * nl_b);
-      }
-      g.pinfree = reinterpret_cast<uint32_t*>(lev + 2 * vf_b + 2 * nl_b);
-    }
+    g.pinfree = swept ? reinterpret_cast<uint32_t*>(lev + 2 * m.vf + 2 * m.nl) : nullptr;
   }
   g.xbuf = nullptr;
   g.xcnt = nullptr;

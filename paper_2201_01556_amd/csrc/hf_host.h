@@ -131,8 +131,82 @@ namespace hf {
 void set_error(const char* fmt, ...);
 fp_status hip_fail(hipError_t e, const char* what);
 
-// defaults filled in
+// defaults filled in, but for those that the size decides (resolve_by_size)
 fp_options resolve_options(const fp_options* o);
+
+// Bytes of the bitmaps of swept reverse-BFS levels (Dev::vf, nl, pinfree).
+// They lie in the memory of the byte marks, which only another form of a level
+// uses: its N bytes hold them unless nets have far more pins than there are
+// nodes.
+struct SweepMaps {
+  size_t vf, nl, pinfree;
+  bool fit;
+  SweepMaps(long long V, long long E, long long P, long long N) {
+    auto up = [](long long n) { return (size_t)((n + 255) & ~255ll); };
+    vf = up((V + 63) / 64 * 8);
+    nl = up((E + 63) / 64 * 16);
+    pinfree = up((P + 31) / 32 * 4);
+    fit = (long long)(2 * vf + 2 * nl + pinfree) <= N;
+  }
+};
+
+// Whether large reverse-BFS levels are swept (phase_bfs_sweep): in the default
+// form of a level, if the bitmaps fit.
+inline bool levels_swept(const fp_options& o, const SweepMaps& m) {
+  return m.fit && o.bfs_flat > 0 && o.bfs_arc_parallel == 0 && o.bfs_marks <= 0 &&
+         o.bfs_xcd <= 0 && o.pull_min <= 0;
+}
+
+constexpr long long kSweepNodes = 1 << 20;  // networks with levels worth a sweep
+
+// A large network whose levels cannot be swept: its relabels cost more.
+inline bool dear_relabels(long long N, bool swept) { return N >= kSweepNodes && !swept; }
+
+// The defaults that depend on the network's size and form.
+//
+// bottom_up_min, from how many nodes on a level is handled without claims.
+// Swept: a sweep costs two more launches a level and a pass over the
+// unlabelled nodes, so it needs levels of some hundred thousand nodes.  From
+// N/50, N/16 and N/8 on and never, a 7.4M-pin flow (N = 5 M, levels of 0.5-1.3 M)
+// takes 19.5, 19.0, 19.1 and 23.1 ms; one of 740k pins (N = 500k, levels of up
+// to 130k) 7.9, 7.5, 7.4 and 7.0 ms, and a region problem (N = 100k) 3.4 ms
+// against 3.0 never.  Not swept, a level is expanded from its list with plain
+// stores, which pays where a level holds many arcs per node, since a claim is
+// an atomic per arc: nets of 60 pins, from N/50 on against N/16 and never, 16.2 /
+// 17.4 / 18.7 ms at N = 1.1 M, 11.6 / - / 12.4 at 660k, 4.9 / - / 5.1 at 220k, but
+// 3.0 / - / 2.7 at 44k (720k pins); nets of 200 and 500 pins, N = 40k to 140k, 3.1 to
+// 4.1 against 3.8 to 5.3; nets of 20 and 30 pins are faster with claims.
+//
+// gr_interval, rounds between global relabels.  Intervals 16 (64 in the
+// single-workgroup loop) / 10 (24) / 8 (24), means over eight seeds in us: V = 2k
+// 2121 / 2123 / 2087, 12k 3840 / 3681 / 3524, 40k 5475 / 4831 / 4892, 100k
+// 7166 / 6412 / 6517, 300k 9894 / 8764 / 9430, 1M 15671 / 15330 / 16403,
+// region problems of 5k, 20k and 40k vertices 2505 / 2489 / 2470,
+// 2771 / 2574 / 2474, 3729 / 3264 / 3754.  Dear relabels keep the longer interval:
+// 60-pin nets with N = 1.1 M 15.1 ms at 16 (64), 16.2 at 10 (25); a 7.4M-pin flow
+// with bfs_arc_parallel 46.3 and 49.4, with bfs_flat = -1 18.4 and 19.1, with
+// pull_min 83.7 and 89.7.
+inline void resolve_by_size(fp_options* o, long long V, long long E, long long P, long long N) {
+  const bool swept = levels_swept(*o, SweepMaps(V, E, P, N));
+  const bool many_arcs = P >= 16 * N && P >= (1 << 21);
+  if (o->bottom_up_min == 0)
+    o->bottom_up_min = N >= kSweepNodes && swept ? (int32_t)(N / 16 > 262144 ? N / 16 : 262144)
+                       : N >= kSweepNodes || many_arcs ? (int32_t)(N / 50 > 1024 ? N / 50 : 1024)
+                                                       : -1;
+  if (o->bottom_up_min < 0) o->bottom_up_min = 0;
+  if (o->gr_interval == 0) o->gr_interval = dear_relabels(N, swept) ? 16 : 10;
+  if (o->gr_interval < 0) o->gr_interval = 0;
+}
+
+// Rounds between global relabels while the frontier fits the single-workgroup
+// loop.  Its rounds cost a few microseconds and a global relabel (a BFS over
+// every node) as much as two hundred of them, so it relabels less often: 2.5
+// times gr_interval, 4 times where relabels are dear (the figures above).
+inline int tail_rounds(const fp_options& o, long long N, bool swept) {
+  if (o.tail_gr_interval > 0) return o.tail_gr_interval;
+  if (o.tail_gr_interval < 0) return o.gr_interval;
+  return dear_relabels(N, swept) ? 4 * o.gr_interval : 5 * o.gr_interval / 2;
+}
 
 // Validate the inputs and build the device layout.  With `ext` the layout
 // (and the temporary memory of the build) is carved from the caller's

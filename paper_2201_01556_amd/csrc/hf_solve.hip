@@ -698,12 +698,7 @@ static fp_status solve_impl(fp_problem* pb, hipStream_t s, int64_t* flow) {
   const unsigned long long budget =
       (unsigned long long)((double)g.N * pb->opt.relabel_factor_x16 / 16.0) + 1ull;
   const int gr_interval = pb->opt.gr_interval;
-  // Once the frontier fits one workgroup, rounds cost a few microseconds and
-  // a global relabel (a BFS over every node) as much as two hundred of them,
-  // so the tail relabels less often (the figures are at the defaults).
-  const int tail_interval = pb->opt.tail_gr_interval > 0 ? pb->opt.tail_gr_interval
-                            : pb->opt.tail_gr_interval < 0 ? gr_interval
-                                                           : 5 * gr_interval / 2;
+  const int tail_interval = tail_rounds(pb->opt, g.N, g.pinfree != nullptr);
   const int stale_limit = pb->opt.stale_rounds;
   unsigned long long rel_at_gr = pb->ctl_h->relabels;
   unsigned long long last_flow = pb->ctl_h->flow;

@@ -80,3 +80,67 @@ def test_lds_exchanges_of_a_wave_are_ordered(tmp_path, source, exchanges):
                            r"(?:tail )?call void @llvm.amdgcn.wave.barrier\(\)[^\n]*\s+"
                            r'fence syncscope\("wavefront"\) acquire', body.group(1))
         assert len(found) >= least, (kernel, len(found))
+
+
+DEFAULTS = r"""
+#include <cstdio>
+#include "hf_host.h"
+int main() {
+  long long V, E, P;
+  int arc, flat, pull, bu, gi, tail;
+  while (scanf("%lld %lld %lld %d %d %d %d %d %d", &V, &E, &P, &arc, &flat, &pull, &bu, &gi,
+               &tail) == 9) {
+    fp_options o{};
+    o.bfs_flat = flat;
+    o.bfs_arc_parallel = arc;
+    o.pull_min = pull;
+    o.bottom_up_min = bu;
+    o.gr_interval = gi;
+    o.tail_gr_interval = tail;
+    const long long N = ((V + 1) & ~1ll) + 2 * E;
+    const bool swept = hf::levels_swept(o, hf::SweepMaps(V, E, P, N));
+    hf::resolve_by_size(&o, V, E, P, N);
+    printf("%d %d %d\n", o.bottom_up_min, o.gr_interval, hf::tail_rounds(o, N, swept));
+  }
+  return 0;
+}
+"""
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="hipcc not available")
+def test_defaults_by_size_and_form(tmp_path):
+    """Level threshold (0 = never) and relabel intervals that a network's size
+    and the form of its levels select.  Large networks whose levels cannot be
+    swept (nets with far more pins than nodes, another form of a level chosen)
+    and smaller ones with many pins per node expand their levels from N/50 on;
+    the former also keep the longer intervals."""
+    # V, E, P, bfs_arc_parallel, bfs_flat, pull_min, bottom_up_min, gr_interval, tail -> result
+    table = [
+        ((2000, 3000, 15_000, 0, 1, 0, 0, 0, 0), (0, 10, 25)),
+        ((100_000, 200_000, 740_000, 0, 1, 0, 0, 0, 0), (0, 10, 25)),
+        ((1_000_000, 2_000_000, 7_400_000, 0, 1, 0, 0, 0, 0), (312_500, 10, 25)),
+        ((1 << 20, 0, 0, 0, 1, 0, 0, 0, 0), (262_144, 10, 25)),
+        ((1_000_000, 2_000_000, 7_400_000, 1, 1, 0, 0, 0, 0), (100_000, 16, 64)),
+        ((1_000_000, 2_000_000, 7_400_000, 0, -1, 0, 0, 0, 0), (100_000, 16, 64)),
+        ((1_000_000, 2_000_000, 7_400_000, 0, 1, 20_000, 0, 0, 0), (100_000, 16, 64)),
+        ((100_000, 200_000, 740_000, 1, 1, 0, 0, 0, 0), (0, 10, 25)),
+        ((500_000, 300_000, 18_000_000, 0, 1, 0, 0, 0, 0), (22_000, 16, 64)),
+        ((100_000, 20_000, 10_000_000, 0, 1, 0, 0, 0, 0), (2800, 10, 25)),
+        ((20_000, 10_000, 5_000_000, 0, 1, 0, 0, 0, 0), (1024, 10, 25)),
+        ((20_000, 12_000, 720_000, 0, 1, 0, 0, 0, 0), (0, 10, 25)),
+        ((100_000, 60_000, 1_800_000, 0, 1, 0, 0, 0, 0), (0, 10, 25)),
+        # chosen by the caller
+        ((500_000, 300_000, 18_000_000, 0, 1, 0, 77, 8, 30), (77, 8, 30)),
+        ((500_000, 300_000, 18_000_000, 0, 1, 0, -1, -1, -1), (0, 0, 0)),
+        ((500_000, 300_000, 18_000_000, 0, 1, 0, 0, 8, 0), (22_000, 8, 32)),
+        ((100_000, 200_000, 740_000, 0, 1, 0, 0, 8, 0), (0, 8, 20)),
+    ]
+    src = tmp_path / "defaults.hip"
+    exe = tmp_path / "defaults"
+    src.write_text(DEFAULTS)
+    r = subprocess.run([build.HIPCC, *build.FLAGS, str(src), "-o", str(exe)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c, _ in table),
+                         capture_output=True, text=True, check=True).stdout.splitlines()
+    assert [tuple(map(int, line.split())) for line in out] == [want for _, want in table]

@@ -335,3 +335,32 @@ def test_round_budget_abort_then_resume(hf, oracle_mod):
     # a generous budget finishes
     F, vs, ns, _ = gpu_solve(hf, hg, round_budget=1 << 30)
     assert_same(hg, r, F, vs, ns, "budget")
+
+
+@pytest.mark.parametrize("V,E,pins", [(20_000, 10_000, 230), (400_000, 330_000, 30)])
+def test_levels_expanded_by_default(hf, V, E, pins):
+    """Networks with many pins per node, whose levels cannot be swept: the
+    default threshold expands them.  Flow and sides equal those of claimed
+    levels, and the cut's weight certifies the flow."""
+    rng = np.random.default_rng(V)
+    p = np.sort(rng.integers(0, V, (E, pins)), axis=1)
+    keep = np.ones((E, pins), bool)
+    keep[:, 1:] = p[:, 1:] != p[:, :-1]
+    off = np.zeros(E + 1, np.int32)
+    off[1:] = np.cumsum(keep.sum(1))
+    w = rng.integers(1, 4, E).astype(np.int32)
+    who = rng.permutation(V)[:V // 50].astype(np.int32)
+    args = (V, off, p[keep].astype(np.int32), w, np.sort(who[::2]), np.sort(who[1::2]))
+    _say(f"expanded by default V={V} pins={off[-1]}")
+    got = []
+    for opts in ({}, dict(bottom_up_min=-1)):
+        with hf.FlowProblem(*args, profile=1, **opts) as q:
+            F = q.solve()
+            vs, ns = q.source_side()
+            got.append((F, vs, ns))
+            collects = {k["kernel"]: k["launches"] for k in q.kernel_times()}["bfs_collect"]
+        assert (collects > 0) == (not opts)
+    assert got[0][0] == got[1][0]
+    assert (got[0][1] == got[1][1]).all() and (got[0][2] == got[1][2]).all()
+    ns = got[0][2]
+    assert int(w[(ns & 3) == 1].sum()) == got[0][0]

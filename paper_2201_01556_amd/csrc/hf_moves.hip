@@ -41,6 +41,7 @@ struct fp_partition {
 namespace hf {
 namespace {
 
+constexpr int kMvWalk = 768;  // threads of the workgroup that walks small stages
 
 size_t mv_align(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -266,6 +267,93 @@ __global__ void __launch_bounds__(256) k_mv_settle(fp_partition pt, MvSeq s, int
   }
 }
 
+// Workgroup sums of two values per thread (block-uniform).
+__device__ __forceinline__ void mv_sum2(long long& a, long long& b) {
+  __shared__ long long part[2][kMvWalk / 64];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o);
+    b += __shfl_xor(b, o);
+  }
+  const int wid = threadIdx.x >> 6;
+  if (__lane_id() == 0) {
+    part[0][wid] = a;
+    part[1][wid] = b;
+  }
+  __syncthreads();
+  a = b = 0;
+  for (int w = 0; w < kMvWalk / 64; ++w) {
+    a += part[0][w];
+    b += part[1][w];
+  }
+  __syncthreads();
+}
+
+// The same for a run of stages that hold one small pair each (at most a vertex
+// per thread): one workgroup walks them, since the three launches of a stage
+// cost 9.5 us however little it holds and a step of the walk 3 without moves.
+// Chains walked / in launches: 100 pairs of 40 to 600 vertices without moves
+// 0.31-0.33 / 0.89-0.97 ms; 28 pairs of 200 vertices with 1 %, 10 % and 50 % of
+// them moved 0.44 / 0.63, 0.75 / 0.94 and 0.90 / 1.08 ms, of 600 0.64 / 0.79,
+// 0.90 / 1.04 and 1.19 / 1.17, of 1,024 0.69 / 0.82, 0.97 / 1.06 and 1.58 / 1.20:
+// hence 768 threads.  The waves share one CU, so a workgroup barrier orders
+// their plain accesses.
+__global__ void __launch_bounds__(kMvWalk) k_mv_walk(fp_partition pt, MvSeq s, int first,
+                                                     int count) {
+  for (int t = first; t < first + count; ++t) {
+    const int q = s.stage[t];
+    const int i = s.pairs[2 * q], j = s.pairs[2 * q + 1];
+    const long long at = s.vbase[q] + threadIdx.x;
+    int u = 0, frm = 0, to = 0;
+    bool mv = false;
+    long long dwi = 0, cnt = 0;
+    if (threadIdx.x < s.nloc[q]) {
+      u = s.vgid[at];
+      frm = s.vside[at] ? j : i;
+      to = s.sides[q][threadIdx.x] ? i : j;
+      mv = to != frm && pt.block[u] == frm;
+      if (mv) {
+        dwi = to == i ? (long long)pt.cv[u] : -(long long)pt.cv[u];
+        cnt = 1;
+      }
+    }
+    mv_sum2(dwi, cnt);
+    const long long wi = (long long)pt.bw[i] + dwi, wj = (long long)pt.bw[j] - dwi;
+    const bool fits = wi <= s.lmax && wj <= s.lmax;  // block-uniform, as what follows
+    long long gain = 0, unused = 0;
+    if (fits && cnt > 0) {
+      if (mv) {
+        pt.block[u] = to;
+        for (int x = pt.voff[u]; x < pt.voff[u + 1]; ++x) {
+          const int e = pt.vnet[x];
+          const long long base = (long long)e * pt.k;
+          if (atomicSub(&pt.phi[base + frm], 1) == 1) gain += pt.w[e];
+          if (atomicAdd(&pt.phi[base + to], 1) == 0) gain -= pt.w[e];
+        }
+      }
+      mv_sum2(gain, unused);
+      if (gain < 0 && mv) {
+        pt.block[u] = frm;
+        for (int x = pt.voff[u]; x < pt.voff[u + 1]; ++x) {
+          const long long base = (long long)pt.vnet[x] * pt.k;
+          atomicSub(&pt.phi[base + to], 1);
+          atomicAdd(&pt.phi[base + frm], 1);
+        }
+      }
+    }
+    if (threadIdx.x == 0) {
+      if (fits && cnt > 0 && gain >= 0) {
+        pt.bw[i] = (unsigned long long)wi;
+        pt.bw[j] = (unsigned long long)wj;
+      }
+      s.out[3 * q] = !fits ? 2 : gain < 0 ? 3 : 1;
+      s.out[3 * q + 1] = gain;
+      s.out[3 * q + 2] = fits ? cnt : 0;
+    }
+    __syncthreads();
+  }
+}
+
 // cut[a * k + b] (a < b) = weight of the nets with pins in blocks a and b
 // (the quotient graph; k <= 64)
 __global__ void k_mv_pair_cuts(fp_partition pt, unsigned long long* cut) {
@@ -482,7 +570,14 @@ static fp_status partition_apply(fp_partition* pt, const fp_regions* rg,
                                                    12ll * npairs);
   // A vertex holds a few nets and each costs two dependent atomics, so a
   // thread takes one vertex until a stage alone fills the chip.
-  for (int t = 0; t < nstages; ++t) {
+  for (int t = 0; t < nstages;) {
+    int run = t;
+    while (run < nstages && first[run + 1] - first[run] == 1 && nmax[run] <= kMvWalk) ++run;
+    if (run > t) {
+      k_mv_walk<<<1, kMvWalk, 0, s>>>(*pt, q, first[t], run - t);
+      t = run;
+      continue;
+    }
     const int np = first[t + 1] - first[t];
     for (int f = 0; f < np; f += 65535) {  // grid y limit
       const int m = std::min(65535, np - f);
@@ -493,6 +588,7 @@ static fp_status partition_apply(fp_partition* pt, const fp_regions* rg,
       k_mv_move<<<grid, 256, 0, s>>>(*pt, q, first[t] + f);
       k_mv_settle<<<grid, 256, 0, s>>>(*pt, q, first[t] + f);
     }
+    ++t;
   }
   MV_TRY(hipGetLastError(), "applying the moves");
   std::vector<long long> res(3ull * npairs);

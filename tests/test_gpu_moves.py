@@ -162,3 +162,50 @@ def test_partition_counts_and_objective(hf, k):
     assert (blocks == block).all()
     assert bw.tolist() == np.bincount(block, weights=vw, minlength=k).astype(int).tolist()
     assert obj == omoves.connectivity(hg, block)
+
+
+@pytest.mark.parametrize("caps", [(1, 1), (40, 25), (384, 384), (384, 385)], ids=str)
+@pytest.mark.parametrize("shape", ["star", "same", "mixed"])
+def test_small_stages_vs_oracle(hf, caps, shape):
+    """Pairs that follow one another because they share a block, of up to as
+    many vertices as the workgroup has threads that walks them and of one more;
+    mixed with stages of several pairs.  The sides are random, so that gains
+    are negative too, and Lmax lets only some sequences pass."""
+    import torch
+    from oracle import moves as omoves
+    k, V = 8, 12_000
+    rng = np.random.default_rng(sum(caps))
+    hg = inputs.uniform_hypergraph(sum(caps), num_vertices=V, num_nets=16_000, size_hi=5)
+    block = (np.arange(V) % k).astype(np.int32)
+    vw = np.ones(V, np.int32)
+    pairs = {"star": [(0, j) for j in range(1, k)] * 2, "same": [(2, 5)] * 9,
+             "mixed": [(0, 1), (0, 2), (3, 4), (5, 6), (0, 3), (0, 7), (1, 2), (0, 1)]}[shape]
+    lmax = V // k + 20
+    with hf.FlowRegions(V, hg.net_offsets, hg.pins, hg.net_weights, vw, block, k,
+                        np.array(pairs, np.int32), np.array([caps] * len(pairs), np.int64)) as rg:
+        n = [rg.info(q)["n"] for q in range(len(pairs))]
+        assert max(n) == sum(caps)
+        # a few vertices move, or about half of them
+        sides, dev = [], []
+        for q in range(len(pairs)):
+            gid = rg.export(q)["vertex_ids"]
+            stay = block[gid] == pairs[q][0]
+            flip = rng.random(n[q]) < (0.5 if q % 3 == 2 else 4.0 / n[q])
+            sides.append((stay ^ flip).astype(np.uint8))
+            dev.append(torch.from_numpy(sides[q]).cuda())
+        gains = np.ones(len(pairs), np.int64)
+        gains[1] = 0  # not tried
+        torch.cuda.synchronize()
+        _say(f"small stages {shape} caps {caps}")
+        with hf.FlowPartition(V, hg.net_offsets, hg.pins, hg.net_weights, vw, block, k) as part:
+            st, g, mv = part.apply(rg, dev, gains, lmax)
+            blocks, bw, obj = part.get()
+        seqs = [dict(pair=pairs[q], gid=rg.export(q)["vertex_ids"],
+                     expected=block[rg.export(q)["vertex_ids"]], side=sides[q],
+                     gain=int(gains[q])) for q in range(len(pairs))]
+    ref_block, ref = omoves.apply_sequences(hg, block, vw, k, lmax, seqs)
+    assert [tuple(int(x) for x in r) for r in ref] == list(zip(st.tolist(), g.tolist(),
+                                                               mv.tolist()))
+    assert (blocks == ref_block).all()
+    assert (bw == np.bincount(ref_block, minlength=k)).all()
+    assert obj == omoves.connectivity(hg, ref_block)

@@ -708,7 +708,7 @@ __global__ void __launch_bounds__(B) k_batch_wg(const Dev* devs, const int32_t* 
                                                          WgParams p, WgResult* res) {
   // the sweeps' staging area, the rounds' or the searches' lists
   constexpr int kWords = lds_words(B) > kLoopWords ? lds_words(B) : kLoopWords;
-  __shared__ int32_t bq[kWords > kWgBfsWords ? kWords : kWgBfsWords];
+  __shared__ __attribute__((aligned(8))) int32_t bq[kWords > kWgBfsWords ? kWords : kWgBfsWords];
   lds_int* const lds = (lds_int*)bq;
   __shared__ int32_t slot;
   for (;;) {

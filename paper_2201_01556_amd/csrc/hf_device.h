@@ -537,7 +537,17 @@ struct LoopQ {
   lds_int* ncnt;  // its counts
   lds_int* cand;  // candidates of the current entries, kNL x kLoopCap
 };
-constexpr int kLoopWords = 3 * kNL * kLoopCap + 3 * kNL + 6;
+constexpr int kLoopWords = 3 * kNL * kLoopCap + 3 * kNL + 6 + 4;
+static_assert((kLoopWords - 4) % 2 == 0, "the 64-bit sums at the end of the area");
+
+// Flow into the sinks, straight into the round's sum (at most INT32_MAX in all):
+// few arcs reach a sink, and no register is held through the pushes.
+struct LoopSink {
+  lds_int* flow;
+  __device__ __forceinline__ void operator+=(uint32_t n) const {
+    if (n) (void)lds_add(flow, (int)n);
+  }
+};
 
 __device__ __forceinline__ void loop_append(const Dev& g, const RoundArgs& ra, const LoopQ& q,
                                             int k, int v) {
@@ -662,9 +672,9 @@ __device__ void push_vertex(const Dev& g, const RoundArgs& ra, const Q& q, int s
   finish_push<G>(g, q, slot, u, UX, carry, cand, gl, active, has);
 }
 
-template <int G, class Q>
+template <int G, class Q, class S>
 __device__ void push_ein(const Dev& g, const RoundArgs& ra, const Q& q, int slot, int node,
-                         bool has, int gl, uint32_t& nbytes, unsigned long long& to_sink) {
+                         bool has, int gl, uint32_t& nbytes, S& to_sink) {
   const int e = (node - g.NB) >> 1;
   int k = 0, X = 0;
   if (has) {
@@ -722,9 +732,9 @@ __device__ void push_ein(const Dev& g, const RoundArgs& ra, const Q& q, int slot
   finish_push<G>(g, q, slot, node, UX, carry, cand, gl, active, has);
 }
 
-template <int G, class Q>
+template <int G, class Q, class S>
 __device__ void push_eout(const Dev& g, const RoundArgs& ra, const Q& q, int slot, int node,
-                          bool has, int gl, uint32_t& nbytes, unsigned long long& to_sink) {
+                          bool has, int gl, uint32_t& nbytes, S& to_sink) {
   const int e = (node - g.NB) >> 1;
   int k = 0, X = 0;
   if (has) {
@@ -782,10 +792,10 @@ __device__ void push_eout(const Dev& g, const RoundArgs& ra, const Q& q, int slo
   finish_push<G>(g, q, slot, node, UX, carry, cand, gl, active, has);
 }
 
-template <int G, class Q>
+template <int G, class Q, class S>
 __device__ __forceinline__ void push_node(const Dev& g, const RoundArgs& ra, const Q& q, int slot,
                                           int v, bool has, int gl, uint32_t& nbytes,
-                                          unsigned long long& to_sink) {
+                                          S& to_sink) {
   // kind is wave-divergent only across groups; each branch is group-uniform
   if (!has || v < g.V) push_vertex<G>(g, ra, q, slot, v, has, gl, nbytes);
   else if (((v - g.NB) & 1) == 0) push_ein<G>(g, ra, q, slot, v, has, gl, nbytes, to_sink);
@@ -883,6 +893,24 @@ __device__ void phase_apply(const Dev& g, int epoch, int tile0, int tstride, int
   block_add_u64(&g.ctl->relabels, nrel, &g.ctl->bytes[kc], nbytes, &g.ctl->items[kc], nrel);
 }
 
+// a value that is the same in every lane, kept in a scalar register
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// What is left of `limit` at `now`, as the loop's 32-bit limit: the relabels of
+// one more round, at most N, on top of it still fit 32 bits.
+__device__ __forceinline__ uint32_t relabels_left(unsigned long long limit,
+                                                  unsigned long long now) {
+  const unsigned long long left = limit > now ? limit - now : 0ull;
+  return left > 0x7fffffffull ? 0x7fffffffu : (uint32_t)left;
+}
+
+struct LoopEnd {
+  int why, rounds, stale;  // stale: rounds since the flow value changed
+  bool flowed;             // the flow value changed
+};
+
+constexpr int kStaleFrontier = 1500;  // "only few active nodes" (paragraph "Avoid Pushing Flow Back")
+
 // Rounds inside one workgroup from round `epoch`'s frontier, which holds at
 // most `cap` nodes (at most kLoopCap, unless kAny: entries past the LDS lists
 // are then read from the global ones).  Ends when the frontier is empty (why 1),
@@ -898,29 +926,11 @@ __device__ void phase_apply(const Dev& g, int epoch, int tile0, int tstride, int
 // round's flow and relabel counts live in LDS (a ring of three, so that the
 // two barriers of a round, after the pushes and after the relabels, also
 // order the counters), the delivery's own atomic tells whether it is the
-// first, and the statistics stay in registers until the loop ends: 6.7 us a
-// round instead of 16 on a 2,000-vertex flow (1,024 threads; values that are
-// the same in every lane are kept in scalar registers, which takes the kernel
-// from 109 to 75 vector registers).  Every
-// exit test reads counters that no wave writes before the next barrier, so
-// all waves take the same decision.
-// a value that is the same in every lane, kept in a scalar register
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// What is left of `limit` at `now`, as the loop's 32-bit limit.
-__device__ __forceinline__ uint32_t relabels_left(unsigned long long limit,
-                                                  unsigned long long now) {
-  const unsigned long long left = limit > now ? limit - now : 0ull;
-  return left > 0xffffffffull ? 0xffffffffu : (uint32_t)left;
-}
-
-struct LoopEnd {
-  int why, rounds, stale;  // stale: rounds since the flow value changed
-  bool flowed;             // the flow value changed
-};
-
-constexpr int kStaleFrontier = 1500;  // "only few active nodes" (paragraph "Avoid Pushing Flow Back")
-
+// first, and the statistics stay in LDS and registers until the loop ends: 6.7
+// us a round instead of 16 on a 2,000-vertex flow (1,024 threads; values that
+// are the same in every lane are kept in scalar registers).  Every exit test
+// reads counters that no wave writes before the next barrier, so all waves take
+// the same decision.
 template <int G, bool kAny>
 __device__ LoopEnd wg_rounds(const Dev& g, int epoch, int max_rounds, int cap,
                              uint32_t relabel_limit, int stale_limit, int kc, lds_int* lds) {
@@ -928,6 +938,7 @@ __device__ LoopEnd wg_rounds(const Dev& g, int epoch, int max_rounds, int cap,
   lds_int* const cand = lds + 2 * kNL * kLoopCap;   // [kNL][kLoopCap]
   lds_int* const cnt = lds + 3 * kNL * kLoopCap;    // [3][kNL]
   lds_int* const acc = cnt + 3 * kNL;               // [3]{flow, relabels}
+  lds_u64* const sum = (lds_u64*)(acc + 6);         // of all rounds: flow, items
   const int tid = threadIdx.x, lane = lane_id(), wid = uni(tid >> 6), nw = blockDim.x >> 6;
   LoopEnd end{0, 0, 0, false};
   {
@@ -942,16 +953,15 @@ __device__ LoopEnd wg_rounds(const Dev& g, int epoch, int max_rounds, int cap,
     __syncthreads();  // earlier users of the area are done with it
     if (tid < 3 * kNL) cnt[tid] = tid / kNL == ra.cur3 ? n[tid % kNL] : 0;
     if (tid >= 64 && tid < 70) acc[tid - 64] = 0;
+    if (tid < 2) sum[tid] = 0ull;
 #pragma unroll
     for (int k = 0; k < kNL; ++k)
       for (int i = tid; i < min(n[k], kLoopCap); i += blockDim.x)
         buf[(ra.cur * kNL + k) * kLoopCap + i] = g.list[ra.cur][k][i];
     __syncthreads();
   }
-  unsigned long long nbytes_all = 0;
-  uint32_t to_sink_all = 0, nrel_all = 0;  // the flow value is at most INT32_MAX
   uint32_t relabels = 0;  // of the workgroup
-  uint32_t nitems = 0;
+  uint32_t nbytes = 0;    // of the lane
   for (;;) {
     const RoundArgs ra = round_args(epoch);
     const Quad n{uni(cnt[ra.cur3 * kNL]), uni(cnt[ra.cur3 * kNL + 1]),
@@ -966,31 +976,33 @@ __device__ LoopEnd wg_rounds(const Dev& g, int epoch, int max_rounds, int cap,
     const lds_int* const cbuf = buf + ra.cur * kNL * kLoopCap;
     const LoopQ q{buf + ra.nxt * kNL * kLoopCap, cnt + ra.nxt3 * kNL, cand};
     constexpr int GN = lanes_of<G>(1);
-    uint32_t nbytes = 0;
-    unsigned long long to_sink = 0;
+    LoopSink to_sink{acc + 2 * ra.cur3};
     for (int it = wid; it < its.total(); it += nw) {
       const int k = its.list_of_item(it);
+      // With 16 lanes a vertex the batch's workgroups, which hold a whole solve
+      // in 128 registers, would spill two: the lane arithmetic of the kinds (and
+      // the scan masks derived from it) is recomputed per item instead of being
+      // carried through all rounds.
+      int ln = lane;
+      if (kAny && G == 16) asm volatile("" : "+v"(ln));
       if (k < kBigList) {
         const int gk = k == 0 ? G : GN;
-        const int idx = (it - its.start[k]) * (kWave / gk) + lane / gk;
+        const int idx = (it - its.start[k]) * (kWave / gk) + ln / gk;
         const bool has = idx < n[k];
         const bool far = kAny && idx >= kLoopCap;
         const int slot = far ? -1 : k * kLoopCap + idx;
         const int v = !has ? 0 : (far ? g.list[ra.cur][k][idx] : (int)cbuf[slot]);
-        nitems += has && (lane % gk) == 0;
-        if (k == 0) push_vertex<G>(g, ra, q, slot, v, has, lane % G, nbytes);
-        else if (k == 1) push_ein<GN>(g, ra, q, slot, v, has, lane % GN, nbytes, to_sink);
-        else push_eout<GN>(g, ra, q, slot, v, has, lane % GN, nbytes, to_sink);
+        if (k == 0) push_vertex<G>(g, ra, q, slot, v, has, ln % G, nbytes);
+        else if (k == 1) push_ein<GN>(g, ra, q, slot, v, has, ln % GN, nbytes, to_sink);
+        else push_eout<GN>(g, ra, q, slot, v, has, ln % GN, nbytes, to_sink);
       } else {
         const int idx = it - its.start[kBigList];
         const bool far = kAny && idx >= kLoopCap;
         const int slot = far ? -1 : kBigList * kLoopCap + idx;
         const int v = far ? g.list[ra.cur][kBigList][idx] : (int)cbuf[slot];
-        nitems += lane == 0;
-        push_node<kWave>(g, ra, q, slot, v, true, lane, nbytes, to_sink);
+        push_node<kWave>(g, ra, q, slot, v, true, ln, nbytes, to_sink);
       }
     }
-    if (to_sink) lds_add(acc + 2 * ra.cur3, (int)to_sink);  // at most INT32_MAX in all
     __syncthreads();
     // the ring slot of the round after next: last read before this barrier
     const int z3 = (epoch + 2) % 3;
@@ -1028,13 +1040,17 @@ __device__ LoopEnd wg_rounds(const Dev& g, int epoch, int max_rounds, int cap,
         nbytes += 8;
       }
       const unsigned long long m = __ballot(rel);
-      nrel_all += rel;
       if (lane == 0 && m) lds_add(acc + 2 * ra.cur3 + 1, __popcll(m));
     }
-    nbytes_all += nbytes;
-    to_sink_all += (uint32_t)to_sink;
     __syncthreads();
     const int fl = uni(acc[2 * ra.cur3]);
+    if (tid < 2)
+      __hip_atomic_fetch_add(sum + tid, (unsigned long long)(tid == 0 ? fl : pre.total),
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (nbytes >> 31) {  // a round adds less than this
+      atomicAdd(&g.ctl->bytes[kc], (unsigned long long)nbytes);
+      nbytes = 0;
+    }
     relabels += (uint32_t)uni(acc[2 * ra.cur3 + 1]);
     ++epoch;
     ++end.rounds;
@@ -1055,13 +1071,12 @@ __device__ LoopEnd wg_rounds(const Dev& g, int epoch, int max_rounds, int cap,
   }
   if (tid < 3 * kNL)
     g.ctl->fcnt[tid / kNL][tid % kNL] = tid / kNL == ra.cur3 ? (int)cnt[tid] : 0;
-  // kAny (the batch's workgroups) leaves the byte and item statistics out
-  if (kAny) block_add_u64(&g.ctl->flow, to_sink_all, &g.ctl->relabels, nrel_all);
-  else {
-    block_add_u64(&g.ctl->flow, to_sink_all, &g.ctl->bytes[kc], nbytes_all + 4ull * nitems,
-                  &g.ctl->items[kc], nitems);
-    block_add_u64(&g.ctl->relabels, nrel_all);
+  if (tid < 2) {  // each the sum that it kept
+    const unsigned long long c = sum[tid];
+    if (c) atomicAdd(tid == 0 ? &g.ctl->flow : &g.ctl->items[kc], c);
+    if (tid == 0 && relabels) atomicAdd(&g.ctl->relabels, (unsigned long long)relabels);
   }
+  block_add_u64(&g.ctl->bytes[kc], nbytes + (tid == 1 ? 4ull * sum[1] : 0ull));
   return end;
 }
 

@@ -334,7 +334,7 @@ __global__ void __launch_bounds__(kLoopBlock) k_round_loop(Dev g, int epoch0, in
                                                            int cap,
                                                            unsigned long long relabel_limit,
                                                            int stale_limit) {
-  __shared__ int32_t area[kLoopWords];
+  __shared__ __attribute__((aligned(8))) int32_t area[kLoopWords];
   const LoopEnd end = wg_rounds<G, false>(
       g, epoch0, max_rounds, cap, relabels_left(relabel_limit, ld_vol64(&g.ctl->relabels)),
       stale_limit, KC_LOOP_ROUNDS, (lds_int*)area);

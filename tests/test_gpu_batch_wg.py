@@ -186,3 +186,30 @@ def test_round_loop_capacity(hf, oracle_mod, tail):
         assert p.solve() == ref.flow
         vs, ns = p.source_side()
     assert (vs == ref.vertex_side).all() and (ns == ref.net_side).all()
+
+
+@pytest.mark.parametrize("lanes,threads", [(4, 256), (8, 1024), (16, 1024)])
+def test_discharge_is_counted(hf, lanes, threads):
+    """The byte statistics of a handle hold the discharge of a solve by a
+    workgroup: at least a node's own fields (12 bytes and its list entry) per
+    round, and no more than every field of the network in every round."""
+    hgs = [inputs.uniform_hypergraph(34, num_vertices=1500, num_nets=2500, num_sources=70,
+                                     num_sinks=70),
+           inputs.uniform_hypergraph(35, num_vertices=6000, num_nets=9000, size_hi=30,
+                                     num_sources=1400, num_sinks=1400)]
+    probs = [hf.FlowProblem.from_hypergraph(h) for h in hgs]
+    try:
+        with hf.FlowBatch(probs, with_cut=True, schedule=3, group_lanes=lanes,
+                          wg_threads=threads) as b:
+            b.run(with_cut=True)
+        for h, p in zip(hgs, probs):
+            p.source_side()  # brings the device counters to the host
+            st = p.stats()
+            loop = {k["kernel"]: k["bytes"] for k in p.kernel_times()}["round_loop"]
+            fields = 60 * (h.num_vertices + 2 * h.num_nets) + 80 * h.num_pins
+            assert st["rounds"] > 0
+            assert 16 * st["rounds"] <= loop <= fields * st["rounds"], (loop, st["rounds"])
+            assert st["alg_bytes"] > loop
+    finally:
+        for p in probs:
+            p.close()

@@ -36,12 +36,38 @@ FLAGS = [
 ]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJDIR, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
-    r = subprocess.run(cmd, capture_output=True, text=True)
+# registers, spills and LDS of every kernel, read by register_spills
+REMARKS = "-Rpass-analysis=kernel-resource-usage"
+
+
+def register_spills(remarks: str) -> dict:
+    """Vector registers that each of the library's own kernels spills, from
+    the compiler's resource remarks (kernels of library headers left out)."""
+    out, name = {}, None
+    for line in remarks.splitlines():
+        if "Function Name:" in line:
+            name = line.split("Function Name:")[1].split()[0]
+        elif "VGPRs Spill:" in line and name and name.startswith("_ZN2hf"):
+            out[name] = int(line.split("VGPRs Spill:")[1].split()[0])
+    return out
+
+
+def compile_source(src: str, obj: str) -> None:
+    """Compile one source file.  A kernel that spills vector registers is
+    refused: a form of k_batch_wg with spills once left the source sides
+    unwritten while its flows were right, for a cause that was not found."""
+    r = subprocess.run([HIPCC, *FLAGS, REMARKS, "-c", src, "-o", obj], capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")
+    spills = {k: n for k, n in register_spills(r.stderr).items() if n}
+    if spills:
+        os.remove(obj)
+        raise RuntimeError(f"{src}: kernels spill vector registers: {spills}")
+
+
+def _compile(src: str) -> str:
+    obj = os.path.join(OBJDIR, os.path.splitext(src)[0] + ".o")
+    compile_source(os.path.join(CSRC, src), obj)
     return obj
 
 

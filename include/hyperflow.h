@@ -158,7 +158,10 @@ typedef struct {
                                relabel and BFS kernels since the handle was
                                created (device counters: a node's own fields
                                once, an arc's fields per scanned arc)        */
-  int64_t reserved[7];
+  int64_t swept_levels;     /* reverse-BFS levels that were swept (see
+                               fp_options.bottom_up_min) instead of expanded
+                               or claimed                                    */
+  int64_t reserved[6];
 } fp_stats;
 
 /*

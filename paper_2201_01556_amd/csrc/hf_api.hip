@@ -435,8 +435,11 @@ fp_status flow_problem_stats(const fp_problem* problem, fp_stats* out) {
   }
   *out = problem->st;
   out->alg_bytes = 0;
-  if (problem->ctl_h)
+  out->swept_levels = 0;
+  if (problem->ctl_h) {
     for (int c = 0; c < KC_N; ++c) out->alg_bytes += (int64_t)problem->ctl_h->bytes[c];
+    out->swept_levels = problem->ctl_h->nswept;
+  }
   return FP_OK;
 }
 

@@ -116,6 +116,7 @@ struct Ctl {
                              // the current global relabel
   int32_t bits_level;  // reverse-BFS level that the level bitmaps describe, -1 none
   int32_t swept;       // last level that was swept (phase_bfs_sweep), -1 none
+  int32_t nswept;      // levels swept since the state was initialised
   int32_t sweep_n[2][3];  // nodes per kind that the sweep of an even (odd) level found
   int32_t fc_done;        // iterations that the last FlowCutter loop finished
   int32_t fc_why;         // why it ended (FcExit)
@@ -2438,6 +2439,7 @@ __device__ void phase_init(const Dev& g, int t0, int tstride) {
     c->err = 0;
     c->flow = 0ull;
     c->relabels = 0ull;
+    c->nswept = 0;
     for (int i = 0; i < KC_N; ++i) c->bytes[i] = c->items[i] = 0ull;
   }
   const int n = max(g.P, g.N);

@@ -111,7 +111,10 @@ __global__ void __launch_bounds__(kBlock) HF_TWO_WORKGROUPS_PER_CU
 k_bfs_sweep(Dev g, int level, int big_min) {
   __shared__ int32_t area[kSweepWords];
   if (count_all(g.ctl->bcnt[level % 3]) < big_min || g.ctl->bits_level != level) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) g.ctl->swept = level;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    g.ctl->swept = level;
+    ++g.ctl->nswept;
+  }
   phase_bfs_sweep(g, level, KC_BFS_REV, (lds_int*)area);
 }
 

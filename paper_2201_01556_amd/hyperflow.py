@@ -77,7 +77,8 @@ class Stats(ctypes.Structure):
         ("host_syncs", ctypes.c_int64),
         ("flow_value", ctypes.c_int64),
         ("alg_bytes", ctypes.c_int64),
-        ("reserved", ctypes.c_int64 * 7),
+        ("swept_levels", ctypes.c_int64),
+        ("reserved", ctypes.c_int64 * 6),
     ]
 
 

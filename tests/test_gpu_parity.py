@@ -364,3 +364,45 @@ def test_levels_expanded_by_default(hf, V, E, pins):
     assert (got[0][1] == got[1][1]).all() and (got[0][2] == got[1][2]).all()
     ns = got[0][2]
     assert int(w[(ns & 3) == 1].sum()) == got[0][0]
+
+
+@pytest.mark.parametrize("V,E,long_nets,hubs,sweeps", [
+    (1023, 2047, 0, 0, True), (1024, 2048, 1, 0, True), (1025, 2049, 3, 0, True),
+    (1089, 2113, 4, 2, True), (2049, 2048, 2, 5, True), (9000, 20_001, 620, 3, True),
+    (9000, 8001, 620, 3, False)], ids=str)
+def test_levels_are_swept_where_the_bitmaps_fit(hf, oracle_mod, V, E, long_nets, hubs, sweeps):
+    """The instances of test_swept_levels do sweep, but for the one whose long
+    nets leave the bitmaps no room: its levels are expanded from their lists.
+    With enough short nets added the bitmaps fit, while the first 2,048 nets,
+    one workgroup's, still set aside more long ones than it has room for."""
+    hg = _swept(V + E, V, E, long_nets, hubs)
+    _say(f"swept levels counted V={V} E={E}")
+    if V == 9000:
+        sizes = np.diff(hg.net_offsets)[:2048]
+        assert (sizes - 4 > 192).sum() > 512
+    r = oracle_mod.maxflow(hg)
+    F, vs, ns, st = gpu_solve(hf, hg, bottom_up_min=1, tail_threshold=1)
+    assert_same(hg, r, F, vs, ns, f"swept {V} {E}")
+    assert (st["swept_levels"] > 0) == sweeps
+    F, vs, ns, st = gpu_solve(hf, hg, bottom_up_min=-1)
+    assert_same(hg, r, F, vs, ns, f"claimed {V} {E}")
+    assert st["swept_levels"] == 0
+
+
+@pytest.mark.parametrize("opts", [
+    dict(bottom_up_min=3000), dict(bottom_up_min=3000, tail_threshold=1),
+    dict(bfs_arc_parallel=1, bottom_up_min=1, tail_threshold=1),
+    dict(bfs_arc_parallel=1, bottom_up_min=3000),
+    dict(bfs_marks=1, bottom_up_min=1, tail_threshold=1),
+    dict(bfs_flat=-1, bottom_up_min=3000), dict(bfs_xcd=2, bottom_up_min=3000)], ids=str)
+def test_levels_around_the_threshold(hf, oracle_mod, opts):
+    """Searches that enter and leave swept or expanded levels on the way, and
+    the expanded form of every kind of level: none of these is reached at a
+    small network's default threshold."""
+    test_schedule_invariance(hf, oracle_mod, opts)
+    test_labels_and_preflow_certificate(hf, oracle_mod, opts)
+    hg = inputs.zipf_hypergraph(4, num_vertices=30000, num_nets=60000, size_hi=500)
+    F, vs, ns, st = gpu_solve(hf, hg, **opts)
+    forms = ("bfs_arc_parallel", "bfs_marks", "bfs_flat", "bfs_xcd")
+    assert (st["swept_levels"] > 0) == (not any(f in opts for f in forms))
+    assert st["bfs_levels"] > st["swept_levels"]

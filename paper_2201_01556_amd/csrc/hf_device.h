@@ -1202,10 +1202,10 @@ __device__ __forceinline__ int xslice(int v) { return (v >> 10) & (kSlices - 1);
 // or, with kSlice, only pre-checked against the labelled bitmap and handed
 // to its slice (xpush); the slice kernel then labels it on the XCD that
 // owns it.
-template <bool kClaim, bool kChecked = false, bool kSlice = false>
+template <bool kChecked, bool kSlice>
 __device__ __forceinline__ bool visit_rev(const Dev& g, int v, int lvl) {
   if (kSlice) return kChecked ? true : !seen_bit(g, v);
-  return label_rev<kClaim, kChecked>(g, v, lvl);
+  return label_rev<false, kChecked>(g, v, lvl);
 }
 
 // Append arc head t (where pred) to this workgroup's segment of its slice:
@@ -1232,13 +1232,12 @@ __device__ __forceinline__ void xpush(const Dev& g, lds_int* xc, int t, bool pre
   }
 }
 
-// Node-grouped reverse BFS: a group of `stride` lanes scans node x (G lanes
+// Node of an expanded level: a group of `stride` lanes scans node x (G lanes
 // per small node, a wave per big node, the workgroup per huge node); gl is
 // the lane's index in the group.
-template <bool kClaim, bool kSlice = false>
-__device__ __forceinline__ void bfs_rev_node(const Dev& g, const BlockQ& q, int x, bool has,
-                                             int gl, int stride, int lvl, uint32_t& nbytes,
-                                             lds_int* xc = nullptr) {
+template <bool kSlice = false>
+__device__ __forceinline__ void bfs_rev_node(const Dev& g, int x, bool has, int gl, int stride,
+                                             int lvl, uint32_t& nbytes, lds_int* xc = nullptr) {
   const bool isv = has && x < g.V;
   const bool isnet = has && x >= g.NB;
   if (!has || isv) {
@@ -1258,13 +1257,9 @@ __device__ __forceinline__ void bfs_rev_node(const Dev& g, const BlockQ& q, int 
         // bits of e_in and e_out share a word (NB and 2e are even)
         const uint32_t sw = g.seen[t1 >> 5] >> (t1 & 31);
         nbytes += 12;
-        if (!(sw & 2u)) vout = visit_rev<kClaim, true, kSlice>(g, t1 + 1, lvl);  // e_out -> x infinite
+        if (!(sw & 2u)) vout = visit_rev<true, kSlice>(g, t1 + 1, lvl);  // e_out -> x infinite
         if (!(sw & 1u) && pin_flow_in(g, ep.y))                    // e_in -> x reverse
-          vin = visit_rev<kClaim, true, kSlice>(g, t1, lvl);
-      }
-      if (kClaim) {
-        qpush(g, q, t1, vin);
-        qpush(g, q, t1 + 1, vout);
+          vin = visit_rev<true, kSlice>(g, t1, lvl);
       }
       if (kSlice) {
         xpush(g, xc, t1, vin, lvl);
@@ -1282,10 +1277,9 @@ __device__ __forceinline__ void bfs_rev_node(const Dev& g, const BlockQ& q, int 
     if (gl == 0) nbytes += 16;
     bool vb = false;
     if (gl == 0) {
-      if (in) vb = (nb & 4u) && visit_rev<kClaim, false, kSlice>(g, x + 1, lvl);  // e_out -> e_in residual fb
-      else vb = (nb & 1u) && visit_rev<kClaim, false, kSlice>(g, x - 1, lvl);     // e_in -> e_out residual w - fb
+      if (in) vb = (nb & 4u) && visit_rev<false, kSlice>(g, x + 1, lvl);  // e_out -> e_in residual fb
+      else vb = (nb & 1u) && visit_rev<false, kSlice>(g, x - 1, lvl);     // e_in -> e_out residual w - fb
     }
-    if (kClaim) qpush(g, q, in ? x + 1 : x - 1, vb);
     if (kSlice) xpush(g, xc, in ? x + 1 : x - 1, vb, lvl);
     for (int base = beg; base < end; base += stride) {
       const int i = base + gl;
@@ -1296,9 +1290,8 @@ __device__ __forceinline__ void bfs_rev_node(const Dev& g, const BlockQ& q, int 
         u = g.pin_v[i];
         const int f = g.fpin[2 * i + (in ? 0 : 1)];  // r_in (u->e_in) or f_out (u->e_out)
         nbytes += 12;
-        if (f > 0) vu = visit_rev<kClaim, false, kSlice>(g, u, lvl);
+        if (f > 0) vu = visit_rev<false, kSlice>(g, u, lvl);
       }
-      if (kClaim) qpush(g, q, u, vu);
       if (kSlice) xpush(g, xc, u, vu, lvl);
     }
   }
@@ -1540,7 +1533,7 @@ __device__ void phase_bfs_node(const Dev& g, int level, int ep, int ep_tmp, int 
       bfs_claim_node<kDir>(g, q, v, has, gl, stride, kDir == kDirRelabel ? level + 1 : ep, nbytes);
     else if constexpr (kDir == kDirSource)
       bfs_fwd_node(g, v, has, gl, stride, ep, ep_tmp, nbytes);
-    else bfs_rev_node<kClaim>(g, q, v, has, gl, stride, level + 1, nbytes);
+    else bfs_rev_node(g, v, has, gl, stride, level + 1, nbytes);
     if (kClaim) bq_tile_end(q, q.cap / 2);
   }
   if (kClaim) bq_flush(q);
@@ -1569,14 +1562,13 @@ __device__ void phase_bfs_rev_node(const Dev& g, int level, int tile0, int tstri
 // huge nodes the workgroup, as in the node-grouped levels.
 // ---------------------------------------------------------------------------
 
-template <bool kClaim, bool kSlice = false>
+template <bool kSlice = false>
 __device__ __forceinline__ void phase_bfs_rev_flat(const Dev& g, int level, int tile0, int tstride,
                                                    int kc, lds_int* lds) {
-  const int c3 = level % 3, n3 = (level + 1) % 3, z3 = (level + 2) % 3;
+  const int c3 = level % 3, z3 = (level + 2) % 3;
   if (tile0 == 0 && threadIdx.x < kNL) g.ctl->bcnt[z3][threadIdx.x] = 0;
-  const int cp = level & 1, np = (level + 1) & 1;
-  const BlockQ q = bq_bind(lds, g.ctl->bcnt[n3], g.list[np]);
-  lds_int* const xc = lds + bq_words();  // slice counts (in the arc-tile area, unused here)
+  const int cp = level & 1;
+  lds_int* const xc = lds;  // slice counts
   if (kSlice) {
     if (threadIdx.x < kSlices) xc[threadIdx.x] = 0;
     __syncthreads();
@@ -1648,16 +1640,16 @@ __device__ __forceinline__ void phase_bfs_rev_flat(const Dev& g, int level, int 
               // bits of e_in and e_out share a word (NB and 2e are even)
               const uint32_t sw = g.seen[t1 >> 5] >> (t1 & 31);
               nbytes += 12;
-              if (!(sw & 2u)) v2 = visit_rev<kClaim, true, kSlice>(g, t2, lvl);  // e_out -> x infinite
+              if (!(sw & 2u)) v2 = visit_rev<true, kSlice>(g, t2, lvl);  // e_out -> x infinite
               if (!(sw & 1u) && pin_flow_in(g, ep.y))                    // e_in -> x reverse
-                v1 = visit_rev<kClaim, true, kSlice>(g, t1, lvl);
+                v1 = visit_rev<true, kSlice>(g, t1, lvl);
             } else if (j == 0) {
               if (k == 1) {
                 t1 = xo + 1;  // e_out -> e_in residual fb
-                v1 = (nbo & 4u) && visit_rev<kClaim, false, kSlice>(g, t1, lvl);
+                v1 = (nbo & 4u) && visit_rev<false, kSlice>(g, t1, lvl);
               } else {
                 t1 = xo - 1;  // e_in -> e_out residual w - fb
-                v1 = (nbo & 1u) && visit_rev<kClaim, false, kSlice>(g, t1, lvl);
+                v1 = (nbo & 1u) && visit_rev<false, kSlice>(g, t1, lvl);
               }
             } else {
               const int i = bo + j - 1;
@@ -1665,12 +1657,8 @@ __device__ __forceinline__ void phase_bfs_rev_flat(const Dev& g, int level, int 
               // r_in (u -> e_in) or f_out (u -> e_out)
               const int f = g.fpin[2 * i + (k == 1 ? 0 : 1)];
               nbytes += 12;
-              if (f > 0) v1 = visit_rev<kClaim, false, kSlice>(g, t1, lvl);
+              if (f > 0) v1 = visit_rev<false, kSlice>(g, t1, lvl);
             }
-          }
-          if (kClaim) {
-            qpush(g, q, t1, v1);
-            qpush(g, q, t2, v2);
           }
           if (kSlice) {
             xpush(g, xc, t1, v1, lvl);
@@ -1681,17 +1669,15 @@ __device__ __forceinline__ void phase_bfs_rev_flat(const Dev& g, int level, int 
         const int v = g.list[cp][kBigList][it - s3];
         const bool has = !is_huge(g, v);
         nitems += has && lane == 0;
-        bfs_rev_node<kClaim, kSlice>(g, q, v, has, lane, kWave, lvl, nbytes, xc);
+        bfs_rev_node<kSlice>(g, v, has, lane, kWave, lvl, nbytes, xc);
       }
     } else {
       const int v = g.list[cp][kBigList][tile - ntiles];
       const bool has = is_huge(g, v);  // block-uniform
       nitems += has && threadIdx.x == 0;
-      bfs_rev_node<kClaim, kSlice>(g, q, v, has, threadIdx.x, blockDim.x, lvl, nbytes, xc);
+      bfs_rev_node<kSlice>(g, v, has, threadIdx.x, blockDim.x, lvl, nbytes, xc);
     }
-    if (kClaim) bq_tile_end(q, q.cap / 2);
   }
-  if (kClaim) bq_flush(q);
   if (kSlice) {
     __syncthreads();
     if (threadIdx.x < kSlices)

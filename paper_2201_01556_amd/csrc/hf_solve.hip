@@ -99,7 +99,7 @@ k_bfs_rev_flat(Dev g, int level, int big_min, int pull_min, int tail) {
     if (blockIdx.x == 0 && threadIdx.x < kNL) g.ctl->bcnt[(level + 2) % 3][threadIdx.x] = 0;
     if (blockIdx.x == 0 && threadIdx.x < 3) g.ctl->sweep_n[level & 1][threadIdx.x] = 0;
   } else if (!g.pinfree && nf >= big_min)
-    phase_bfs_rev_flat<false>(g, level, blockIdx.x, gridDim.x, KC_BFS_REV, lds);
+    phase_bfs_rev_flat(g, level, blockIdx.x, gridDim.x, KC_BFS_REV, lds);
   else phase_bfs_rev_node<G, true>(g, level, blockIdx.x, gridDim.x, KC_BFS_REV, lds);
 }
 
@@ -160,7 +160,7 @@ k_bfs_rev_xflat(Dev g, int level, int big_min, int pull_min, int tail) {
     phase_bfs_rev_pull(g, level, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x,
                        KC_BFS_REV);
   else if (nf >= big_min)
-    phase_bfs_rev_flat<false, true>(g, level, blockIdx.x, gridDim.x, KC_BFS_REV, lds);
+    phase_bfs_rev_flat<true>(g, level, blockIdx.x, gridDim.x, KC_BFS_REV, lds);
   else phase_bfs_rev_node<G, true>(g, level, blockIdx.x, gridDim.x, KC_BFS_REV, lds);
 }
 

@@ -359,9 +359,10 @@ void flow_batch_destroy(fp_batch *batch);
 
 /*
  * flow_release_cached_memory: free the device pools and pinned control
- * blocks that destroyed handles and region builds left for reuse.  Handles keep working; the
- * library keeps at most 4 GiB of released pools per process and reuses a
- * block for a new handle it covers without wasting more than half of it.
+ * blocks that destroyed handles and region builds left for reuse.  Handles
+ * keep working; the library keeps at most 4 GiB of released pools per process
+ * and reuses a block for a new handle it covers without wasting more than half
+ * of it.
  * Waits for the current device to be idle.
  */
 void flow_release_cached_memory(void);

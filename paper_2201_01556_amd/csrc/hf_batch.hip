@@ -1,6 +1,6 @@
 // Batched solve of many independent flow problems (the paper's refinement
 // runs many block-pair flow problems at once, section "Parallel Active Block
-// Scheduling").  Two schedules, both with the single-problem device phases:
+// Scheduling").  Three schedules, all with the single-problem device phases:
 //   union    the kept problems are copied into one network, their disjoint
 //            union, solved once with the device-wide kernels: one global
 //            relabel is one BFS over every problem, one round discharges all
@@ -9,7 +9,9 @@
 //   workers  host workers take problems from a shared queue, largest first,
 //            and drive the single-problem path on HIP streams of their own,
 //            so the kernels and host round trips of different problems
-//            overlap.
+//            overlap;
+//   workgroups  one persistent launch whose workgroups take problems from a
+//            shared counter and solve each alone.
 // Results are identical.
 #include <algorithm>
 #include <atomic>
@@ -319,11 +321,10 @@ __global__ void __launch_bounds__(256) k_union_pins(const Dev* devs, UnionMap m,
 }
 
 // Terminal lists of the union from the problems' current roles (piercing
-// included); list order does not matter.
-// The union's sources and sinks.  A workgroup counts those of 2,048 vertices,
-// reserves their places with one atomic per kind and writes them: with an
-// atomic per terminal the two counters, one address each, took 611 us for 512
-// problems (49k terminals).
+// included); list order does not matter.  A workgroup counts the sources and
+// sinks of 2,048 vertices, reserves their places with one atomic per kind and
+// writes them: with an atomic per terminal the two counters, one address each,
+// took 611 us for 512 problems (49k terminals).
 constexpr int kUnionTile = 8;  // vertices per thread
 __global__ void __launch_bounds__(256) k_union_terminals(const Dev* devs, UnionMap m, int32_t V,
                                                          int32_t* src, int32_t* snk,
@@ -372,6 +373,8 @@ __global__ void __launch_bounds__(256) k_union_terminals(const Dev* devs, UnionM
   }
 }
 
+// Flow value of kept problem blockIdx.x: weight of its nets with e_in on the
+// source side and e_out not (bit0 set, bit1 clear).
 __global__ void __launch_bounds__(256) k_union_flows(UnionMap m, const int32_t* w,
                                                      const uint8_t* nside,
                                                      unsigned long long* flows) {

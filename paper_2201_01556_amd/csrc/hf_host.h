@@ -177,8 +177,9 @@ inline bool dear_relabels(long long N, bool swept) { return N >= kSweepNodes && 
 // 3.0 / - / 2.7 at 44k (720k pins); nets of 200 and 500 pins, N = 40k to 140k, 3.1 to
 // 4.1 against 3.8 to 5.3; nets of 20 and 30 pins are faster with claims.
 //
-// gr_interval, rounds between global relabels.  Intervals 16 (64 in the
-// single-workgroup loop) / 10 (24) / 8 (24), means over eight seeds in us: V = 2k
+// gr_interval, rounds between global relabels (in the single-workgroup loop
+// 25 by default, tail_rounds; measured at 24).  Intervals 16 (64 in the loop) / 10
+// (24) / 8 (24), means over eight seeds in us: V = 2k
 // 2121 / 2123 / 2087, 12k 3840 / 3681 / 3524, 40k 5475 / 4831 / 4892, 100k
 // 7166 / 6412 / 6517, 300k 9894 / 8764 / 9430, 1M 15671 / 15330 / 16403,
 // region problems of 5k, 20k and 40k vertices 2505 / 2489 / 2470,

@@ -797,10 +797,9 @@ __global__ void k_rg_alive_sizes(long long nk, const long long* koff, const int3
 }
 
 // Nets and pins left per pair: the kept nets of a pair are consecutive, so
-// the scans of the alive flags and sizes at the pairs' bounds give both.
-// (Two atomics per net on 500 pairs' counters, which a wave's nets share,
-// took 15.1 ms for 500 pairs of a
-// 2 M-vertex, 10 M-pin hypergraph.)
+// the scans of the alive flags and sizes at the pairs' bounds give both (two
+// atomics per net on the pairs' counters, which a wave's nets share, took 15.1
+// ms for 500 pairs of a 2 M-vertex, 10 M-pin hypergraph).
 __global__ void k_rg_alive_per_pair(int npairs, const long long* tbase, int nt,
                                     const int32_t* kidx, const long long* fidx,
                                     const long long* fpos, unsigned long long* ne,
@@ -817,7 +816,9 @@ __global__ void k_rg_alive_per_pair(int npairs, const long long* tbase, int nt,
 // consecutive in the output; a lane finds its pin's net by binary search over
 // the wave's prefix sums), and keeps the seven size counts of its current
 // pair in lanes 0..6 until the pair changes.  `per` (a multiple of 64) nets
-// per wave.  500 pairs of a 2 M-vertex, 10 M-pin hypergraph: 4.1 -> 0.54 ms
+// per wave.  The prefix sums fit an int although the 64 nets may belong to many
+// pairs: the kept pins of all pairs are fewer than 2^31 (checked when they are
+// counted).  500 pairs of a 2 M-vertex, 10 M-pin hypergraph: 4.1 -> 0.54 ms
 // against a thread per net and an atomic per net on its pair's counters.
 __global__ void __launch_bounds__(256) k_rg_final(long long nk, long long per,
                                                   const long long* koff, const int32_t* kpins,

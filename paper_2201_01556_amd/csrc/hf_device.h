@@ -1454,14 +1454,21 @@ __device__ __forceinline__ void bfs_claim_node(const Dev& g, const BlockQ& q, in
           want = f > 0 && !seen_bit(g, u);
         } else {
           const int2 fp = *reinterpret_cast<const int2*>(g.fpin + 2 * i);
-          const int st = g.stamp[u], r = g.role[u];
+          // the flows come with the vertex, so looking at them first lengthens
+          // no chain; few of a net node's reverse arcs exist, and each stamp
+          // and role is a line of its own
           if (kDir == kDirSource) {  // e_in -> u reverse, e_out -> u infinite
-            want = (in ? we - fp.x > 0 : r == 0) && st != val;
-            if (!in && r == 2) atomicOr(&g.ctl->err, ERR_SINK_REACHED);
-          } else {  // u -> e_in always, u -> e_out by flow
-            const bool arc = in || fp.y > 0;
-            want = arc && r != 1 && st != val;
-            if (arc && r == 1) atomicOr(&g.ctl->err, ERR_SOURCE_REACHED);
+            if (in) {
+              want = we - fp.x > 0 && g.stamp[u] != val;
+            } else {
+              const int st = g.stamp[u], r = g.role[u];
+              want = r == 0 && st != val;
+              if (r == 2) atomicOr(&g.ctl->err, ERR_SINK_REACHED);
+            }
+          } else if (in || fp.y > 0) {  // u -> e_in always, u -> e_out by flow
+            const int st = g.stamp[u], r = g.role[u];
+            want = r != 1 && st != val;
+            if (r == 1) atomicOr(&g.ctl->err, ERR_SOURCE_REACHED);
           }
         }
       }

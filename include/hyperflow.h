@@ -103,7 +103,8 @@ typedef struct {
                                  or nets with far more pins than there are
                                  nodes), they are expanded and collected.
                                  Default from 1048576 nodes on: N/16 (at least
-                                 262144) if swept, else N/50; with fewer
+                                 262144) if swept, else (and in the forward
+                                 BFS) N/50; with fewer
                                  nodes N/50 (at least 1024) from 2097152 pins
                                  and 16 pins per node on, else never; -1 =
                                  never                                       */

@@ -488,7 +488,9 @@ static void launch_levels(fp_problem* pb, hipStream_t s, int ep, int ep_tmp, int
                           int steps, bool predict, bool small) {
   Dev& g = pb->dev;
   const int cap = pb->opt.tail_threshold;
-  const int big_min = pb->opt.bottom_up_min > 0 ? pb->opt.bottom_up_min : (1 << 30);
+  const int level_min =
+      mode == 1 ? forward_min(pb->opt, pb->opt_user, g.N) : pb->opt.bottom_up_min;
+  const int big_min = level_min > 0 ? level_min : (1 << 30);
   const int pull_min = pb->opt.pull_min > 0 ? pb->opt.pull_min : (1 << 30);
   const int off = 1 << 30;
   // largest size expected of a level, from the previous relabel; -1 unknown

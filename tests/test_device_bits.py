@@ -99,8 +99,10 @@ int main() {
     o.tail_gr_interval = tail;
     const long long N = ((V + 1) & ~1ll) + 2 * E;
     const bool swept = hf::levels_swept(o, hf::SweepMaps(V, E, P, N));
+    const fp_options user = o;
     hf::resolve_by_size(&o, V, E, P, N);
     printf("%d %d %d\n", o.bottom_up_min, o.gr_interval, hf::tail_rounds(o, N, swept));
+    fprintf(stderr, "%d\n", hf::forward_min(o, user, N));
   }
   return 0;
 }
@@ -141,6 +143,12 @@ def test_defaults_by_size_and_form(tmp_path):
     r = subprocess.run([build.HIPCC, *build.FLAGS, str(src), "-o", str(exe)],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
-    out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c, _ in table),
-                         capture_output=True, text=True, check=True).stdout.splitlines()
+    run = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c, _ in table),
+                         capture_output=True, text=True, check=True)
+    out = run.stdout.splitlines()
     assert [tuple(map(int, line.split())) for line in out] == [want for _, want in table]
+    # the forward search: N/50 in large networks by default, else the same
+    for (c, want), forward in zip(table, map(int, run.stderr.split())):
+        n = ((c[0] + 1) & ~1) + 2 * c[1]
+        default = c[6] == 0 and n >= 1 << 20
+        assert forward == (n // 50 if default else want[0]), c
